@@ -175,6 +175,7 @@ rh_status rh_network_destroy(rh_network *net) {
   if (!net) return RH_OK;
   device_newton_free(net->n);
   device_track_free(net->n);
+  device_tree_free(net->n);
   device_free(net->n);
   delete net;
   return RH_OK;
@@ -252,6 +253,7 @@ rh_status rh_solve_powerflow(rh_network *net, double tol, int32_t max_iter, int3
   GUARD_BEGIN
   if (!net) return fail(RH_EINVAL, "null network");
   std::string err;
+  device_newton_stale(net->n);
   rh_status s = network_solve(net->n, tol, max_iter, err);
   if (iters) *iters = net->n.newton_iters;
   if (resid_inf) *resid_inf = net->n.newton_resid;
@@ -559,7 +561,7 @@ rh_status rh_network_device_bytes(const rh_network *net, rh_precision prec, int6
   if (!net) return fail(RH_EINVAL, "null network");
   if (prec != RH_FP64 && prec != RH_FP32_REFINED) return fail(RH_EINVAL, "unknown precision");
   if (resident) *resident = device_network_bytes(net->n);
-  if (scratch_per_direction) *scratch_per_direction = device_scratch_per_direction(net->n.n_x, prec);
+  if (scratch_per_direction) *scratch_per_direction = device_scratch_per_direction(net->n, prec);
   return RH_OK;
 }
 

@@ -46,6 +46,7 @@
 #include <thread>
 
 #include "rh_internal.h"
+#include "tree_device.h"
 
 // Launch scratch of the allocation-free entry point (rh_hvp_device_noalloc):
 // one fixed array per GPU, held from the code object's load until the process
@@ -1520,6 +1521,9 @@ struct Runner {
   WorkItem *items_dev = nullptr, *items_host = nullptr;
   int32_t items_cap = 0;
   hipEvent_t items_done = nullptr;  // the last launch that read the work list
+  TreeItem *titems_dev = nullptr, *titems_host = nullptr;  // the tree path's work list
+  int32_t titems_cap = 0;
+  hipEvent_t titems_done = nullptr;
   int32_t launches = 0, last_c = 0;
   long long *step_stamps = nullptr;  // debug (RH_STEP_STAMPS)
   bool step_stamps_pending = false;
@@ -1548,6 +1552,9 @@ void runner_free(Runner &r) {
   if (r.items_dev) (void)hipFree(r.items_dev);
   if (r.items_host) (void)hipHostFree(r.items_host);
   if (r.items_done) (void)hipEventDestroy(r.items_done);
+  if (r.titems_dev) (void)hipFree(r.titems_dev);
+  if (r.titems_host) (void)hipHostFree(r.titems_host);
+  if (r.titems_done) (void)hipEventDestroy(r.titems_done);
   if (r.step_stamps) (void)hipFree(r.step_stamps);
   r = Runner();
 }
@@ -1786,6 +1793,106 @@ rh_status launch_plan(const LaunchPlan &pl, int32_t groups, hipStream_t s, const
   }
 }
 
+rh_status grow_scratch(Runner &r, size_t need, hipStream_t s, std::string &err) {
+  if (need <= r.scratch_bytes) return RH_OK;
+  HIP_TRY(hipStreamSynchronize(s));  // earlier work on this stream may still use it
+  if (r.scratch) HIP_TRY(hipFree(r.scratch));
+  r.scratch = nullptr;
+  r.scratch_bytes = 0;
+  void *p = nullptr;
+  HIP_TRY(hipMalloc(&p, need));
+  r.scratch = (double *)p;
+  r.scratch_bytes = need;
+  return RH_OK;
+}
+
+// The next pair of timing events of a runner.
+rh_status timing_events(Runner &r, hipEvent_t &e0, hipEvent_t &e1, std::string &err) {
+  while (r.ev.size() < r.ev_used + 2) {
+    hipEvent_t e;
+    HIP_TRY(hipEventCreate(&e));
+    r.ev.push_back(e);
+  }
+  e0 = r.ev[r.ev_used];
+  e1 = r.ev[r.ev_used + 1];
+  r.ev_used += 2;
+  return RH_OK;
+}
+
+rh_status grow_stamps(Runner &r, int32_t groups, hipStream_t s, std::string &err) {
+  if (r.stamps_cap >= groups) return RH_OK;
+  HIP_TRY(hipStreamSynchronize(s));
+  if (r.stamps) HIP_TRY(hipFree(r.stamps));
+  r.stamps = nullptr;
+  r.stamps_cap = 0;
+  HIP_TRY(hipMalloc(&r.stamps, (size_t)groups * kStamps * sizeof(long long)));
+  r.stamps_cap = groups;
+  return RH_OK;
+}
+
+// The tree path's launches for a list of requests (a sequence of kernels that
+// counts as one launch of the reduction).
+rh_status run_tree(Runner &r, int32_t timing, int32_t refine, double refine_tol, const std::vector<TreeRequest> &req,
+                   hipStream_t s, std::string &err, const FixedScratch *fixed = nullptr) {
+  TreeShape sh = tree_shape(req, refine);
+  if (sh.chunks == 0) return RH_OK;
+  if (fixed) {
+    // chunks in more rounds when the fixed range is short
+    TreeShape one = sh;
+    one.round = 1;
+    const int64_t fit = fixed->bytes / (int64_t)one.scratch_bytes();
+    if (fit < 1) {
+      err = "network too large for the fixed scratch: 16 directions need " + std::to_string(one.scratch_bytes()) +
+            " bytes, " + std::to_string(fixed->bytes) + " available";
+      return RH_EINVAL;
+    }
+    sh.round = (int32_t)std::min<int64_t>(sh.round, fit);
+    timing = 0;
+  } else {
+    const rh_status gs = grow_scratch(r, sh.scratch_bytes(), s, err);
+    if (gs != RH_OK) return gs;
+  }
+  std::vector<TreeItem> items;
+  tree_items(req, sh, items);
+  if (req.size() > 1) {  // (a single request travels by value)
+    if ((int32_t)items.size() > r.titems_cap) {
+      HIP_TRY(hipStreamSynchronize(s));
+      if (r.titems_dev) HIP_TRY(hipFree(r.titems_dev));
+      if (r.titems_host) HIP_TRY(hipHostFree(r.titems_host));
+      r.titems_dev = r.titems_host = nullptr;
+      r.titems_cap = 0;
+      HIP_TRY(hipMalloc(&r.titems_dev, items.size() * sizeof(TreeItem)));
+      HIP_TRY(hipHostMalloc(&r.titems_host, items.size() * sizeof(TreeItem), hipHostMallocDefault));
+      r.titems_cap = (int32_t)items.size();
+    }
+    if (!r.titems_done) HIP_TRY(hipEventCreateWithFlags(&r.titems_done, hipEventDisableTiming));
+    HIP_TRY(hipEventSynchronize(r.titems_done));  // the previous list is no longer read
+    std::memcpy(r.titems_host, items.data(), items.size() * sizeof(TreeItem));
+    HIP_TRY(hipMemcpyAsync(r.titems_dev, r.titems_host, items.size() * sizeof(TreeItem), hipMemcpyHostToDevice, s));
+  }
+  long long *stamps = nullptr;
+  if (timing >= 2) {
+    const rh_status gs = grow_stamps(r, 1, s, err);
+    if (gs != RH_OK) return gs;
+    stamps = r.stamps;
+    r.stamps_groups = 1;
+  }
+  hipEvent_t e0 = nullptr, e1 = nullptr;
+  if (timing >= 1) {
+    const rh_status es = timing_events(r, e0, e1, err);
+    if (es != RH_OK) return es;
+    HIP_TRY(hipEventRecord(e0, s));
+  }
+  const rh_status st = tree_launch(req, items, r.titems_dev, sh, fixed ? fixed->ptr : r.scratch, refine, refine_tol,
+                                   stamps, s, err);
+  if (st != RH_OK) return st;
+  if (req.size() > 1) HIP_TRY(hipEventRecord(r.titems_done, s));
+  if (timing >= 1) HIP_TRY(hipEventRecord(e1, s));
+  r.launches += 1;
+  r.last_c = kTreeDirs;
+  return RH_OK;
+}
+
 rh_status run_items(const DeviceInfo &info, Runner &r, int32_t timing, int32_t refine, double refine_tol,
                     std::vector<WorkItem> &items, int32_t max_nx, hipStream_t s, std::string &err,
                     const FixedScratch *fixed = nullptr, int32_t force_c = 0) {
@@ -1812,16 +1919,9 @@ rh_status run_items(const DeviceInfo &info, Runner &r, int32_t timing, int32_t r
     groups = (int32_t)std::min<int64_t>(groups, fit);
     timing = 0;
   }
-  const size_t need = (size_t)groups * stride * sizeof(double);
-  if (!fixed && need > r.scratch_bytes) {
-    HIP_TRY(hipStreamSynchronize(s));  // earlier work on this stream may still use it
-    if (r.scratch) HIP_TRY(hipFree(r.scratch));
-    r.scratch = nullptr;
-    r.scratch_bytes = 0;
-    void *p = nullptr;
-    HIP_TRY(hipMalloc(&p, need));
-    r.scratch = (double *)p;
-    r.scratch_bytes = need;
+  if (!fixed) {
+    const rh_status gs = grow_scratch(r, (size_t)groups * stride * sizeof(double), s, err);
+    if (gs != RH_OK) return gs;
   }
   LaunchArgs la{};
   la.refine = refine;
@@ -1861,27 +1961,15 @@ rh_status run_items(const DeviceInfo &info, Runner &r, int32_t timing, int32_t r
   }
   la.stamps = nullptr;
   if (timing >= 2) {
-    if (r.stamps_cap < groups) {
-      HIP_TRY(hipStreamSynchronize(s));
-      if (r.stamps) HIP_TRY(hipFree(r.stamps));
-      r.stamps = nullptr;
-      r.stamps_cap = 0;
-      HIP_TRY(hipMalloc(&r.stamps, (size_t)groups * kStamps * sizeof(long long)));
-      r.stamps_cap = groups;
-    }
+    const rh_status gs = grow_stamps(r, groups, s, err);
+    if (gs != RH_OK) return gs;
     la.stamps = r.stamps;
     r.stamps_groups = groups;
   }
   hipEvent_t e0 = nullptr, e1 = nullptr;
   if (timing >= 1) {
-    while (r.ev.size() < r.ev_used + 2) {
-      hipEvent_t e;
-      HIP_TRY(hipEventCreate(&e));
-      r.ev.push_back(e);
-    }
-    e0 = r.ev[r.ev_used];
-    e1 = r.ev[r.ev_used + 1];
-    r.ev_used += 2;
+    const rh_status es = timing_events(r, e0, e1, err);
+    if (es != RH_OK) return es;
     HIP_TRY(hipEventRecord(e0, s));
   }
   const rh_status st = launch_plan(pl, groups, s, la, err);
@@ -1912,6 +2000,8 @@ struct DeviceNet {
   std::multimap<size_t, void *> pool;
   DeviceInfo info;
   Runner run;
+  bool tree = false;    // the products take the tree path
+  bool groups = false;  // the arrays of the one-workgroup path are uploaded
 };
 
 // A context's resources for batched launches: one runner per stream, since
@@ -2352,41 +2442,68 @@ rh_status device_ctx_collect(Context &ctx, rh_report &rep, std::string &err) {
   return RH_OK;
 }
 
-rh_status device_upload(Network &net, std::string &err, const std::function<rh_status(std::string &)> &accept) {
-  HIP_TRY(hipSetDevice(net.ctx->device));
-  Runner keep;  // keep the launch resources across operating points
-  double *keep_rinfo = nullptr;
-  int64_t keep_cols = 0;
-  std::multimap<size_t, void *> pool;  // and the arrays' device memory (see DeviceNet::pool)
-  if (net.dev) {
-    keep = net.dev->run;
-    net.dev->run = Runner();
-    keep_rinfo = net.dev->rinfo;
-    keep_cols = net.dev->rinfo_cols;
-    net.dev->rinfo = nullptr;
-    (void)hipDeviceSynchronize();  // no kernel uses them any more
-    for (size_t q = 0; q < net.dev->allocs.size(); ++q)
-      pool.emplace(net.dev->alloc_bytes[q], net.dev->allocs[q]);
-    net.dev->allocs.clear();
-    net.dev->alloc_bytes.clear();
-    device_free(net);
-  }
-  DeviceNet *dn = new DeviceNet();
-  net.dev = dn;
-  ++net.dev_gen;
-  dn->run = keep;
-  dn->rinfo = keep_rinfo;
-  dn->rinfo_cols = keep_cols;
-  dn->pool = std::move(pool);
-  rh_status qs = query_info(net.ctx->device, dn->info, err);
-  if (qs != RH_OK) return qs;
+namespace {
 
+// Arrays that both paths read: G_p, G_p^T and the first-order adjoint.
+rh_status upload_common(Network &net, DeviceNet *dn, std::string &err) {
   NetDesc &nd = dn->nd;
   const LuPlan &lu = net.lu;
-  nd.n_x = net.n_x;
-  nd.n_p = net.n_p;
-  nd.n_bus = net.n_bus;
+  // G_p with rows in permuted order, and G_p^T with permuted columns
+  {
+    std::vector<int4> grows;
+    std::vector<int32_t> col;
+    std::vector<double> val;
+    for (int32_t ip = 0; ip < net.n_x; ++ip) {
+      const int32_t r = lu.perm[ip], e0 = (int32_t)col.size();
+      for (int32_t e = net.gp.ptr[r]; e < net.gp.ptr[r + 1]; ++e) {
+        col.push_back(net.gp.col[e]);
+        val.push_back(net.gp.val[e]);
+      }
+      if ((int32_t)col.size() > e0) grows.push_back(make_int4(ip, e0, (int32_t)col.size(), 0));
+    }
+    nd.n_gp_rows = (int32_t)grows.size();
+    UP(grows, nd.gp_rows);
+    UP(col, nd.gp_col);
+    UP(val, nd.gp_val);
+    std::vector<std::vector<std::pair<int32_t, double>>> rows(net.n_p);
+    for (int32_t r = 0; r < net.n_x; ++r)
+      for (int32_t e = net.gp.ptr[r]; e < net.gp.ptr[r + 1]; ++e)
+        rows[net.gp.col[e]].push_back({lu.iperm[r], net.gp.val[e]});
+    std::vector<int32_t> tptr(net.n_p + 1, 0), tcol;
+    std::vector<double> tval;
+    for (int32_t q = 0; q < net.n_p; ++q) {
+      std::sort(rows[q].begin(), rows[q].end());
+      for (auto &pr : rows[q]) {
+        tcol.push_back(pr.first);
+        tval.push_back(pr.second);
+      }
+      tptr[q + 1] = (int32_t)tcol.size();
+    }
+    std::vector<double> c2(net.n_p, std::numeric_limits<double>::quiet_NaN());
+    for (int32_t b : net.pv) c2[net.pg_p[b]] = 2.0 * net.c2[net.gen_of_bus[b]];
+    std::vector<double> lam_p(net.n_x);
+    for (int32_t ip = 0; ip < net.n_x; ++ip) lam_p[ip] = net.lam[lu.perm[ip]];
+    Blob bl;
+    const int64_t o_ptr = bl.add(tptr), o_col = bl.add(tcol), o_val = bl.add(tval), o_c2 = bl.add(c2);
+    const int64_t o_lam = bl.add(lam_p), o_fp = bl.add(net.fp);
+    const char *base = nullptr;
+    UP(bl.h, base);
+    nd.gpt_ptr = at_off<int32_t>(base, o_ptr);
+    nd.gpt_col = at_off<int32_t>(base, o_col);
+    nd.gpt_val = at_off<double>(base, o_val);
+    nd.p_c2x2 = at_off<double>(base, o_c2);
+    nd.lam = at_off<double>(base, o_lam);
+    nd.fp = at_off<double>(base, o_fp);
+  }
+  return RH_OK;
+}
 
+// Arrays of the one-workgroup path: the four sweeps, G_x and G_x^T, the
+// projection records.  `accept` as in device_upload.
+rh_status upload_groups(Network &net, DeviceNet *dn, const std::function<rh_status(std::string &)> &accept,
+                        std::string &err) {
+  NetDesc &nd = dn->nd;
+  const LuPlan &lu = net.lu;
   // The factors' sweeps read the factors only: they are prepared and
   // uploaded on a thread of their own while `accept` finishes the host side
   // of the solve.  On every way out of this function the guard joins the
@@ -2481,53 +2598,8 @@ rh_status device_upload(Network &net, std::string &err, const std::function<rh_s
       }
     });
 
-  // G_p with rows in permuted order, and G_p^T with permuted columns
-  {
-    std::vector<int4> grows;
-    std::vector<int32_t> col;
-    std::vector<double> val;
-    for (int32_t ip = 0; ip < net.n_x; ++ip) {
-      const int32_t r = lu.perm[ip], e0 = (int32_t)col.size();
-      for (int32_t e = net.gp.ptr[r]; e < net.gp.ptr[r + 1]; ++e) {
-        col.push_back(net.gp.col[e]);
-        val.push_back(net.gp.val[e]);
-      }
-      if ((int32_t)col.size() > e0) grows.push_back(make_int4(ip, e0, (int32_t)col.size(), 0));
-    }
-    nd.n_gp_rows = (int32_t)grows.size();
-    UP(grows, nd.gp_rows);
-    UP(col, nd.gp_col);
-    UP(val, nd.gp_val);
-    std::vector<std::vector<std::pair<int32_t, double>>> rows(net.n_p);
-    for (int32_t r = 0; r < net.n_x; ++r)
-      for (int32_t e = net.gp.ptr[r]; e < net.gp.ptr[r + 1]; ++e)
-        rows[net.gp.col[e]].push_back({lu.iperm[r], net.gp.val[e]});
-    std::vector<int32_t> tptr(net.n_p + 1, 0), tcol;
-    std::vector<double> tval;
-    for (int32_t q = 0; q < net.n_p; ++q) {
-      std::sort(rows[q].begin(), rows[q].end());
-      for (auto &pr : rows[q]) {
-        tcol.push_back(pr.first);
-        tval.push_back(pr.second);
-      }
-      tptr[q + 1] = (int32_t)tcol.size();
-    }
-    std::vector<double> c2(net.n_p, std::numeric_limits<double>::quiet_NaN());
-    for (int32_t b : net.pv) c2[net.pg_p[b]] = 2.0 * net.c2[net.gen_of_bus[b]];
-    std::vector<double> lam_p(net.n_x);
-    for (int32_t ip = 0; ip < net.n_x; ++ip) lam_p[ip] = net.lam[lu.perm[ip]];
-    Blob bl;
-    const int64_t o_ptr = bl.add(tptr), o_col = bl.add(tcol), o_val = bl.add(tval), o_c2 = bl.add(c2);
-    const int64_t o_lam = bl.add(lam_p), o_fp = bl.add(net.fp);
-    const char *base = nullptr;
-    UP(bl.h, base);
-    nd.gpt_ptr = at_off<int32_t>(base, o_ptr);
-    nd.gpt_col = at_off<int32_t>(base, o_col);
-    nd.gpt_val = at_off<double>(base, o_val);
-    nd.p_c2x2 = at_off<double>(base, o_c2);
-    nd.lam = at_off<double>(base, o_lam);
-    nd.fp = at_off<double>(base, o_fp);
-  }
+  const rh_status cs = upload_common(net, dn, err);
+  if (cs != RH_OK) return cs;
   // tangent sources per bus in permuted numbering: theta from X[thx] (-1 at
   // the reference bus); v from X[vs] at PQ buses, else from W[-vs - 1]
   std::vector<int32_t> thx(net.n_bus), vs(net.n_bus);
@@ -2632,6 +2704,104 @@ rh_status device_upload(Network &net, std::string &err, const std::function<rh_s
       err = ell_err[k];
       return ell_st[k];
     }
+  dn->groups = true;
+  return RH_OK;
+}
+
+// The smallest network of the tree path (tree.hip).  Its launches cost about
+// the same whatever the network's size, while the one-workgroup path takes as
+// long as its longest chain of dependent steps; neither depends on k until the
+// chip is full.  Measured in us, one-workgroup | tree:
+//   states           4,749       9,499       13,299      18,999      38,571
+//   FP64, k = 1      98 | 109   160 | 116   216 | 124   288 | 148  1627 | 204
+//   FP64, k = 256   103 | 154   169 | 187   221 | 214   296 | 262      -
+//   refined, k = 1  201 | 287   363 | 290   492 | 305   671 | 340  1321 | 470
+//   refined, k = 256 216 | 414  370 | 504   511 | 575   711 | 711      -
+// (256 directions are one workgroup per CU, the other path's best case.)  The
+// choice cannot depend on k, as a direction's bits may not, and both
+// precisions go one way, so that only one path's arrays are uploaded: the line
+// is where no case is slower.
+constexpr int32_t kTreeMinStates = 18000;
+
+bool tree_wanted(const Network &net) {
+  return net.n_x >= kTreeMinStates && !std::getenv("RH_DIRS_PER_GROUP") && !std::getenv("RH_NO_LDS");
+}
+
+// Whether the network's products take the tree path: chosen at the upload;
+// a launch shape forced through the environment asks for the one-workgroup
+// path, whose arrays are then uploaded on first use.
+bool tree_path(const Network &net) {
+  return net.dev->tree && !std::getenv("RH_DIRS_PER_GROUP") && !std::getenv("RH_NO_LDS");
+}
+
+rh_status need_groups(Network &net, std::string &err) {
+  DeviceNet *dn = net.dev;
+  if (dn->groups) return RH_OK;
+  HIP_TRY(hipSetDevice(net.ctx->device));
+  HIP_TRY(hipDeviceSynchronize());
+  const rh_status s = upload_groups(net, dn, nullptr, err);
+  if (s != RH_OK) return s;
+  HIP_TRY(hipMemcpy(dn->nd_dev, &dn->nd, sizeof dn->nd, hipMemcpyHostToDevice));
+  return RH_OK;
+}
+
+}  // namespace
+
+rh_status device_upload(Network &net, std::string &err, const std::function<rh_status(std::string &)> &accept) {
+  HIP_TRY(hipSetDevice(net.ctx->device));
+  Runner keep;  // keep the launch resources across operating points
+  double *keep_rinfo = nullptr;
+  int64_t keep_cols = 0;
+  std::multimap<size_t, void *> pool;  // and the arrays' device memory (see DeviceNet::pool)
+  if (net.dev) {
+    keep = net.dev->run;
+    net.dev->run = Runner();
+    keep_rinfo = net.dev->rinfo;
+    keep_cols = net.dev->rinfo_cols;
+    net.dev->rinfo = nullptr;
+    (void)hipDeviceSynchronize();  // no kernel uses them any more
+    for (size_t q = 0; q < net.dev->allocs.size(); ++q)
+      pool.emplace(net.dev->alloc_bytes[q], net.dev->allocs[q]);
+    net.dev->allocs.clear();
+    net.dev->alloc_bytes.clear();
+    device_free(net);
+  }
+  DeviceNet *dn = new DeviceNet();
+  net.dev = dn;
+  ++net.dev_gen;
+  dn->run = keep;
+  dn->rinfo = keep_rinfo;
+  dn->rinfo_cols = keep_cols;
+  dn->pool = std::move(pool);
+  rh_status qs = query_info(net.ctx->device, dn->info, err);
+  if (qs != RH_OK) return qs;
+
+  NetDesc &nd = dn->nd;
+  nd.n_x = net.n_x;
+  nd.n_p = net.n_p;
+  nd.n_bus = net.n_bus;
+
+  if (tree_wanted(net)) {
+    // the host side of the solve first: the tree path's values are filled on
+    // the device in a millisecond, so there is nothing to overlap it with
+    if (accept) {
+      const rh_status s = accept(err);
+      if (s != RH_OK) return s;
+    }
+    bool used = false;
+    rh_status s = tree_upload(net, device_newton_factors(net), &used, err);
+    if (s != RH_OK) return s;
+    if (used) {
+      dn->tree = true;
+      if ((s = upload_common(net, dn, err)) != RH_OK) return s;
+      tree_steps(net.dtree, net.report.steps_l, net.report.steps_u);
+    } else if ((s = upload_groups(net, dn, nullptr, err)) != RH_OK) {
+      return s;
+    }
+  } else {
+    const rh_status s = upload_groups(net, dn, accept, err);
+    if (s != RH_OK) return s;
+  }
   {
     const NetDesc *p = nullptr;
     const std::vector<NetDesc> one(1, dn->nd);
@@ -2713,9 +2883,16 @@ rh_status device_hvp(Network &net, int32_t k, const double *dW, int64_t ldw, dou
     }
     it.rinfo = dn->rinfo + 4 * (int64_t)(identity_from >= 0 ? identity_from : 0);
   }
-  const rh_tile &t = net.tile[prec == RH_FP32_REFINED ? 1 : 0];
-  rh_status s = run_items(dn->info, dn->run, net.ctx->timing, refine, net.ctx->refine_tol, items, net.n_x,
-                          (hipStream_t)stream, err, nullptr, t.k > 0 ? t.dirs_per_group : 0);
+  rh_status s;
+  if (tree_path(net)) {
+    s = run_tree(dn->run, net.ctx->timing, refine, net.ctx->refine_tol,
+                 {TreeRequest{net.dtree, dW, dHW, ldw, ldhw, k, identity_from, it.rinfo}}, (hipStream_t)stream, err);
+  } else {
+    if ((s = need_groups(net, err)) != RH_OK) return s;
+    const rh_tile &t = net.tile[prec == RH_FP32_REFINED ? 1 : 0];
+    s = run_items(dn->info, dn->run, net.ctx->timing, refine, net.ctx->refine_tol, items, net.n_x,
+                  (hipStream_t)stream, err, nullptr, t.k > 0 ? t.dirs_per_group : 0);
+  }
   net.report.dirs_per_group = dn->run.last_c;
   return s;
 }
@@ -2750,6 +2927,11 @@ rh_status device_hvp_noalloc(Network &net, int32_t k, const double *dW, int64_t 
   it.rinfo = nullptr;  // no per-column refinement figures
   const FixedScratch fx{static_cast<double *>(fp), (int64_t)RH_NOALLOC_SCRATCH_BYTES};
   const int32_t refine = prec == RH_FP32_REFINED ? net.ctx->refine : -1;
+  if (tree_path(net))
+    return run_tree(dn->run, 0, refine, net.ctx->refine_tol,
+                    {TreeRequest{net.dtree, dW, dHW, ldw, ldhw, k, -1, nullptr}}, (hipStream_t)stream, err, &fx);
+  const rh_status gs = need_groups(net, err);
+  if (gs != RH_OK) return gs;
   const rh_tile &t = net.tile[prec == RH_FP32_REFINED ? 1 : 0];
   return run_items(dn->info, dn->run, 0, refine, net.ctx->refine_tol, items, net.n_x, (hipStream_t)stream, err,
                    &fx, t.k > 0 ? t.dirs_per_group : 0);
@@ -2766,10 +2948,17 @@ rh_status device_hvp_batch(Context &ctx, int32_t n, Network *const *nets, const 
     if (qs != RH_OK) return qs;
   }
   std::vector<WorkItem> items;
+  std::vector<TreeRequest> req;
   int32_t max_nx = 0;
   for (int32_t i = 0; i < n; ++i) {
     Network &net = *nets[i];
     if (k[i] == 0) continue;
+    if (tree_path(net)) {
+      req.push_back({net.dtree, dW[i], dHW[i], ldw[i], ldhw[i], k[i], identity_from ? identity_from[i] : -1, nullptr});
+      continue;
+    }
+    const rh_status gs = need_groups(net, err);
+    if (gs != RH_OK) return gs;
     WorkItem it{};
     it.nd = net.dev->nd_dev;
     it.W = dW[i];
@@ -2782,15 +2971,23 @@ rh_status device_hvp_batch(Context &ctx, int32_t n, Network *const *nets, const 
     items.push_back(it);
     max_nx = std::max(max_nx, net.n_x);
   }
-  if (items.empty()) return RH_OK;
   const int32_t refine = prec == RH_FP32_REFINED ? ctx.refine : -1;
-  return run_items(ctx.dev->info, ctx.dev->on(stream), ctx.timing, refine, ctx.refine_tol, items, max_nx,
-                   (hipStream_t)stream, err);
+  Runner &r = ctx.dev->on(stream);
+  if (!req.empty()) {
+    // (phase stamps are those of one kind of launch: the other's, if there is one)
+    const rh_status s = run_tree(r, items.empty() ? ctx.timing : std::min(ctx.timing, 1), refine, ctx.refine_tol, req,
+                                 (hipStream_t)stream, err);
+    if (s != RH_OK) return s;
+  }
+  if (items.empty()) return RH_OK;
+  return run_items(ctx.dev->info, r, ctx.timing, refine, ctx.refine_tol, items, max_nx, (hipStream_t)stream, err);
 }
+
+bool device_tree(const Network &net) { return net.dev && tree_path(net); }
 
 int32_t device_max_c(const Network &net, rh_precision prec) {
   const DeviceNet *dn = net.dev;
-  if (!dn) return 1;
+  if (!dn || tree_path(net)) return 1;
   const size_t elem = prec == RH_FP32_REFINED ? sizeof(float) : sizeof(double);
   const int64_t pad_rows = (int64_t)net.n_x + kWavePadRows;
   const bool lds = (size_t)pad_rows * elem <= dn->info.lds_max && !std::getenv("RH_NO_LDS");
@@ -2809,6 +3006,7 @@ std::string device_key(int32_t device) {
 int32_t device_launch_dirs(const Network &net, rh_precision prec) {
   const DeviceNet *dn = net.dev;
   if (!dn) return 1;
+  if (tree_path(net)) return kTreeLaunchDirs;
   const rh_tile &t = net.tile[prec == RH_FP32_REFINED ? 1 : 0];
   if (t.k > 0) return t.dirs_per_group * dn->info.cus;  // the tuner's count
   const bool refined = prec == RH_FP32_REFINED;
@@ -2823,6 +3021,7 @@ struct DeviceBatch {
   std::vector<const Network *> nets;
   std::vector<uint64_t> gens;
   WorkItem *items_dev = nullptr;
+  TreeItem *titems_dev = nullptr;
   double *scratch = nullptr;
   hipStream_t cap = nullptr;
   hipGraph_t graph = nullptr;
@@ -2840,19 +3039,30 @@ void device_batch_free(DeviceBatch *b) {
   if (b->graph) (void)hipGraphDestroy(b->graph);
   if (b->cap) (void)hipStreamDestroy(b->cap);
   if (b->items_dev) (void)hipFree(b->items_dev);
+  if (b->titems_dev) (void)hipFree(b->titems_dev);
   if (b->scratch) (void)hipFree(b->scratch);
   delete b;
 }
 
 namespace {
 rh_status batch_build(DeviceBatch &b, const DeviceInfo &info, int32_t refine, double refine_tol,
-                      std::vector<WorkItem> &items, int32_t max_nx, std::string &err) {
+                      std::vector<WorkItem> &items, int32_t max_nx, const std::vector<TreeRequest> &req,
+                      std::string &err) {
+  const TreeShape sh = tree_shape(req, refine);
+  std::vector<TreeItem> titems;
+  tree_items(req, sh, titems);
+  if (req.size() > 1) {
+    HIP_TRY(hipMalloc(&b.titems_dev, titems.size() * sizeof(TreeItem)));
+    HIP_TRY(hipMemcpy(b.titems_dev, titems.data(), titems.size() * sizeof(TreeItem), hipMemcpyHostToDevice));
+  }
   LaunchPlan pl;
   rh_status ps = plan_launch(info, refine, items, max_nx, pl, err);
   if (ps != RH_OK) return ps;
-  b.C = pl.C;
-  b.groups = pl.groups;
-  HIP_TRY(hipMalloc(&b.scratch, std::max<size_t>(256, (size_t)pl.groups * pl.stride * sizeof(double))));
+  b.C = pl.n_chunks > 0 ? pl.C : kTreeDirs;
+  b.groups = pl.groups + sh.chunks;
+  // the two kinds of launches follow each other and share the scratch
+  HIP_TRY(hipMalloc(&b.scratch, std::max<size_t>({256, (size_t)pl.groups * pl.stride * sizeof(double),
+                                                  sh.scratch_bytes()})));
   LaunchArgs la{};
   la.refine = refine;
   la.refine_tol = refine_tol;
@@ -2868,14 +3078,20 @@ rh_status batch_build(DeviceBatch &b, const DeviceInfo &info, int32_t refine, do
     HIP_TRY(hipMemcpy(b.items_dev, items.data(), items.size() * sizeof(WorkItem), hipMemcpyHostToDevice));
     la.items = b.items_dev;
   }
-  if (pl.n_chunks == 0) return RH_OK;  // nothing to record: replays do nothing
-  // kernel attributes first (not stream work), then the launch alone in the graph
+  if (pl.n_chunks == 0 && sh.chunks == 0) return RH_OK;  // nothing to record: replays do nothing
+  // kernel attributes first (not stream work), then the launches alone in the
+  // graph (the tree path's kernels have theirs since the upload)
   std::string e2;
-  rh_status as = launch_plan(pl, pl.groups, nullptr, la, err, kAttrsOnly);
-  if (as != RH_OK) return as;
+  if (pl.n_chunks > 0) {
+    const rh_status as = launch_plan(pl, pl.groups, nullptr, la, err, kAttrsOnly);
+    if (as != RH_OK) return as;
+  }
   HIP_TRY(hipStreamCreateWithFlags(&b.cap, hipStreamNonBlocking));
   HIP_TRY(hipStreamBeginCapture(b.cap, hipStreamCaptureModeThreadLocal));
-  rh_status ls = launch_plan(pl, pl.groups, b.cap, la, e2, kLaunchOnly);
+  rh_status ls = RH_OK;
+  if (sh.chunks > 0)
+    ls = tree_launch(req, titems, b.titems_dev, sh, b.scratch, refine, refine_tol, nullptr, b.cap, e2);
+  if (ls == RH_OK && pl.n_chunks > 0) ls = launch_plan(pl, pl.groups, b.cap, la, e2, kLaunchOnly);
   hipGraph_t g = nullptr;
   const hipError_t ce = hipStreamEndCapture(b.cap, &g);
   b.graph = g;
@@ -2903,12 +3119,23 @@ rh_status device_batch_create(Context &ctx, int32_t n, Network *const *nets, con
   DeviceBatch *b = new DeviceBatch();
   b->device = ctx.device;
   std::vector<WorkItem> items;
+  std::vector<TreeRequest> req;
   int32_t max_nx = 0;
   for (int32_t i = 0; i < n; ++i) {
     Network &net = *nets[i];
     b->nets.push_back(&net);
     b->gens.push_back(net.dev_gen);
     if (k[i] == 0) continue;
+    b->dirs += k[i];
+    if (tree_path(net)) {
+      req.push_back({net.dtree, dW[i], dHW[i], ldw[i], ldhw[i], k[i], identity_from ? identity_from[i] : -1, nullptr});
+      continue;
+    }
+    const rh_status gs = need_groups(net, err);
+    if (gs != RH_OK) {
+      device_batch_free(b);
+      return gs;
+    }
     WorkItem it{};
     it.nd = net.dev->nd_dev;
     it.W = dW[i];
@@ -2919,11 +3146,10 @@ rh_status device_batch_create(Context &ctx, int32_t n, Network *const *nets, con
     it.identity_from = identity_from ? identity_from[i] : -1;
     it.rinfo = nullptr;
     items.push_back(it);
-    b->dirs += k[i];
     max_nx = std::max(max_nx, net.n_x);
   }
   const int32_t refine = prec == RH_FP32_REFINED ? ctx.refine : -1;
-  rh_status s = batch_build(*b, ctx.dev->info, refine, ctx.refine_tol, items, max_nx, err);
+  rh_status s = batch_build(*b, ctx.dev->info, refine, ctx.refine_tol, items, max_nx, req, err);
   if (s != RH_OK) {
     device_batch_free(b);
     return s;
@@ -2966,10 +3192,17 @@ rh_status device_refinement_report(Network &net, int32_t n, std::vector<double> 
 int64_t device_network_bytes(const Network &net) {
   const DeviceNet *dn = net.dev;
   if (!dn) return 0;
-  return dn->bytes + dn->rinfo_cols * 4 * (int64_t)sizeof(double) + (int64_t)dn->run.scratch_bytes;
+  return dn->bytes + tree_bytes(net.dtree) + dn->rinfo_cols * 4 * (int64_t)sizeof(double) + (int64_t)dn->run.scratch_bytes;
 }
 
-int64_t device_scratch_per_direction(int32_t n_x, rh_precision prec) {
+int64_t device_scratch_per_direction(const Network &net, rh_precision prec) {
+  const int32_t n_x = net.n_x;
+  if (net.dev && tree_path(net)) {
+    // a chunk's share (chunks are padded to kTreeDirs directions)
+    const TreeShape sh = tree_shape({TreeRequest{net.dtree, nullptr, nullptr, 0, 0, 1, -1, nullptr}},
+                                    prec == RH_FP32_REFINED ? net.ctx->refine : -1);
+    return (int64_t)(sh.scratch_bytes() + kTreeDirs - 1) / kTreeDirs;
+  }
   // per-workgroup scratch of run_items, per direction it owns, with the
   // vector in global memory (the larger case): FP64 Y_x and X; refined V1,
   // V2 and the FP32 correction

@@ -667,6 +667,7 @@ __global__ __launch_bounds__(kNtThreads) void nt_dense_solve(const NtArgs A) {
 
 struct DevNewton {
   int device = -1;
+  bool current = false;  // w.lu holds the factors of the network's accepted state
   std::vector<void *> allocs;
   NtArgs args{};
   size_t lds_bytes = 0;
@@ -949,6 +950,7 @@ rh_status device_newton(Network &net, double tol, int32_t max_iter, NewtonResult
     }
   }
   DevNewton &d = *net.dnewton;
+  d.current = false;
   NtVectors &w = d.args.w;
   std::vector<double> x(net.n_x, 0.0);
   if ((int32_t)net.x0.size() == net.n_x)
@@ -999,7 +1001,16 @@ rh_status device_newton(Network &net, double tol, int32_t max_iter, NewtonResult
     lu.lval[i].assign(r, r + nl);
     lu.uval[i].assign(r + nl, r + nl + lu.urow[i].size());
   }
+  d.current = true;
   return RH_OK;
+}
+
+const double *device_newton_factors(const Network &net) {
+  return net.dnewton && net.dnewton->current ? net.dnewton->args.w.lu : nullptr;
+}
+
+void device_newton_stale(Network &net) {
+  if (net.dnewton) net.dnewton->current = false;
 }
 
 }  // namespace rh

@@ -152,6 +152,7 @@ struct DeviceNet;  // defined by the device translation unit
 struct DeviceCtx;  // likewise: a context's resources for batched launches
 struct DeviceBatch;  // likewise: a batched launch recorded as a graph
 struct DevNewton;    // the device Newton's arrays (newton.hip)
+struct DevTree;      // the tree path's plan and arrays (tree.hip)
 struct DevTrack;     // the tracking update's device workspace (track.hip)
 
 struct Context {
@@ -207,6 +208,7 @@ struct Network {
   DeviceNet *dev = nullptr;
   DevNewton *dnewton = nullptr;  // device Newton arrays (rh_solve_powerflow_device)
   DevTrack *dtrack = nullptr;    // tracking workspace (rh_tracking_step_device)
+  DevTree *dtree = nullptr;      // tree path of the products (larger networks)
   uint64_t dev_gen = 0;  // device uploads so far (a recorded launch checks it is unchanged)
   // launch shape per precision (0 FP64, 1 refined) chosen by the tuner
   // (tune.cpp); k == 0: not chosen, the library's defaults apply
@@ -270,6 +272,10 @@ struct NewtonResult {
 };
 rh_status device_newton(Network &net, double tol, int32_t max_iter, NewtonResult &res, std::string &err);
 void device_newton_free(Network &net);
+// The flat factors of the accepted state on the device (row by row, L part
+// then U part), or null if the last solve was the host's.
+const double *device_newton_factors(const Network &net);
+void device_newton_stale(Network &net);  // the host factorised since
 // Newton at rounding level: after three steps, a residual below 1e-11 that
 // no longer halves is accepted (the tolerance may lie below what the
 // arithmetic can reach for a large grid).
@@ -365,6 +371,7 @@ bool wave_records(const Packed &pk, bool compact, bool fp64, std::vector<char> &
 rh_status device_upload(Network &net, std::string &err,
                         const std::function<rh_status(std::string &)> &accept = nullptr);
 void device_free(Network &net);
+void device_tree_free(Network &net);
 void device_ctx_free(Context &ctx);
 // Fill the report's launch count, summed kernel time and phase times of the
 // launches since the previous collection, and start a new window.
@@ -419,9 +426,10 @@ int32_t device_launch_dirs(const Network &net, rh_precision prec);
 rh_status device_refinement_report(Network &net, int32_t n, std::vector<double> &out, std::string &err);
 // Device bytes held by the network (factors, schedules, coefficients,
 // descriptors, its launch scratch and report buffers), and the launch
-// scratch a direction of a network with n_x states may take.
+// scratch one of its directions may take.
 int64_t device_network_bytes(const Network &net);
-int64_t device_scratch_per_direction(int32_t n_x, rh_precision prec);
+int64_t device_scratch_per_direction(const Network &net, rh_precision prec);
+bool device_tree(const Network &net);  // whether the products take the tree path (tree.hip)
 rh_status device_alloc(void **p, size_t bytes, std::string &err);
 void device_release(void *p);
 rh_status device_sync(void *stream, std::string &err);

@@ -70,7 +70,9 @@ std::string cache_key(const Network &net, rh_precision prec) {
   char hx[17];
   std::snprintf(hx, sizeof hx, "%016llx", (unsigned long long)topology_hash(net));
   return std::string(kCacheVersion) + " " + hx + " " + device_key(net.ctx->device) + " " +
-         (prec == RH_FP32_REFINED ? "refined" : "fp64");
+         (prec == RH_FP32_REFINED ? "refined" : "fp64") +
+         // the tree path's launches have other shapes
+         (device_tree(net) ? "-tree" : "");
 }
 
 // Networks tuned on several threads read and append the cache one at a time.
@@ -135,6 +137,8 @@ rh_status autotune(Network &net, rh_precision prec, int32_t flags, rh_tile &out,
     const std::pair<int32_t, int32_t> scheds[4] = {{64, 1}, {32, 1}, {16, 1}, {64, 0}};
     double best_ms = 0.0;
     for (const auto &sc : scheds) {
+      // (the schedule is the one-workgroup path's)
+      if (best.k > 0 && device_tree(net)) break;
       net.sched_bmax = sc.first;
       net.sched_wave = sc.second;
       if ((s = device_upload(net, err)) != RH_OK) break;

@@ -1,0 +1,476 @@
+// P G_x P^T = L U by dense fronts (multifrontal, static diagonal pivots).
+//
+// Row by row, the factorisation is a chain of elimination steps as long as
+// the rows at the top of the tree are wide: 3.1 ms of 3.5 at 10k buses, in one
+// workgroup.  Here every node of the tree plan (tree.h) has a front, the
+// dense matrix of its own rows S and its border B; the entries of G_x and
+// what is left of the fronts below are summed into it, the rows of S are
+// eliminated, and the rest (B, B) waits for the nodes above.  A tier is two
+// launches, so that the chain is a few dozen panels of 16 columns.
+//
+// Fronts are stored in tiles of 16 x 16 (own rows first, then the border, as
+// in the plan), row-major in a tile.  A panel's diagonal tile is factored by
+// one wave in registers, its rows of L and columns of U by substitution, one
+// per thread, and the rest of the front takes the panel's product on the
+// matrix cores.  Measured, the whole factorisation before and after: 3.5 ms and
+// 0.43 ms at 10k buses (leaves 30 us, the tier above 239, the top 123), 0.60 ms
+// and 0.13 ms at 1k.
+#include <hip/hip_runtime.h>
+
+#include <algorithm>
+#include <cmath>
+#include <limits>
+
+#include "fronts.h"
+#include "tree.h"
+
+namespace rh {
+
+namespace {
+
+#define HIP_TRY(expr)                                                          \
+  do {                                                                         \
+    hipError_t e_ = (expr);                                                    \
+    if (e_ != hipSuccess) {                                                    \
+      err = std::string(#expr) + ": " + hipGetErrorString(e_);                 \
+      return RH_EDEVICE;                                                       \
+    }                                                                          \
+  } while (0)
+
+constexpr int kT = kTreeTile, kTT = kT * kT;
+typedef double v4d __attribute__((ext_vector_type(4)));
+
+struct FrontNode {
+  int64_t f0;            // first value of the front
+  int32_t ns, mt, nt;    // own rows; tiles of own rows, and of all
+  int32_t a0, a1;        // leaves: entries of G_x
+};
+
+// Lane C of each group of 16 lanes to all its lanes.
+template <int C>
+__device__ __forceinline__ double group_bcast(double v) {
+  return __builtin_amdgcn_mov_dpp(v, 0x150 + C, 0xF, 0xF, true);
+}
+// L U of a tile in a wave's registers: register r holds row 4 r + lane / 16,
+// column lane % 16.
+template <int C>
+__device__ __forceinline__ void tile_lu(double (&d)[4], double *dinv, int lane) {
+  if constexpr (C < kT) {
+    const int l16 = lane & 15, g = lane >> 4;
+    // row C: register C / 4 of group C % 4
+    const double u = __shfl(d[C >> 2], (C & 3) * 16 + l16);
+    const double rp = 1.0 / group_bcast<C>(u);
+    if (lane == 0) dinv[C] = rp;
+#pragma unroll
+    for (int r = C >> 2; r < 4; ++r) {
+      const double l = group_bcast<C>(d[r]) * rp;
+      if (4 * r + g > C) d[r] = l16 == C ? l : l16 > C ? fma(-l, u, d[r]) : d[r];
+    }
+    tile_lu<C + 1>(d, dinv, lane);
+  }
+}
+
+// The next panel's diagonal tile (in a wave's registers as the matrix
+// instructions leave it) factored, to LDS and back to the front.  Rows past
+// the node's own (`own` of the tile are) get a unit diagonal.
+__device__ __forceinline__ void front_diag(v4d t, double *T, double *D, double *dinv, int32_t own, int lane) {
+  const int l16 = lane & 15, g = lane >> 4;
+  double d[4];
+#pragma unroll
+  for (int r = 0; r < 4; ++r) d[r] = 4 * r + g < own ? t[r] : 4 * r + g == l16 ? 1.0 : 0.0;
+  tile_lu<0>(d, dinv, lane);
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    D[r * 64 + lane] = d[r];
+    T[r * 64 + lane] = d[r];
+  }
+}
+
+// A node's own rows eliminated, 16 columns (a panel) at a time.  NW waves: a
+// panel has at most 2 * 16 * (nt - 1) rows of L and columns of U, one per
+// thread.  LDS: the panel (a row's 16 values of L in steps of 16, a column's
+// of U likewise, as the matrix instructions read them) and the diagonal
+// tiles.  The first wave factors the next diagonal tile while the others
+// take the product.  LEAF: the front is cleared and G_x's entries are put in
+// first (no front below).  What bounds it: a panel is a chain of a trip to
+// L2, a substitution of 16, and of 16 pivots or the product, whichever is
+// longer: one CU's matrix cores and path to L2 in the large fronts.
+template <int NW, bool LEAF>
+__global__ __launch_bounds__(NW * 64) void front_factor(double *fronts, const FrontNode *nodes, int32_t node0,
+                                                        const int32_t *a_dst, const int32_t *a_src,
+                                                        const double *gx) {
+  extern __shared__ __align__(16) double lds[];
+  const FrontNode nd = nodes[node0 + blockIdx.x];
+  const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, g = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  double *F = fronts + nd.f0;
+  const int nt = nd.nt, mt = nd.mt;
+  double *Dall = lds, *Lp = Dall + 2 * (kTT + kT), *Up = Lp + (nt - 1) * kTT;
+  auto tile_at = [&](int i, int j) { return F + (int64_t)(i * nt + j) * kTT; };
+  if constexpr (LEAF) {
+    for (int i = tid; i < nt * nt * kTT; i += NW * 64) F[i] = 0.0;
+    __syncthreads();
+    for (int32_t e = nd.a0 + tid; e < nd.a1; e += NW * 64) F[a_dst[e]] = gx[a_src[e]];
+    __syncthreads();
+  }
+  if (wave == 0 && mt > 0) {
+    v4d t;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) t[r] = F[r * 64 + lane];
+    front_diag(t, F, Dall, Dall + kTT, nd.ns, lane);
+  }
+  __syncthreads();
+  for (int k = 0; k < mt; ++k) {
+    const int n1 = nt - k - 1;
+    const double *D = Dall + (k & 1) * (kTT + kT), *dinv = D + kTT;
+    if (tid < n1 * kT) {
+      // a row of L: x U = v
+      double *P = tile_at(k + 1 + (tid >> 4), k) + (tid & 15) * kT;
+      double v[kT];
+#pragma unroll
+      for (int c = 0; c < kT; c += 2) {
+        const double2 p = *reinterpret_cast<const double2 *>(P + c);
+        v[c] = p.x;
+        v[c + 1] = p.y;
+      }
+#pragma unroll
+      for (int c = 0; c < kT; ++c) {
+        v[c] *= dinv[c];
+#pragma unroll
+        for (int m = c + 1; m < kT; ++m) v[m] = fma(-v[c], D[c * kT + m], v[m]);
+      }
+      double *to = Lp + (tid >> 4) * kTT + (tid & 15);
+#pragma unroll
+      for (int c = 0; c < kT; c += 2) {
+        *reinterpret_cast<double2 *>(P + c) = make_double2(v[c], v[c + 1]);
+        to[c * kT] = v[c];
+        to[(c + 1) * kT] = v[c + 1];
+      }
+    } else if (tid < 2 * n1 * kT) {
+      // a column of U: L x = v
+      const int q = tid - n1 * kT;
+      double *P = tile_at(k, k + 1 + (q >> 4)) + (q & 15);
+      double v[kT];
+#pragma unroll
+      for (int c = 0; c < kT; ++c) v[c] = P[c * kT];
+#pragma unroll
+      for (int c = 0; c < kT; ++c)
+#pragma unroll
+        for (int m = c + 1; m < kT; ++m) v[m] = fma(-D[m * kT + c], v[c], v[m]);
+      double *to = Up + (q >> 4) * kTT + (q & 15);
+#pragma unroll
+      for (int c = 0; c < kT; ++c) {
+        P[c * kT] = v[c];
+        to[c * kT] = v[c];
+      }
+    }
+    __syncthreads();
+    // the rest of the front: tile t of it loses L U
+    auto load = [&](int t) {
+      const double *C = tile_at(k + 1 + t / n1, k + 1 + t % n1) + lane;
+      v4d acc;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) acc[r] = C[r * 64];
+      return acc;
+    };
+    auto take = [&](int t, v4d acc) {
+      const double *l = Lp + (t / n1) * kTT + lane, *u = Up + (t % n1) * kTT + lane;
+#pragma unroll
+      for (int s = 0; s < 4; ++s) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(-l[s * 64], u[s * 64], acc, 0, 0, 0);
+      return acc;
+    };
+    const bool ahead = k + 1 < mt;  // a panel follows
+    if (ahead && wave == 0) {
+      double *next = Dall + ((k + 1) & 1) * (kTT + kT);
+      front_diag(take(0, load(0)), tile_at(k + 1, k + 1), next, next + kTT, nd.ns - (k + 1) * kT, lane);
+    } else {
+      // kB tiles of a wave at a time
+      constexpr int kB = 4;
+      const int w = ahead ? wave - 1 : wave, nw = ahead ? NW - 1 : NW, first = ahead ? 1 : 0, n = n1 * n1;
+      for (int t0 = first + w; t0 < n; t0 += kB * nw) {
+        v4d acc[kB];
+#pragma unroll
+        for (int b = 0; b < kB; ++b) acc[b] = load(min(t0 + b * nw, n - 1));
+#pragma unroll
+        for (int b = 0; b < kB; ++b) acc[b] = take(min(t0 + b * nw, n - 1), acc[b]);
+#pragma unroll
+        for (int b = 0; b < kB; ++b) {
+          const int t = t0 + b * nw;
+          if (t >= n) break;
+          double *C = tile_at(k + 1 + t / n1, k + 1 + t % n1) + lane;
+#pragma unroll
+          for (int r = 0; r < 4; ++r) C[r * 64] = acc[b][r];
+        }
+      }
+    }
+    __syncthreads();
+  }
+}
+
+__global__ __launch_bounds__(256) void front_clear(double *f, int64_t n) {
+  for (int64_t i = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 2; i < n; i += (int64_t)gridDim.x * 512) {
+    f[i] = 0.0;
+    f[i + 1] = 0.0;
+  }
+}
+
+// Entry e of a tier's fronts: the sum of its sources in their order, entries
+// of G_x (~index) and of the fronts below.
+__global__ __launch_bounds__(256) void front_gather(double *fronts, const int32_t *dst, const int32_t *ptr,
+                                                    const int32_t *src, int32_t e0, int32_t e1, const double *gx) {
+  const int32_t e = e0 + blockIdx.x * 256 + threadIdx.x;
+  if (e >= e1) return;
+  double s = 0.0;
+  for (int32_t q = ptr[e]; q < ptr[e + 1]; ++q) {
+    const int32_t at = src[q];
+    s += at < 0 ? gx[~at] : fronts[at];
+  }
+  fronts[dst[e]] = s;
+}
+
+// The fronts' factors into the flat layout: per entry of the plan one of L
+// and one of U, per row its pivot, the reciprocal and the pivot test (a pivot
+// below 1e-13 times the row's largest entry of G_x, or not finite).
+struct FrontRow {
+  int32_t front, pos, a0, a1;  // the pivot's value and flat position; entries of G_x
+};
+__global__ __launch_bounds__(256) void front_out(const double *fronts, const int2 *at, const int32_t *lo,
+                                                 const int32_t *up, int32_t n, const FrontRow *rows, int32_t n_rows,
+                                                 const int32_t *row_src, FrontIo io) {
+  const int32_t e = blockIdx.x * 256 + threadIdx.x;
+  if (e < n_rows) {
+    const FrontRow r = rows[e];
+    const double d = fronts[r.front];
+    double amax = 0.0;
+    for (int32_t q = r.a0; q < r.a1; ++q) amax = fmax(amax, fabs(io.gx[row_src[q]]));
+    io.lu[r.pos] = d;
+    io.rinv[e] = 1.0 / d;
+    if (!isfinite(d) || !(fabs(d) > 1e-13 * amax) || amax == 0.0) io.stat[2] = (double)(e + 1);
+  }
+  if (e < n) {
+    const int2 f = at[e];
+    io.lu[lo[e]] = fronts[f.x];
+    io.lu[up[e]] = fronts[f.y];
+  }
+}
+
+}  // namespace
+
+struct DevFronts {
+  std::vector<void *> allocs;
+  double *fronts = nullptr;
+  int64_t leaf_values = 0, values = 0;
+  const FrontNode *nodes = nullptr;
+  const int32_t *a_dst = nullptr, *a_src = nullptr;         // leaves: entries of G_x
+  const int32_t *dst = nullptr, *ptr = nullptr, *src = nullptr;  // the tiers above: sums
+  const int2 *at = nullptr;                                 // per plan entry: its L and U values in the fronts
+  const int32_t *lo = nullptr, *up = nullptr, *row_src = nullptr;
+  const FrontRow *rows = nullptr;
+  int32_t n = 0, n_ents = 0;
+  std::vector<int32_t> tier, ents, most;  // per tier: first node, first sum, most tiles of a node
+};
+
+namespace {
+
+template <class T>
+rh_status f_up(DevFronts &f, const std::vector<T> &v, const T **out, std::string &err) {
+  void *p = nullptr;
+  HIP_TRY(hipMalloc(&p, std::max<size_t>(sizeof(T), v.size() * sizeof(T))));
+  f.allocs.push_back(p);
+  if (!v.empty()) HIP_TRY(hipMemcpy(p, v.data(), v.size() * sizeof(T), hipMemcpyHostToDevice));
+  *out = static_cast<const T *>(p);
+  return RH_OK;
+}
+
+// The fronts of a network may take this much; beyond it (more than a million
+// states) the row-by-row factorisation remains.
+constexpr int64_t kMostFrontBytes = int64_t(4) << 30;
+
+size_t front_lds(int32_t nt) { return ((size_t)2 * (nt - 1) * kTT + 2 * (kTT + kT)) * sizeof(double); }
+
+rh_status fill(DevFronts &f, const LuPlan &lu, const LuMaps &mp, const TreePlan &p, std::string &err) {
+  const int32_t n = lu.n, n_nodes = (int32_t)p.nodes.size(), tiers = (int32_t)p.tier.size() - 1;
+  f.n = n;
+  f.tier = p.tier;
+  std::vector<FrontNode> nodes(n_nodes);
+  std::vector<int32_t> owner(n);  // tree position -> node
+  int64_t total = 0;
+  for (int32_t t = 0; t < tiers; ++t) {
+    int32_t most = 0;
+    for (int32_t q = p.tier[t]; q < p.tier[t + 1]; ++q) {
+      const TreeNode &nd = p.nodes[q];
+      nodes[q] = FrontNode{total, nd.ns, nd.mt, nd.mt + nd.bt, 0, 0};
+      total += (int64_t)nodes[q].nt * nodes[q].nt * kTT;
+      most = std::max(most, nodes[q].nt);
+      for (int32_t a = 0; a < nd.ns; ++a) owner[nd.row0 + a] = q;
+    }
+    f.most.push_back(most);
+    if (t == 0) f.leaf_values = total;
+  }
+  f.values = total;
+  // local row of a node in its front's tiles, and the value (r, c)
+  auto tiled = [](const TreeNode &nd, int32_t l) { return l < nd.ns ? l : nd.mt * kT + l - nd.ns; };
+  auto value = [&](int32_t q, int32_t r, int32_t c) {  // tiled rows
+    return nodes[q].f0 + (int64_t)((r / kT) * nodes[q].nt + c / kT) * kTT + (r % kT) * kT + c % kT;
+  };
+  // G_x by the node that eliminates the earlier of row and column
+  struct Entry {
+    int32_t r, c, src;  // tree positions
+  };
+  std::vector<std::vector<Entry>> of_node(n_nodes);
+  for (int32_t i = 0; i < n; ++i)
+    for (int32_t e = mp.a_ptr[i]; e < mp.a_ptr[i + 1]; ++e) {
+      const int32_t r = p.pos[i], c = p.pos[mp.lucol[mp.row_ptr[i] + mp.a_dst[e]]];
+      of_node[owner[std::min(r, c)]].push_back({r, c, mp.a_src[e]});
+    }
+  // the nodes with border rows in a node
+  std::vector<std::vector<int32_t>> below(n_nodes);
+  for (int32_t q = 0; q < n_nodes; ++q) {
+    const TreeNode &nd = p.nodes[q];
+    for (int32_t b = 0; b < nd.nb; ++b) {
+      auto &v = below[owner[p.border[nd.border0 + b]]];
+      if (v.empty() || v.back() != q) v.push_back(q);
+    }
+  }
+  std::vector<int32_t> a_dst, a_src, dst, ptr, src, at(n, -1), loc;
+  f.ents.assign(tiers + 1, 0);
+  const bool leaves = tiers > 1;  // (a single node is assembled like the upper ones)
+  for (int32_t t = 0; t < tiers; ++t) {
+    for (int32_t q = p.tier[t]; q < p.tier[t + 1]; ++q) {
+      const TreeNode &nd = p.nodes[q];
+      for (int32_t a = 0; a < nd.ns; ++a) at[nd.row0 + a] = tiled(nd, a);
+      for (int32_t b = 0; b < nd.nb; ++b) at[p.border[nd.border0 + b]] = tiled(nd, nd.ns + b);
+      if (t == 0 && leaves) {
+        nodes[q].a0 = (int32_t)a_dst.size();
+        for (const Entry &e : of_node[q]) {
+          a_dst.push_back((int32_t)(value(q, at[e.r], at[e.c]) - nodes[q].f0));
+          a_src.push_back(e.src);
+        }
+        nodes[q].a1 = (int32_t)a_dst.size();
+      } else {
+        // lists of sources by value, in order
+        const int32_t w = nodes[q].nt * kT;
+        std::vector<int32_t> head((size_t)w * w, -1), tail((size_t)w * w, -1), next, what;
+        auto add = [&](int32_t r, int32_t c, int32_t s) {
+          const size_t k = (size_t)r * w + c;
+          const int32_t id = (int32_t)what.size();
+          what.push_back(s);
+          next.push_back(-1);
+          (tail[k] >= 0 ? next[tail[k]] : head[k]) = id;
+          tail[k] = id;
+        };
+        for (const Entry &e : of_node[q]) add(at[e.r], at[e.c], ~e.src);
+        for (int32_t ch : below[q]) {
+          const TreeNode &cd = p.nodes[ch];
+          for (int32_t i = 0; i < cd.nb; ++i)
+            for (int32_t j = 0; j < cd.nb; ++j) {
+              const int32_t r = p.border[cd.border0 + i], c = p.border[cd.border0 + j];
+              // (a pair that is not in the front is a zero of the pattern:
+              // rows of different subtrees of the node below)
+              if (owner[std::min(r, c)] != q || at[r] < 0 || at[c] < 0) continue;
+              add(at[r], at[c], (int32_t)value(ch, tiled(cd, cd.ns + i), tiled(cd, cd.ns + j)));
+            }
+        }
+        for (int32_t r = 0; r < w; ++r)
+          for (int32_t c = 0; c < w; ++c) {
+            int32_t id = head[(size_t)r * w + c];
+            if (id < 0) continue;
+            dst.push_back((int32_t)value(q, r, c));
+            ptr.push_back((int32_t)src.size());
+            for (; id >= 0; id = next[id]) src.push_back(what[id]);
+          }
+      }
+      for (int32_t a = 0; a < nd.ns; ++a) at[nd.row0 + a] = -1;
+      for (int32_t b = 0; b < nd.nb; ++b) at[p.border[nd.border0 + b]] = -1;
+    }
+    f.ents[t + 1] = (int32_t)dst.size();
+  }
+  ptr.push_back((int32_t)src.size());
+  // the way out
+  std::vector<int2> where(p.col.size());
+  for (int32_t q = 0; q < n_nodes; ++q) {
+    const TreeNode &nd = p.nodes[q];
+    for (int32_t a = 0; a < nd.ns + nd.nb; ++a)
+      for (int32_t e = p.ent_ptr[nd.ent0 + a]; e < p.ent_ptr[nd.ent0 + a + 1]; ++e) {
+        const int32_t r = tiled(nd, a), c = p.col[e];
+        where[e] = make_int2((int32_t)value(q, r, c), (int32_t)value(q, c, r));
+      }
+  }
+  std::vector<FrontRow> rows(n);
+  for (int32_t i = 0; i < n; ++i) {
+    const int32_t q = owner[p.pos[i]], a = p.pos[i] - p.nodes[q].row0;
+    rows[i] = FrontRow{(int32_t)value(q, a, a), mp.row_ptr[i] + mp.nl[i], mp.a_ptr[i], mp.a_ptr[i + 1]};
+  }
+  f.n_ents = (int32_t)where.size();
+  rh_status s;
+  if ((s = f_up(f, nodes, &f.nodes, err)) != RH_OK || (s = f_up(f, a_dst, &f.a_dst, err)) != RH_OK ||
+      (s = f_up(f, a_src, &f.a_src, err)) != RH_OK || (s = f_up(f, dst, &f.dst, err)) != RH_OK ||
+      (s = f_up(f, ptr, &f.ptr, err)) != RH_OK || (s = f_up(f, src, &f.src, err)) != RH_OK ||
+      (s = f_up(f, where, &f.at, err)) != RH_OK || (s = f_up(f, p.lo, &f.lo, err)) != RH_OK ||
+      (s = f_up(f, p.up, &f.up, err)) != RH_OK || (s = f_up(f, rows, &f.rows, err)) != RH_OK ||
+      (s = f_up(f, mp.a_src, &f.row_src, err)) != RH_OK)
+    return s;
+  void *m = nullptr;
+  HIP_TRY(hipMalloc(&m, std::max<size_t>(1, (size_t)f.values) * sizeof(double)));
+  f.allocs.push_back(m);
+  f.fronts = static_cast<double *>(m);
+  for (const void *kernel : {reinterpret_cast<const void *>(&front_factor<kLeafWaves, true>),
+                             reinterpret_cast<const void *>(&front_factor<kUpperWaves, false>)})
+    HIP_TRY(hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                (int)front_lds(*std::max_element(f.most.begin(), f.most.end()))));
+  return RH_OK;
+}
+
+}  // namespace
+
+rh_status fronts_build(const LuPlan &lu, const LuMaps &mp, DevFronts **out, std::string &err) {
+  *out = nullptr;
+  const TreePlan p = tree_plan(lu, mp.row_ptr);
+  if (!p.ok) return RH_OK;
+  int64_t total = 0;
+  for (const TreeNode &nd : p.nodes) total += (int64_t)(nd.mt + nd.bt) * (nd.mt + nd.bt) * kTT;
+  if (total * (int64_t)sizeof(double) > kMostFrontBytes) return RH_OK;
+  DevFronts *f = new DevFronts();
+  const rh_status s = fill(*f, lu, mp, p, err);
+  if (s != RH_OK) {
+    fronts_free(f);
+    return s;
+  }
+  *out = f;
+  return RH_OK;
+}
+
+void fronts_free(DevFronts *f) {
+  if (!f) return;
+  for (void *p : f->allocs) (void)hipFree(p);
+  delete f;
+}
+
+rh_status fronts_refactor(const DevFronts &f, const FrontIo &io, std::string &err) {
+  const int32_t tiers = (int32_t)f.tier.size() - 1;
+  const int64_t first = tiers > 1 ? f.leaf_values : 0;
+  if (f.values > first)
+    hipLaunchKernelGGL(front_clear, dim3((uint32_t)std::min<int64_t>(2048, (f.values - first + 511) / 512)), dim3(256),
+                       0, nullptr, f.fronts + first, f.values - first);
+  for (int32_t t = 0; t < tiers; ++t) {
+    const uint32_t nodes = (uint32_t)(f.tier[t + 1] - f.tier[t]);
+    const size_t lds = front_lds(std::max(1, f.most[t]));
+    if (t == 0 && tiers > 1) {
+      hipLaunchKernelGGL((front_factor<kLeafWaves, true>), dim3(nodes), dim3(kLeafWaves * 64), lds, nullptr, f.fronts,
+                         f.nodes, 0, f.a_dst, f.a_src, io.gx);
+      continue;
+    }
+    const int32_t e0 = f.ents[t], e1 = f.ents[t + 1];
+    if (e1 > e0)
+      hipLaunchKernelGGL(front_gather, dim3((e1 - e0 + 255) / 256), dim3(256), 0, nullptr, f.fronts, f.dst, f.ptr,
+                         f.src, e0, e1, io.gx);
+    hipLaunchKernelGGL((front_factor<kUpperWaves, false>), dim3(nodes), dim3(kUpperWaves * 64), lds, nullptr, f.fronts,
+                       f.nodes, f.tier[t], f.a_dst, f.a_src, io.gx);
+  }
+  hipLaunchKernelGGL(front_out, dim3((std::max(f.n_ents, f.n) + 255) / 256), dim3(256), 0, nullptr, f.fronts, f.at,
+                     f.lo, f.up, f.n_ents, f.rows, f.n, f.row_src, io);
+  HIP_TRY(hipGetLastError());
+  return RH_OK;
+}
+
+}  // namespace rh

@@ -11,7 +11,9 @@
 //      order) and max |g|, the one number the host reads per step;
 //   3. the values of G_x on its fixed pattern (per entry, its branch
 //      partials summed in branch order: no atomics);
-//   4. P G_x P^T = L U with static diagonal pivots: row by row, the rows of
+//   4. P G_x P^T = L U with static diagonal pivots, by dense fronts on the
+//      nodes of the tree plan (fronts.hip).  For a network that the plan does
+//      not take: row by row, the rows of
 //      one elimination level at a time (one wave per row, the row's values
 //      in LDS), except the last rows (the top of the elimination tree, where
 //      the factors are nearly dense), which after their steps with earlier
@@ -30,6 +32,7 @@
 #include <cstring>
 #include <vector>
 
+#include "fronts.h"
 #include "rh_internal.h"
 
 namespace rh {
@@ -479,6 +482,15 @@ __global__ __launch_bounds__(kNtThreads) void nt_dense_lu(const NtArgs A) {
   }
 }
 
+// The dense block's factors out of the flat ones, for the Newton step's
+// solves (the fronts write the flat ones only).
+__global__ __launch_bounds__(256) void nt_block_copy(const NtArgs A) {
+  const int32_t m = A.a.m_blk, e = blockIdx.x * 256 + threadIdx.x;
+  if (e >= m * m) return;
+  const int32_t p = A.a.dmap[e];
+  A.w.S[e] = p >= 0 ? A.w.lu[A.a.row_ptr[A.a.b0 + e / m] + p] : 0.0;
+}
+
 // ---- Newton step: y = P g; L y; U y; x -= P^T y ---------------------------
 // One wave per row: lanes take the row's entries in turn and the wave sums.
 // Y is the vector being solved (global memory, or its copy in LDS).
@@ -667,6 +679,7 @@ __global__ __launch_bounds__(kNtThreads) void nt_dense_solve(const NtArgs A) {
 
 struct DevNewton {
   int device = -1;
+  DevFronts *fronts = nullptr;  // null: row by row
   bool current = false;  // w.lu holds the factors of the network's accepted state
   std::vector<void *> allocs;
   NtArgs args{};
@@ -770,6 +783,13 @@ rh_status nt_build(Network &net, DevNewton &d, std::string &err) {
       err = "LU row pattern too wide for the device refactorisation (" + std::to_string(mp.maxpat) + ")";
       return RH_EINVAL;
     }
+    const rh_status fs = fronts_build(lu, mp, &d.fronts, err);
+    if (fs != RH_OK) return fs;
+    if (d.fronts) {  // the rows' elimination steps are not taken
+      mp.upd_ptr.clear();
+      mp.tgt.clear();
+      mp.step.clear();
+    }
     a.maxpat = mp.maxpat;
     a.nnz_lu = mp.row_ptr[n];
     NT_UP(mp.row_ptr, a.row_ptr);
@@ -863,6 +883,14 @@ rh_status nt_step_kernels(DevNewton &d, int32_t m, int32_t nb, int32_t nnz_gx, b
   hipLaunchKernelGGL(nt_norm, dim3(1), dim3(kNtThreads), 0, nullptr, d.args);
   if (jacobian) {
     hipLaunchKernelGGL(nt_gx, dim3((nnz_gx + T - 1) / T), dim3(T), 0, nullptr, d.args);
+    const int32_t mb = d.args.a.m_blk;
+    if (d.fronts) {
+      const NtVectors &w = d.args.w;
+      const rh_status fs = fronts_refactor(*d.fronts, FrontIo{w.gx, w.lu, w.rinv, w.stat}, err);
+      if (fs != RH_OK) return fs;
+      if (mb > 0) hipLaunchKernelGGL(nt_block_copy, dim3((mb * mb + T - 1) / T), dim3(T), 0, nullptr, d.args);
+      return RH_OK;
+    }
     const size_t lds_w = (size_t)d.args.a.maxpat * sizeof(double) * kNtWideWaves;
     const std::vector<int32_t> &rows = d.lev_rows_f;
     const int32_t nlev = (int32_t)rows.size();
@@ -878,7 +906,6 @@ rh_status nt_step_kernels(DevNewton &d, int32_t m, int32_t nb, int32_t nnz_gx, b
       hipLaunchKernelGGL(nt_refactor_run, dim3(1), dim3(kNtThreads), d.lds_bytes, nullptr, d.args, l, l1);
       l = l1;
     }
-    const int32_t mb = d.args.a.m_blk;
     if (mb > 0) {
       hipLaunchKernelGGL(nt_block_rows, dim3((mb + kNtWideWaves - 1) / kNtWideWaves), dim3(64 * kNtWideWaves),
                          lds_w, nullptr, d.args);
@@ -933,6 +960,7 @@ void device_newton_free(Network &net) {
   (void)hipSetDevice(d->device);
   (void)hipDeviceSynchronize();
   for (void *p : d->allocs) (void)hipFree(p);
+  fronts_free(d->fronts);
   delete d;
   net.dnewton = nullptr;
 }

@@ -154,3 +154,27 @@ def test_full_hessian_into_a_padded_buffer(solved, k_block):
     want = net.hvp(E)
     assert np.array_equal(got[cols, :n].T, want)
     _close(want, s.hvp(E), TOL["fp64"])
+
+
+# one node (up to 448 states), two tiers, three tiers; sizes that end within
+# and at a tile
+@pytest.mark.gpu
+@pytest.mark.parametrize("n_bus", [9, 60, 75, 120, 260, 1000, 2600])
+def test_device_factors_by_fronts(n_bus):
+    torch = pytest.importorskip("torch")
+    if not torch.cuda.is_available():
+        pytest.skip("needs a GPU")
+    from paper_2201_00241_amd import rh
+
+    g = gridgen.config_grid("c0", 0) if n_bus == 9 else gridgen.geometric(
+        n_bus, int(1.35 * n_bus), max(3, n_bus // 10), seed=500 + n_bus, alpha=0.2, kappa=0.017)
+    ctx = rh.Context(0)
+    host, dev = rh.Network(ctx, g), rh.Network(ctx, g)
+    host.solve()
+    for _ in range(2):  # the second solve finds the fronts of the first
+        dev.solve_device()
+    # the same elimination in another order of sums: a few hundred roundings
+    # at most, on factors of a matrix whose pivots stay within 1e4 of another
+    for d, h in zip(dev.factors(), host.factors()):
+        assert np.max(np.abs(d - h)) <= 1e-11 * np.max(np.abs(h))
+    assert np.max(np.abs(dev.state() - host.state())) <= 1e-11

@@ -51,22 +51,32 @@ template <int C>
 __device__ __forceinline__ double group_bcast(double v) {
   return __builtin_amdgcn_mov_dpp(v, 0x150 + C, 0xF, 0xF, true);
 }
-// L U of a tile in a wave's registers: register r holds row 4 r + lane / 16,
-// column lane % 16.
+// 1 / d for a pivot d: the hardware reciprocal (to 2^-23) and two Newton
+// steps, the last of which leaves the rounding of one operation; a division's
+// scaling and fix-up, for denormal and infinite pivots (which the pivot test
+// refuses), would double the chain.
+__device__ __forceinline__ double pivot_rcp(double d) {
+  double r = __builtin_amdgcn_rcp(d);
+  r = fma(r, fma(-d, r, 1.0), r);
+  return fma(r, fma(-d, r, 1.0), r);
+}
+
+// Step C of L U of a 16 x 16 tile: lane c of each group of 16 lanes holds
+// column c, register r its entry r (L not yet divided by the pivots; rl: the
+// reciprocal of the lane's own).  The groups do the same, so that every
+// broadcast stays within one.  The empty asm statements materialise d[r] at
+// the end of the step: the compiler would otherwise sink each entry's updates
+// down to its own step, where they are a serial chain.
 template <int C>
-__device__ __forceinline__ void tile_lu(double (&d)[4], double *dinv, int lane) {
+__device__ __forceinline__ void tile_lu(double (&d)[kT], double &rl, int l16) {
   if constexpr (C < kT) {
-    const int l16 = lane & 15, g = lane >> 4;
-    // row C: register C / 4 of group C % 4
-    const double u = __shfl(d[C >> 2], (C & 3) * 16 + l16);
-    const double rp = 1.0 / group_bcast<C>(u);
-    if (lane == 0) dinv[C] = rp;
+    const double rp = pivot_rcp(group_bcast<C>(d[C])), u = l16 > C ? d[C] : 0.0;
+    rl = l16 == C ? rp : rl;
 #pragma unroll
-    for (int r = C >> 2; r < 4; ++r) {
-      const double l = group_bcast<C>(d[r]) * rp;
-      if (4 * r + g > C) d[r] = l16 == C ? l : l16 > C ? fma(-l, u, d[r]) : d[r];
-    }
-    tile_lu<C + 1>(d, dinv, lane);
+    for (int r = C + 1; r < kT; ++r) d[r] = fma(-(group_bcast<C>(d[r]) * rp), u, d[r]);
+#pragma unroll
+    for (int r = C + 1; r < kT; ++r) asm volatile("" : "+v"(d[r]));
+    tile_lu<C + 1>(d, rl, l16);
   }
 }
 
@@ -75,14 +85,21 @@ __device__ __forceinline__ void tile_lu(double (&d)[4], double *dinv, int lane) 
 // the node's own (`own` of the tile are) get a unit diagonal.
 __device__ __forceinline__ void front_diag(v4d t, double *T, double *D, double *dinv, int32_t own, int lane) {
   const int l16 = lane & 15, g = lane >> 4;
-  double d[4];
 #pragma unroll
-  for (int r = 0; r < 4; ++r) d[r] = 4 * r + g < own ? t[r] : 4 * r + g == l16 ? 1.0 : 0.0;
-  tile_lu<0>(d, dinv, lane);
+  for (int r = 0; r < 4; ++r) D[r * 64 + lane] = 4 * r + g < own ? t[r] : 4 * r + g == l16 ? 1.0 : 0.0;
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  double d[kT], rl = 0.0;
 #pragma unroll
-  for (int r = 0; r < 4; ++r) {
-    D[r * 64 + lane] = d[r];
-    T[r * 64 + lane] = d[r];
+  for (int r = 0; r < kT; ++r) d[r] = D[r * kT + l16];
+  tile_lu<0>(d, rl, l16);
+  // a quarter of the rows from each group
+  if (g == 0) dinv[l16] = rl;
+#pragma unroll
+  for (int r = 0; r < kT; ++r) {
+    if ((r & 3) != g) continue;
+    const double v = r > l16 ? d[r] * rl : d[r];
+    D[r * kT + l16] = v;
+    T[r * kT + l16] = v;
   }
 }
 

@@ -73,7 +73,7 @@ rh_status track_alloc(Network &net, DevTrack *&t, std::string &err) {
   TR_TRY(hipMalloc(&t->g, n * sizeof(double)));
   TR_TRY(hipMalloc(&t->d, n * sizeof(double)));
   TR_TRY(hipMalloc(&t->diag, n * sizeof(double)));
-  TR_TRY(hipMalloc(&t->info, sizeof(int32_t)));
+  TR_TRY(hipMalloc(&t->info, dense_info_bytes()));
   for (hipEvent_t &e : t->ev) TR_TRY(hipEventCreate(&e));
   return RH_OK;
 }
@@ -99,7 +99,7 @@ rh_status dense_spd_solve(int device, int32_t n, double *A, int64_t lda, double 
   hipStream_t st = static_cast<hipStream_t>(stream);
   int32_t *info = nullptr;
   double *work = nullptr;
-  TR_TRY(hipMalloc(&info, sizeof(int32_t)));
+  TR_TRY(hipMalloc(&info, dense_info_bytes()));
   {
     hipError_t e = hipMalloc(&work, std::max<size_t>(1, (size_t)n * std::max(1, nrhs)) * sizeof(double));
     if (e != hipSuccess) {

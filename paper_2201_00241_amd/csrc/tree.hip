@@ -48,8 +48,8 @@ constexpr int kTileVals = kT * kT;  // a tile in operand order: value [s][lane] 
 // Workgroups a tier's launch has at most where a node has several chunks to
 // take: what the chip holds at once, twice over.
 constexpr uint32_t kLeafGroups = 2048, kProjGroups = 8192;
-// Chunks of one round (a leaf workgroup keeps a bit for each).
-constexpr int32_t kRoundChunks = 64;
+// Chunks a leaf workgroup takes in turn at most (it keeps a bit for each).
+constexpr int32_t kLeafChunks = 64;
 // Dynamic LDS of a workgroup: 160 KB less the little that is static.
 constexpr size_t kTreeLds = 159 * 1024;
 
@@ -551,7 +551,7 @@ __global__ __launch_bounds__(kLeafWaves * 64, 4) void tree_leaf(const TreeArgs a
 #pragma unroll
       for (int o = 0; o < 8; ++o) put(m, kNone, T(0));
     }
-    // Refined mode: the chunks (at most kRoundChunks) with directions that
+    // Refined mode: the chunks (at most kLeafChunks) with directions that
     // still take corrections.
     uint64_t active = ~uint64_t(0);
     if (kRef && iter > 0) {
@@ -1522,9 +1522,14 @@ size_t TreeShape::scratch_bytes() const {
   return ((size_t)stride + norms) * sizeof(double) * (size_t)round;
 }
 
-// Chunks of one round: enough to fill the chip, few enough that a round's
-// vectors stay in the caches between the launches that write and read them.
-constexpr int64_t kRoundBytes = int64_t(1) << 30;
+// A round's scratch and chunks at most.  A round costs its launches' chains
+// (13 of 5 to 25 us at 10k buses) besides its traffic, so the fewer the better,
+// even though its vectors then leave the caches: the full Hessian at 10k
+// buses (175 chunks of 6 MB) takes 4.39 ms in rounds of 8, 2.04 in rounds of
+// 32, 1.75 in rounds of 64 and 1.59 in one; four batches of 128 at 70k (32
+// chunks of 50 MB) 4.17 ms in rounds of 256 MB, 2.93 of 1 GB, 2.61 in one.
+constexpr int64_t kRoundBytes = int64_t(2) << 30;
+constexpr int32_t kRoundChunks = 256;
 
 TreeShape tree_shape(const std::vector<TreeRequest> &req, int32_t refine) {
   TreeShape sh;
@@ -1541,7 +1546,9 @@ TreeShape tree_shape(const std::vector<TreeRequest> &req, int32_t refine) {
   sh.norm_iters = refine >= 0 ? refine + 1 : 0;
   sh.chunks = (int32_t)chunks;
   const int64_t fit = std::max<int64_t>(1, kRoundBytes / std::max<int64_t>(1, sh.stride * 8));
-  sh.round = (int32_t)std::max<int64_t>(1, std::min<int64_t>({chunks, fit, kRoundChunks}));
+  // as many rounds as that takes, of equal length
+  const int64_t most = std::min<int64_t>(fit, kRoundChunks), rounds = std::max<int64_t>(1, (chunks + most - 1) / most);
+  sh.round = (int32_t)std::max<int64_t>(1, (chunks + rounds - 1) / rounds);
   return sh;
 }
 
@@ -1627,7 +1634,7 @@ rh_status tree_launch(const std::vector<TreeRequest> &req, const std::vector<Tre
       // grid is a multiple of eight: its matrices stay in that XCD's L2
       const uint32_t gx = q == 0 ? (uint32_t)((nodes[0] + 7) & ~7) : (uint32_t)nodes[q];
       const uint32_t most = q == 0 ? std::max<uint32_t>(1, kLeafGroups / gx) : nc;
-      const int per = (int)((nc + most - 1) / most);
+      const int per = std::min<int>(kLeafChunks, (int)((nc + most - 1) / most));
       const dim3 grid(gx, (nc + per - 1) / per), block((q == 0 ? kLeafWaves : kUpperWaves) * 64);
       a.lds_rows = (q == 0 ? leaf : upper) * kT;
       const size_t lds = (per > 1 ? 2 : 1) * (size_t)a.lds_rows * kD * el + (q == 0 ? 0 : parts);

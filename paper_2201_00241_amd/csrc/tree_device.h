@@ -26,7 +26,7 @@ struct TreeInc {
 constexpr int kTreeTiers = 12;
 // Directions a full Hessian gives one call: the rounds within it keep the
 // chip busy, and a call's launches are paid once.
-constexpr int32_t kTreeLaunchDirs = 1024;
+constexpr int32_t kTreeLaunchDirs = 4096;
 
 struct TreeDesc {
   int32_t n_x, n_p, n_bus, n_u, n_slack, n_gp_rows, n_tiers, gat0;

@@ -97,9 +97,9 @@ def test_products_against_the_oracle(solved, k, prec):
 def test_other_path_agrees_and_bits_do_not_depend_on_the_launch(solved, prec, monkeypatch):
     rh, _, net, _ = solved
     p = rh.RH_FP64 if prec == "fp64" else rh.RH_FP32_REFINED
-    W = gridgen.directions(net.n_p, 1040, 6)  # 65 chunks: a second round of one
+    W = gridgen.directions(net.n_p, 4112, 6)  # 257 chunks: two rounds, of 129 and 128
     got = net.hvp(W, prec=p)
-    for at, k in ((0, 1), (15, 2), (31, 17), (1023, 17)):
+    for at, k in ((0, 1), (15, 2), (31, 17), (1023, 17), (2060, 9), (4095, 17)):
         assert np.array_equal(net.hvp(np.ascontiguousarray(W[:, at:at + k]), prec=p), got[:, at:at + k])
     monkeypatch.setenv("RH_DIRS_PER_GROUP", "1")
     _close(net.hvp(np.ascontiguousarray(W[:, :40]), prec=p), got[:, :40], TOL[prec])

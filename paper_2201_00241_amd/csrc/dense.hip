@@ -212,9 +212,9 @@ struct PanelLds {
 };
 
 // Strip blk of panel j.
-// The diagonal block's factor goes to `diag` (the other strips may still be
-// reading the block).
-__device__ __forceinline__ void panel_strip(const Aug &M, int32_t j, int32_t blk, int32_t *info, double *diag,
+// The diagonal block's factor goes to `diag` where there are other strips,
+// which may still be reading the block.
+__device__ __forceinline__ void panel_strip(const Aug &M, int32_t j, int32_t blk, int32_t strips, int32_t *info, double *diag,
                                             PanelLds &L) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, l16 = lane & 15, g = lane >> 4;
   const int32_t nb = min(kNB, M.n - j), below = j + nb + blk * kNB;  // first row below
@@ -273,7 +273,8 @@ __device__ __forceinline__ void panel_strip(const Aug &M, int32_t j, int32_t blk
     }
   };
   if (wave == 0) factor(0);
-  for (int s = 0; s < kNB / kSub; ++s) {
+  // (sub-panels past nb are the identity)
+  for (int s = 0; s * kSub < nb; ++s) {
     __syncthreads();
     if (L.bad >= 0) break;
     const int first = (s + 1) * kSub;  // first row below the tile
@@ -343,7 +344,10 @@ __device__ __forceinline__ void panel_strip(const Aug &M, int32_t j, int32_t blk
   const int i = tid & (kStrip - 1);
   const int32_t r = row_of(i);
   if (i < kNB) {
-    if (blk == 0)
+    if (strips == 1) {  // (nothing else reads the block)
+      for (int c = tid / kStrip; c <= i && i < nb; c += kThreads / kStrip)
+        M.A[r + (int64_t)(j + c) * M.lda] = L.S[c * kStripLd + i];
+    } else if (blk == 0)
       for (int c = tid / kStrip; c < kNB; c += kThreads / kStrip) diag[c * kNB + i] = L.S[c * kStripLd + i];
   } else if (r < M.rows) {
     const AugRow a = aug_row(M, r);
@@ -435,10 +439,11 @@ __global__ __launch_bounds__(kThreads, 2) void chol_panel(Aug M, int32_t j, int3
   __shared__ PanelLds L;
   if (*info) return;
   double *mine = diag + (j / kNB & 1) * kNB * kNB, *before = diag + (j / kNB & 1 ^ 1) * kNB * kNB;
+  const int32_t strips_before = (M.rows - j + kNB - 1) / kNB;  // of the panel before
   if ((int32_t)blockIdx.x < strips) {
-    panel_strip(M, j, blockIdx.x, info, mine, L);
+    panel_strip(M, j, blockIdx.x, strips, info, mine, L);
   } else if (blockIdx.x + 1 == gridDim.x) {
-    put_diag(M, j - kNB, before);
+    if (strips_before > 1) put_diag(M, j - kNB, before);
   } else {
     int32_t ti, tk;
     // two tiles, four waves each
@@ -550,9 +555,10 @@ rh_status dense_cholesky(int32_t n, double *A, int64_t lda, double *B, int64_t l
     hipLaunchKernelGGL(chol_panel, dim3((uint32_t)(strips + (tiles + 1) / 2 + (j > 0 ? 1 : 0))), dim3(kThreads), 0, st,
                        M, j, strips, (int32_t)T, (int32_t)tiles, dinfo, diag);
   }
-  if (n > 0)
-    hipLaunchKernelGGL(chol_last_diag, dim3(1), dim3(256), 0, st, M, (n - 1) / kNB * kNB, (const int32_t *)dinfo,
-                       (const double *)(diag + ((n - 1) / kNB & 1) * kNB * kNB));
+  const int32_t last = n > 0 ? (n - 1) / kNB * kNB : 0;
+  if (nrhs > kNB && n > 0)  // the last panel has several strips
+    hipLaunchKernelGGL(chol_last_diag, dim3(1), dim3(256), 0, st, M, last, (const int32_t *)dinfo,
+                       (const double *)(diag + (last / kNB & 1) * kNB * kNB));
   DENSE_TRY(hipGetLastError());
   return RH_OK;
 }

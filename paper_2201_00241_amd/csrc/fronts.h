@@ -12,17 +12,21 @@ namespace rh {
 
 struct DevFronts;  // a network's fronts on the device
 
-// Where the factorisation reads and writes (device memory).
+// Device vectors of the Newton step.
 struct FrontIo {
-  const double *gx;  // values of G_x
-  double *lu, *rinv, *stat;  // flat factors, pivot reciprocals; stat[2]: singular row + 1
+  const double *gx, *g;  // values of G_x; the mismatch
+  double *lu, *stat;     // flat factors; stat[2]: singular row + 1
+  double *x;             // the state
 };
 
 // Builds the fronts; null in *out where the plan does not take the network.
 // maps: the factors' flat layout and the entries of G_x in it.
 rh_status fronts_build(const LuPlan &lu, const LuMaps &maps, DevFronts **out, std::string &err);
 void fronts_free(DevFronts *f);
-// P G_x P^T = L U into io.lu, on the null stream.
+// All on the null stream: P G_x P^T = L U and L y = P g in the fronts;
+// x -= G_x^{-1} g, from them; the factors out of the fronts into io.lu.
 rh_status fronts_refactor(const DevFronts &f, const FrontIo &io, std::string &err);
+rh_status fronts_solve(const DevFronts &f, const FrontIo &io, std::string &err);
+rh_status fronts_factors(const DevFronts &f, const FrontIo &io, std::string &err);
 
 }  // namespace rh

@@ -12,9 +12,14 @@
 // in the plan), row-major in a tile.  A panel's diagonal tile is factored by
 // one wave in registers, its rows of L and columns of U by substitution, one
 // per thread, and the rest of the front takes the panel's product on the
-// matrix cores.  Measured, the whole factorisation before and after: 3.5 ms and
-// 0.43 ms at 10k buses (leaves 30 us, the tier above 239, the top 123), 0.60 ms
-// and 0.13 ms at 1k.
+// matrix cores.  The mismatch g is one more column of the front, so that L y =
+// P g comes with the factorisation, and the Newton step is the sweep with U
+// from the top down, a launch per tier.
+//
+// Measured before and after: the factorisation 3.5 ms and 0.43 ms at 10k buses
+// (leaves 31 us, the tier above 240, the top 125), 0.60 ms and 0.13 ms at 1k; the
+// two triangular solves by levels 0.46 ms and 0.05 ms at 10k (top 21 us, the
+// tier below 23, leaves 9), 0.16 ms and 0.02 ms at 1k.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -42,8 +47,9 @@ typedef double v4d __attribute__((ext_vector_type(4)));
 
 struct FrontNode {
   int64_t f0;            // first value of the front
-  int32_t ns, mt, nt;    // own rows; tiles of own rows, and of all
+  int32_t ns, nb, mt, nt;  // own and border rows; tiles of own rows, and of all
   int32_t a0, a1;        // leaves: entries of G_x
+  int32_t row0, border0;  // tree position of the own rows, place in the list of the border's
 };
 
 // Lane C of each group of 16 lanes to all its lanes.
@@ -51,6 +57,39 @@ template <int C>
 __device__ __forceinline__ double group_bcast(double v) {
   return __builtin_amdgcn_mov_dpp(v, 0x150 + C, 0xF, 0xF, true);
 }
+// Columns C .. 0 of the back substitution with a 16 x 16 triangle: lane r of
+// each group holds v_r and row r right of the diagonal, rl = 1 / U(r, r).
+template <int C>
+__device__ __forceinline__ void back_steps(double &v, const double (&d)[kT], double rl) {
+  v = fma(-d[C], group_bcast<C>(v * rl), v);
+  if constexpr (C > 0) back_steps<C - 1>(v, d, rl);
+}
+
+// Columns C .. 14 of the substitution with a unit lower triangle: lane r holds
+// v_r and row r left of the diagonal.
+template <int C>
+__device__ __forceinline__ void forward_steps(double &v, const double (&l)[kT]) {
+  if constexpr (C + 1 < kT) {
+    v = fma(-l[C], group_bcast<C>(v), v);
+    forward_steps<C + 1>(v, l);
+  }
+}
+
+// Sum over the 16 lanes of each group, in all of them.
+template <int R>
+__device__ __forceinline__ double rotate(double v) {
+  const long long b = __double_as_longlong(v);
+  const int lo = __builtin_amdgcn_mov_dpp((int)b, 0x120 + R, 0xF, 0xF, true);
+  const int hi = __builtin_amdgcn_mov_dpp((int)(b >> 32), 0x120 + R, 0xF, 0xF, true);
+  return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
+}
+__device__ __forceinline__ double group_sum(double v) {
+  v += rotate<8>(v);
+  v += rotate<4>(v);
+  v += rotate<2>(v);
+  return v + rotate<1>(v);
+}
+
 // 1 / d for a pivot d: the hardware reciprocal (to 2^-23) and two Newton
 // steps, the last of which leaves the rounding of one operation; a division's
 // scaling and fix-up, for denormal and infinite pivots (which the pivot test
@@ -112,17 +151,27 @@ __device__ __forceinline__ void front_diag(v4d t, double *T, double *D, double *
 // first (no front below).  What bounds it: a panel is a chain of a trip to
 // L2, a substitution of 16, and of 16 pivots or the product, whichever is
 // longer: one CU's matrix cores and path to L2 in the large fronts.
+//
+// The right-hand side, after the front's tiles: in LDS meanwhile; own rows end
+// as y, the border's as what is left for the fronts above.
 template <int NW, bool LEAF>
 __global__ __launch_bounds__(NW * 64) void front_factor(double *fronts, const FrontNode *nodes, int32_t node0,
                                                         const int32_t *a_dst, const int32_t *a_src,
-                                                        const double *gx) {
+                                                        const int32_t *row_g, const double *gx, const double *grhs) {
   extern __shared__ __align__(16) double lds[];
   const FrontNode nd = nodes[node0 + blockIdx.x];
-  const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, g = lane >> 4;
+  const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   double *F = fronts + nd.f0;
   const int nt = nd.nt, mt = nd.mt;
-  double *Dall = lds, *Lp = Dall + 2 * (kTT + kT), *Up = Lp + (nt - 1) * kTT;
+  double *Dall = lds, *Y = Dall + 2 * (kTT + kT), *R = Y + kT, *Lp = R + nt * kT, *Up = Lp + (nt - 1) * kTT;
+  double *Rf = F + (int64_t)nt * nt * kTT;
+  for (int r = tid; r < nt * kT; r += NW * 64) {
+    if constexpr (LEAF)
+      R[r] = r < nd.ns ? grhs[row_g[nd.row0 + r]] : 0.0;
+    else
+      R[r] = r < nd.ns ? Rf[r] : 0.0;
+  }
   auto tile_at = [&](int i, int j) { return F + (int64_t)(i * nt + j) * kTT; };
   if constexpr (LEAF) {
     for (int i = tid; i < nt * nt * kTT; i += NW * 64) F[i] = 0.0;
@@ -140,10 +189,10 @@ __global__ __launch_bounds__(NW * 64) void front_factor(double *fronts, const Fr
   for (int k = 0; k < mt; ++k) {
     const int n1 = nt - k - 1;
     const double *D = Dall + (k & 1) * (kTT + kT), *dinv = D + kTT;
+    double v[kT];  // the thread's row of L, or column of U
     if (tid < n1 * kT) {
       // a row of L: x U = v
       double *P = tile_at(k + 1 + (tid >> 4), k) + (tid & 15) * kT;
-      double v[kT];
 #pragma unroll
       for (int c = 0; c < kT; c += 2) {
         const double2 p = *reinterpret_cast<const double2 *>(P + c);
@@ -167,7 +216,6 @@ __global__ __launch_bounds__(NW * 64) void front_factor(double *fronts, const Fr
       // a column of U: L x = v
       const int q = tid - n1 * kT;
       double *P = tile_at(k, k + 1 + (q >> 4)) + (q & 15);
-      double v[kT];
 #pragma unroll
       for (int c = 0; c < kT; ++c) v[c] = P[c * kT];
 #pragma unroll
@@ -181,7 +229,21 @@ __global__ __launch_bounds__(NW * 64) void front_factor(double *fronts, const Fr
         to[c * kT] = v[c];
       }
     }
+    if (wave == NW - 1) {
+      // the right-hand side: L x = v, a row per lane (the groups alike)
+      double l[kT], y = R[k * kT + l16];
+#pragma unroll
+      for (int c = 0; c < kT; ++c) l[c] = c < l16 ? D[l16 * kT + c] : 0.0;
+      forward_steps<0>(y, l);
+      if (lane < kT) R[k * kT + l16] = Y[l16] = y;
+    }
     __syncthreads();
+    if (tid < n1 * kT) {
+      double s = 0.0;
+#pragma unroll
+      for (int c = 0; c < kT; ++c) s = fma(v[c], Y[c], s);
+      R[(k + 1) * kT + tid] -= s;
+    }
     // the rest of the front: tile t of it loses L U
     auto load = [&](int t) {
       const double *C = tile_at(k + 1 + t / n1, k + 1 + t % n1) + lane;
@@ -222,6 +284,116 @@ __global__ __launch_bounds__(NW * 64) void front_factor(double *fronts, const Fr
     }
     __syncthreads();
   }
+  for (int r = tid; r < nt * kT; r += NW * 64) Rf[r] = R[r];
+}
+
+// x_S = U_SS^{-1} (y_S - U_SB x_B) of every node of a tier, into xt (tree
+// order) and off the state.  A wave has every NW-th row of tiles: their sums
+// (kOwn at most) with the solved columns stay spread over its lanes until the row's turn,
+// when it adds them up, solves the diagonal tile (a row per lane) and hands
+// the 16 values over in LDS.  What bounds it: that chain, about 0.5 us a tile.
+template <int NW, int kOwn>
+__global__ __launch_bounds__(NW * 64) void front_back(const double *fronts, const FrontNode *nodes, int32_t node0,
+                                                      const int32_t *border, const int32_t *row_x, double *xt,
+                                                      double *x) {
+  static_assert(kTreeLeafRows <= kLeafWaves * kT && kTreeTopRows <= 2 * kUpperWaves * kT, "rows of tiles");
+  __shared__ double X[(kTreeTopRows > kUpperTiles * kT ? kTreeTopRows : kUpperTiles * kT) + kT];
+  const FrontNode nd = nodes[node0 + blockIdx.x];
+  const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, g = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int nt = nd.nt, mt = nd.mt;
+  const double *F = fronts + nd.f0, *Rf = F + (int64_t)nt * nt * kTT;
+  auto tile_at = [&](int i, int j) { return F + (int64_t)(i * nt + j) * kTT; };
+  for (int b = tid; b < (nt - mt) * kT; b += NW * 64) X[mt * kT + b] = b < nd.nb ? xt[border[nd.border0 + b]] : 0.0;
+  // the wave's diagonal tiles (row l16 right of the diagonal) and y
+  double d[kOwn][kT], y[kOwn], rl[kOwn], acc[kOwn][4];
+#pragma unroll
+  for (int o = 0; o < kOwn; ++o) {
+    const int i = wave + o * NW;
+    y[o] = rl[o] = 0.0;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) acc[o][q] = 0.0;
+#pragma unroll
+    for (int c = 0; c < kT; ++c) d[o][c] = 0.0;
+    if (i >= mt) continue;
+    const double *T = tile_at(i, i) + l16 * kT;
+    y[o] = Rf[i * kT + l16];
+    double diag = 1.0;
+#pragma unroll
+    for (int c = 0; c < kT; ++c) {
+      const double v = T[c];
+      diag = c == l16 ? v : diag;
+      d[o][c] = c > l16 ? v : 0.0;
+    }
+    rl[o] = 1.0 / diag;
+  }
+  __syncthreads();
+  // a row's tile times the 16 values of its column
+  auto load = [&](int i, int j, double (&t)[4]) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) t[q] = tile_at(i, j)[q * 64 + lane];
+  };
+#pragma unroll
+  for (int o = 0; o < kOwn; ++o) {
+    const int i = wave + o * NW;
+    if (i >= mt) continue;
+    for (int j = mt; j < nt; ++j) {
+      double t[4];
+      load(i, j, t);
+      const double v = X[j * kT + l16];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) acc[o][q] = fma(t[q], v, acc[o][q]);
+    }
+  }
+  // the tiles of the next two columns
+  double t[kOwn][4], next[kOwn][4], later[kOwn][4];
+  auto prefetch = [&](int k, double (&to)[kOwn][4]) {
+#pragma unroll
+    for (int o = 0; o < kOwn; ++o)
+      if (wave + o * NW < k) load(wave + o * NW, k, to[o]);
+  };
+  if (mt > 0) prefetch(mt - 1, t);
+  if (mt > 1) prefetch(mt - 2, next);
+  for (int k = mt - 1; k >= 0; --k) {
+    if (k > 1) prefetch(k - 2, later);
+#pragma unroll
+    for (int o = 0; o < kOwn; ++o) {
+      if (wave + o * NW != k) continue;
+      // row 4 q + g of the sums is register q of group g: lane l16 takes row l16
+      double s = 0.0;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const double a = group_sum(acc[o][q]);
+        s = (l16 >> 2) == q ? a : s;
+      }
+      double v = y[o] - __shfl(s, (l16 & 3) * 16 + l16);
+      back_steps<kT - 1>(v, d[o], rl[o]);
+      v *= rl[o];
+      if (g == 0) {
+        X[k * kT + l16] = v;
+        if (k * kT + l16 < nd.ns) {
+          const int32_t row = nd.row0 + k * kT + l16;
+          xt[row] = v;
+          x[row_x[row]] -= v;
+        }
+      }
+    }
+    __syncthreads();
+    const double v = X[k * kT + l16];
+#pragma unroll
+    for (int o = 0; o < kOwn; ++o)
+      if (wave + o * NW < k) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) acc[o][q] = fma(t[o][q], v, acc[o][q]);
+      }
+#pragma unroll
+    for (int o = 0; o < kOwn; ++o)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        t[o][q] = next[o][q];
+        next[o][q] = later[o][q];
+      }
+  }
 }
 
 __global__ __launch_bounds__(256) void front_clear(double *f, int64_t n) {
@@ -232,42 +404,60 @@ __global__ __launch_bounds__(256) void front_clear(double *f, int64_t n) {
 }
 
 // Entry e of a tier's fronts: the sum of its sources in their order, entries
-// of G_x (~index) and of the fronts below.
-__global__ __launch_bounds__(256) void front_gather(double *fronts, const int32_t *dst, const int32_t *ptr,
-                                                    const int32_t *src, int32_t e0, int32_t e1, const double *gx) {
-  const int32_t e = e0 + blockIdx.x * 256 + threadIdx.x;
-  if (e >= e1) return;
+// of G_x (~index) and of the fronts below; then the tier's right-hand sides,
+// a row of g and what the fronts below left.
+struct FrontSums {
+  const int32_t *dst, *ptr, *src;     // entries
+  const int32_t *rdst, *rptr, *rsrc;  // right-hand sides, by tree position less first
+  const int32_t *row_g;
+  int32_t first;
+};
+__global__ __launch_bounds__(256) void front_gather(double *fronts, FrontSums S, int32_t e0, int32_t e1, int32_t r0,
+                                                    int32_t r1, const double *gx, const double *g) {
+  const int32_t i = blockIdx.x * 256 + threadIdx.x;
   double s = 0.0;
-  for (int32_t q = ptr[e]; q < ptr[e + 1]; ++q) {
-    const int32_t at = src[q];
-    s += at < 0 ? gx[~at] : fronts[at];
+  if (i < e1 - e0) {
+    const int32_t e = e0 + i;
+    for (int32_t q = S.ptr[e]; q < S.ptr[e + 1]; ++q) {
+      const int32_t at = S.src[q];
+      s += at < 0 ? gx[~at] : fronts[at];
+    }
+    fronts[S.dst[e]] = s;
+  } else if (i - (e1 - e0) < r1 - r0) {
+    const int32_t row = r0 + i - (e1 - e0), e = row - S.first;
+    s = g[S.row_g[row]];
+    for (int32_t q = S.rptr[e]; q < S.rptr[e + 1]; ++q) s += fronts[S.rsrc[q]];
+    fronts[S.rdst[e]] = s;
   }
-  fronts[dst[e]] = s;
 }
 
-// The fronts' factors into the flat layout: per entry of the plan one of L
-// and one of U, per row its pivot, the reciprocal and the pivot test (a pivot
-// below 1e-13 times the row's largest entry of G_x, or not finite).
+// The pivot test: a pivot below 1e-13 times its row's largest entry of G_x
+// (or not finite) marks the row.
 struct FrontRow {
   int32_t front, pos, a0, a1;  // the pivot's value and flat position; entries of G_x
 };
+__global__ __launch_bounds__(256) void front_pivots(const double *fronts, const FrontRow *rows, int32_t n,
+                                                    const int32_t *row_src, const double *gx, double *stat) {
+  const int32_t e = blockIdx.x * 256 + threadIdx.x;
+  if (e >= n) return;
+  const FrontRow r = rows[e];
+  const double d = fronts[r.front];
+  double amax = 0.0;
+  for (int32_t q = r.a0; q < r.a1; ++q) amax = fmax(amax, fabs(gx[row_src[q]]));
+  if (!isfinite(d) || !(fabs(d) > 1e-13 * amax) || amax == 0.0) stat[2] = (double)(e + 1);
+}
+
+// The fronts' factors into the flat layout: per entry of the plan one of L
+// and one of U, per row its pivot.
 __global__ __launch_bounds__(256) void front_out(const double *fronts, const int2 *at, const int32_t *lo,
                                                  const int32_t *up, int32_t n, const FrontRow *rows, int32_t n_rows,
-                                                 const int32_t *row_src, FrontIo io) {
+                                                 double *lu) {
   const int32_t e = blockIdx.x * 256 + threadIdx.x;
-  if (e < n_rows) {
-    const FrontRow r = rows[e];
-    const double d = fronts[r.front];
-    double amax = 0.0;
-    for (int32_t q = r.a0; q < r.a1; ++q) amax = fmax(amax, fabs(io.gx[row_src[q]]));
-    io.lu[r.pos] = d;
-    io.rinv[e] = 1.0 / d;
-    if (!isfinite(d) || !(fabs(d) > 1e-13 * amax) || amax == 0.0) io.stat[2] = (double)(e + 1);
-  }
+  if (e < n_rows) lu[rows[e].pos] = fronts[rows[e].front];
   if (e < n) {
     const int2 f = at[e];
-    io.lu[lo[e]] = fronts[f.x];
-    io.lu[up[e]] = fronts[f.y];
+    lu[lo[e]] = fronts[f.x];
+    lu[up[e]] = fronts[f.y];
   }
 }
 
@@ -278,13 +468,16 @@ struct DevFronts {
   double *fronts = nullptr;
   int64_t leaf_values = 0, values = 0;
   const FrontNode *nodes = nullptr;
-  const int32_t *a_dst = nullptr, *a_src = nullptr;         // leaves: entries of G_x
-  const int32_t *dst = nullptr, *ptr = nullptr, *src = nullptr;  // the tiers above: sums
+  const int32_t *a_dst = nullptr, *a_src = nullptr;  // leaves: entries of G_x
+  FrontSums sums{};                                  // the tiers above
+  const int32_t *border = nullptr;                   // tree positions
+  double *xt = nullptr;                              // the step, in tree order
   const int2 *at = nullptr;                                 // per plan entry: its L and U values in the fronts
   const int32_t *lo = nullptr, *up = nullptr, *row_src = nullptr;
   const FrontRow *rows = nullptr;
   int32_t n = 0, n_ents = 0;
-  std::vector<int32_t> tier, ents, most;  // per tier: first node, first sum, most tiles of a node
+  // per tier: first node, sum and row, most tiles and tiles of own rows of a node
+  std::vector<int32_t> tier, ents, rows_at, most, most_own;
 };
 
 namespace {
@@ -302,8 +495,11 @@ rh_status f_up(DevFronts &f, const std::vector<T> &v, const T **out, std::string
 // The fronts of a network may take this much; beyond it (more than a million
 // states) the row-by-row factorisation remains.
 constexpr int64_t kMostFrontBytes = int64_t(4) << 30;
+int64_t front_values(int32_t nt) { return (int64_t)nt * nt * kTT + nt * kT; }
 
-size_t front_lds(int32_t nt) { return ((size_t)2 * (nt - 1) * kTT + 2 * (kTT + kT)) * sizeof(double); }
+size_t front_lds(int32_t nt) {
+  return ((size_t)2 * (nt - 1) * kTT + 2 * (kTT + kT) + kT + nt * kT) * sizeof(double);
+}
 
 rh_status fill(DevFronts &f, const LuPlan &lu, const LuMaps &mp, const TreePlan &p, std::string &err) {
   const int32_t n = lu.n, n_nodes = (int32_t)p.nodes.size(), tiers = (int32_t)p.tier.size() - 1;
@@ -313,15 +509,17 @@ rh_status fill(DevFronts &f, const LuPlan &lu, const LuMaps &mp, const TreePlan 
   std::vector<int32_t> owner(n);  // tree position -> node
   int64_t total = 0;
   for (int32_t t = 0; t < tiers; ++t) {
-    int32_t most = 0;
+    int32_t most = 0, most_own = 0;
     for (int32_t q = p.tier[t]; q < p.tier[t + 1]; ++q) {
       const TreeNode &nd = p.nodes[q];
-      nodes[q] = FrontNode{total, nd.ns, nd.mt, nd.mt + nd.bt, 0, 0};
-      total += (int64_t)nodes[q].nt * nodes[q].nt * kTT;
+      nodes[q] = FrontNode{total, nd.ns, nd.nb, nd.mt, nd.mt + nd.bt, 0, 0, nd.row0, nd.border0};
+      total += front_values(nodes[q].nt);
       most = std::max(most, nodes[q].nt);
+      most_own = std::max(most_own, nd.mt);
       for (int32_t a = 0; a < nd.ns; ++a) owner[nd.row0 + a] = q;
     }
     f.most.push_back(most);
+    f.most_own.push_back(most_own);
     if (t == 0) f.leaf_values = total;
   }
   f.values = total;
@@ -403,6 +601,30 @@ rh_status fill(DevFronts &f, const LuPlan &lu, const LuMaps &mp, const TreePlan 
     f.ents[t + 1] = (int32_t)dst.size();
   }
   ptr.push_back((int32_t)src.size());
+  // right-hand sides: the rows of g, and above the leaves their sums
+  std::vector<int32_t> row_g(n), rdst, rptr, rsrc;
+  for (int32_t i = 0; i < n; ++i) row_g[p.pos[i]] = lu.perm[i];
+  const int32_t first = leaves ? (p.tier[1] < n_nodes ? p.nodes[p.tier[1]].row0 : n) : 0;
+  {
+    std::vector<std::vector<int32_t>> left(n - first);
+    for (int32_t q = 0; q < n_nodes; ++q) {
+      const TreeNode &nd = p.nodes[q];
+      const int64_t r0 = nodes[q].f0 + (int64_t)nodes[q].nt * nodes[q].nt * kTT;
+      for (int32_t b = 0; b < nd.nb; ++b)
+        left[p.border[nd.border0 + b] - first].push_back((int32_t)(r0 + nd.mt * kT + b));
+    }
+    for (int32_t r = first; r < n; ++r) {
+      const FrontNode &nd = nodes[owner[r]];
+      rdst.push_back((int32_t)(nd.f0 + (int64_t)nd.nt * nd.nt * kTT + r - nd.row0));
+      rptr.push_back((int32_t)rsrc.size());
+      rsrc.insert(rsrc.end(), left[r - first].begin(), left[r - first].end());
+    }
+    rptr.push_back((int32_t)rsrc.size());
+  }
+  for (int32_t t = 0; t < tiers; ++t)
+    f.rows_at.push_back(p.tier[t] < n_nodes ? p.nodes[p.tier[t]].row0 : n);
+  f.rows_at.push_back(n);
+  f.sums.first = first;
   // the way out
   std::vector<int2> where(p.col.size());
   for (int32_t q = 0; q < n_nodes; ++q) {
@@ -421,8 +643,11 @@ rh_status fill(DevFronts &f, const LuPlan &lu, const LuMaps &mp, const TreePlan 
   f.n_ents = (int32_t)where.size();
   rh_status s;
   if ((s = f_up(f, nodes, &f.nodes, err)) != RH_OK || (s = f_up(f, a_dst, &f.a_dst, err)) != RH_OK ||
-      (s = f_up(f, a_src, &f.a_src, err)) != RH_OK || (s = f_up(f, dst, &f.dst, err)) != RH_OK ||
-      (s = f_up(f, ptr, &f.ptr, err)) != RH_OK || (s = f_up(f, src, &f.src, err)) != RH_OK ||
+      (s = f_up(f, a_src, &f.a_src, err)) != RH_OK || (s = f_up(f, dst, &f.sums.dst, err)) != RH_OK ||
+      (s = f_up(f, ptr, &f.sums.ptr, err)) != RH_OK || (s = f_up(f, src, &f.sums.src, err)) != RH_OK ||
+      (s = f_up(f, rdst, &f.sums.rdst, err)) != RH_OK || (s = f_up(f, rptr, &f.sums.rptr, err)) != RH_OK ||
+      (s = f_up(f, rsrc, &f.sums.rsrc, err)) != RH_OK || (s = f_up(f, row_g, &f.sums.row_g, err)) != RH_OK ||
+      (s = f_up(f, p.border, &f.border, err)) != RH_OK ||
       (s = f_up(f, where, &f.at, err)) != RH_OK || (s = f_up(f, p.lo, &f.lo, err)) != RH_OK ||
       (s = f_up(f, p.up, &f.up, err)) != RH_OK || (s = f_up(f, rows, &f.rows, err)) != RH_OK ||
       (s = f_up(f, mp.a_src, &f.row_src, err)) != RH_OK)
@@ -431,6 +656,9 @@ rh_status fill(DevFronts &f, const LuPlan &lu, const LuMaps &mp, const TreePlan 
   HIP_TRY(hipMalloc(&m, std::max<size_t>(1, (size_t)f.values) * sizeof(double)));
   f.allocs.push_back(m);
   f.fronts = static_cast<double *>(m);
+  HIP_TRY(hipMalloc(&m, std::max<size_t>(1, n) * sizeof(double)));
+  f.allocs.push_back(m);
+  f.xt = static_cast<double *>(m);
   for (const void *kernel : {reinterpret_cast<const void *>(&front_factor<kLeafWaves, true>),
                              reinterpret_cast<const void *>(&front_factor<kUpperWaves, false>)})
     HIP_TRY(hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
@@ -445,7 +673,7 @@ rh_status fronts_build(const LuPlan &lu, const LuMaps &mp, DevFronts **out, std:
   const TreePlan p = tree_plan(lu, mp.row_ptr);
   if (!p.ok) return RH_OK;
   int64_t total = 0;
-  for (const TreeNode &nd : p.nodes) total += (int64_t)(nd.mt + nd.bt) * (nd.mt + nd.bt) * kTT;
+  for (const TreeNode &nd : p.nodes) total += front_values(nd.mt + nd.bt);
   if (total * (int64_t)sizeof(double) > kMostFrontBytes) return RH_OK;
   DevFronts *f = new DevFronts();
   const rh_status s = fill(*f, lu, mp, p, err);
@@ -474,18 +702,43 @@ rh_status fronts_refactor(const DevFronts &f, const FrontIo &io, std::string &er
     const size_t lds = front_lds(std::max(1, f.most[t]));
     if (t == 0 && tiers > 1) {
       hipLaunchKernelGGL((front_factor<kLeafWaves, true>), dim3(nodes), dim3(kLeafWaves * 64), lds, nullptr, f.fronts,
-                         f.nodes, 0, f.a_dst, f.a_src, io.gx);
+                         f.nodes, 0, f.a_dst, f.a_src, f.sums.row_g, io.gx, io.g);
       continue;
     }
-    const int32_t e0 = f.ents[t], e1 = f.ents[t + 1];
-    if (e1 > e0)
-      hipLaunchKernelGGL(front_gather, dim3((e1 - e0 + 255) / 256), dim3(256), 0, nullptr, f.fronts, f.dst, f.ptr,
-                         f.src, e0, e1, io.gx);
+    const int32_t e0 = f.ents[t], e1 = f.ents[t + 1], r0 = f.rows_at[t], r1 = f.rows_at[t + 1];
+    if (e1 - e0 + r1 - r0 > 0)
+      hipLaunchKernelGGL(front_gather, dim3((e1 - e0 + r1 - r0 + 255) / 256), dim3(256), 0, nullptr, f.fronts, f.sums, e0,
+                         e1, r0, r1, io.gx, io.g);
     hipLaunchKernelGGL((front_factor<kUpperWaves, false>), dim3(nodes), dim3(kUpperWaves * 64), lds, nullptr, f.fronts,
-                       f.nodes, f.tier[t], f.a_dst, f.a_src, io.gx);
+                       f.nodes, f.tier[t], f.a_dst, f.a_src, f.sums.row_g, io.gx, io.g);
   }
+  hipLaunchKernelGGL(front_pivots, dim3((f.n + 255) / 256), dim3(256), 0, nullptr, f.fronts, f.rows, f.n, f.row_src,
+                     io.gx, io.stat);
+  HIP_TRY(hipGetLastError());
+  return RH_OK;
+}
+
+rh_status fronts_solve(const DevFronts &f, const FrontIo &io, std::string &err) {
+  const int32_t tiers = (int32_t)f.tier.size() - 1;
+  for (int32_t t = tiers - 1; t >= 0; --t) {
+    const uint32_t nodes = (uint32_t)(f.tier[t + 1] - f.tier[t]);
+    if (t == 0 && tiers > 1)
+      hipLaunchKernelGGL((front_back<kLeafWaves, 1>), dim3(nodes), dim3(kLeafWaves * 64), 0, nullptr, f.fronts, f.nodes, 0,
+                         f.border, f.sums.row_g, f.xt, io.x);
+    else if (f.most_own[t] <= kUpperWaves)
+      hipLaunchKernelGGL((front_back<kUpperWaves, 1>), dim3(nodes), dim3(kUpperWaves * 64), 0, nullptr, f.fronts, f.nodes,
+                         f.tier[t], f.border, f.sums.row_g, f.xt, io.x);
+    else
+      hipLaunchKernelGGL((front_back<kUpperWaves, 2>), dim3(nodes), dim3(kUpperWaves * 64), 0, nullptr, f.fronts, f.nodes,
+                         f.tier[t], f.border, f.sums.row_g, f.xt, io.x);
+  }
+  HIP_TRY(hipGetLastError());
+  return RH_OK;
+}
+
+rh_status fronts_factors(const DevFronts &f, const FrontIo &io, std::string &err) {
   hipLaunchKernelGGL(front_out, dim3((std::max(f.n_ents, f.n) + 255) / 256), dim3(256), 0, nullptr, f.fronts, f.at,
-                     f.lo, f.up, f.n_ents, f.rows, f.n, f.row_src, io);
+                     f.lo, f.up, f.n_ents, f.rows, f.n, io.lu);
   HIP_TRY(hipGetLastError());
   return RH_OK;
 }

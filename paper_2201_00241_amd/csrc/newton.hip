@@ -18,7 +18,8 @@
 //      in LDS), except the last rows (the top of the elimination tree, where
 //      the factors are nearly dense), which after their steps with earlier
 //      rows are factored as one dense block by one workgroup, in registers;
-//   5. the Newton step from the two triangular solves (the rows below the
+//   5. the Newton step from the two triangular solves (with the fronts L y =
+//      P g comes with the factorisation; else the rows below the
 //      dense block by levels, the block by dense substitution), and
 //      x -= step.
 // After convergence the state and the factors are copied to the host, which
@@ -482,15 +483,6 @@ __global__ __launch_bounds__(kNtThreads) void nt_dense_lu(const NtArgs A) {
   }
 }
 
-// The dense block's factors out of the flat ones, for the Newton step's
-// solves (the fronts write the flat ones only).
-__global__ __launch_bounds__(256) void nt_block_copy(const NtArgs A) {
-  const int32_t m = A.a.m_blk, e = blockIdx.x * 256 + threadIdx.x;
-  if (e >= m * m) return;
-  const int32_t p = A.a.dmap[e];
-  A.w.S[e] = p >= 0 ? A.w.lu[A.a.row_ptr[A.a.b0 + e / m] + p] : 0.0;
-}
-
 // ---- Newton step: y = P g; L y; U y; x -= P^T y ---------------------------
 // One wave per row: lanes take the row's entries in turn and the wave sums.
 // Y is the vector being solved (global memory, or its copy in LDS).
@@ -875,6 +867,11 @@ rh_status nt_build(Network &net, DevNewton &d, std::string &err) {
   return RH_OK;
 }
 
+FrontIo front_io(const DevNewton &d) {
+  const NtVectors &w = d.args.w;
+  return FrontIo{w.gx, w.g, w.lu, w.stat, w.x};
+}
+
 rh_status nt_step_kernels(DevNewton &d, int32_t m, int32_t nb, int32_t nnz_gx, bool jacobian, std::string &err) {
   const int T = 256;
   hipLaunchKernelGGL(nt_state, dim3((nb + T - 1) / T), dim3(T), 0, nullptr, d.args);
@@ -885,11 +882,8 @@ rh_status nt_step_kernels(DevNewton &d, int32_t m, int32_t nb, int32_t nnz_gx, b
     hipLaunchKernelGGL(nt_gx, dim3((nnz_gx + T - 1) / T), dim3(T), 0, nullptr, d.args);
     const int32_t mb = d.args.a.m_blk;
     if (d.fronts) {
-      const NtVectors &w = d.args.w;
-      const rh_status fs = fronts_refactor(*d.fronts, FrontIo{w.gx, w.lu, w.rinv, w.stat}, err);
-      if (fs != RH_OK) return fs;
-      if (mb > 0) hipLaunchKernelGGL(nt_block_copy, dim3((mb * mb + T - 1) / T), dim3(T), 0, nullptr, d.args);
-      return RH_OK;
+      HIP_TRY(hipGetLastError());
+      return fronts_refactor(*d.fronts, front_io(d), err);
     }
     const size_t lds_w = (size_t)d.args.a.maxpat * sizeof(double) * kNtWideWaves;
     const std::vector<int32_t> &rows = d.lev_rows_f;
@@ -921,6 +915,7 @@ rh_status nt_step_kernels(DevNewton &d, int32_t m, int32_t nb, int32_t nnz_gx, b
 // with earlier rows, then the block; the U sweep the block first (one kernel
 // for the block's two solves), then the rows below it by levels.
 rh_status nt_solve_kernels(DevNewton &d, std::string &err) {
+  if (d.fronts) return fronts_solve(*d.fronts, front_io(d), err);
   const int T = 256;
   const int32_t n = d.args.a.n_x, mb = d.args.a.m_blk;
   auto levels = [&](const std::vector<int32_t> &rows, int32_t upper) {
@@ -1018,6 +1013,10 @@ rh_status device_newton(Network &net, double tol, int32_t max_iter, NewtonResult
   }
   // the accepted state and the factors of G_x there (from the last step's
   // kernels, which ran at this x)
+  if (d.fronts) {
+    const rh_status fs = fronts_factors(*d.fronts, front_io(d), err);
+    if (fs != RH_OK) return fs;
+  }
   res.x.resize(net.n_x);
   HIP_TRY(hipMemcpy(res.x.data(), w.x, net.n_x * sizeof(double), hipMemcpyDeviceToHost));
   std::vector<double> luv(d.row_ptr.back());

@@ -97,19 +97,16 @@ rh_status dense_spd_solve(int device, int32_t n, double *A, int64_t lda, double 
                           void *stream, int32_t &failed_col, std::string &err) {
   TR_TRY(hipSetDevice(device));
   hipStream_t st = static_cast<hipStream_t>(stream);
-  int32_t *info = nullptr;
-  double *work = nullptr;
-  TR_TRY(hipMalloc(&info, dense_info_bytes()));
-  {
-    hipError_t e = hipMalloc(&work, std::max<size_t>(1, (size_t)n * std::max(1, nrhs)) * sizeof(double));
-    if (e != hipSuccess) {
-      (void)hipFree(info);
-      err = std::string("dense solve workspace: ") + hipGetErrorString(e);
-      return RH_ENOMEM;
-    }
+  // one allocation: the status word's memory and the solution
+  char *work = nullptr;
+  const size_t head = dense_info_bytes();
+  if (hipMalloc(&work, head + (size_t)n * std::max(1, nrhs) * sizeof(double)) != hipSuccess) {
+    err = "dense solve workspace: out of memory";
+    return RH_ENOMEM;
   }
+  int32_t *info = reinterpret_cast<int32_t *>(work);
   rh_status s = dense_cholesky(n, A, lda, B, ldb, nrhs, info, stream, err);
-  if (s == RH_OK) s = dense_back_solve(n, A, lda, B, ldb, nrhs, work, info, stream, err);
+  if (s == RH_OK) s = dense_back_solve(n, A, lda, B, ldb, nrhs, reinterpret_cast<double *>(work + head), info, stream, err);
   int32_t h = 0;
   if (s == RH_OK) {
     hipError_t e = hipMemcpyAsync(&h, info, sizeof h, hipMemcpyDeviceToHost, st);
@@ -120,7 +117,6 @@ rh_status dense_spd_solve(int device, int32_t n, double *A, int64_t lda, double 
     }
   }
   if (s != RH_OK) (void)hipStreamSynchronize(st);  // the launches may still use the buffers
-  (void)hipFree(info);
   (void)hipFree(work);
   failed_col = h > 0 ? h - 1 : -1;
   return s;

@@ -133,7 +133,7 @@ TreePlan tree_plan(const LuPlan &lu, const std::vector<int32_t> &row_ptr) {
   std::vector<std::vector<std::vector<int32_t>>> tiers;
   std::vector<int32_t> rest(n);
   for (int32_t i = 0; i < n; ++i) rest[i] = i;
-  while ((int32_t)rest.size() > kTreeTopRows) {
+  while ((int32_t)rest.size() > (tiers.empty() ? kTreeSingleRows : kTreeTopRows)) {
     const bool leaf = tiers.empty();
     const int32_t most = leaf ? kLeafTiles : kUpperTiles;
     bool done = false;
@@ -147,6 +147,7 @@ TreePlan tree_plan(const LuPlan &lu, const std::vector<int32_t> &row_ptr) {
       rest = std::move(c.rest);
       done = true;
     }
+    if (!done && tiers.empty() && n <= kTreeTopRows) break;
     if (!done || tiers.size() > 10) return plan;
   }
   std::sort(rest.begin(), rest.end(), [&](int32_t a, int32_t b) { return post[a] < post[b]; });

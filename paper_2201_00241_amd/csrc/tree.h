@@ -60,6 +60,10 @@ constexpr int kWaveProds = 64, kLeafProds = 6;
 // so nodes are as large as one workgroup solves in about the launch's own
 // time.
 constexpr int kTreeLeafRows = 64, kTreeUpperRows = 256, kTreeTopRows = 448;
+// A network of more rows than this has leaves: the fronts of fronts.hip are
+// factored by one workgroup each (a tracking step at 200 buses, 379 rows, takes
+// 3.06 ms with a single front and 1.64 ms with leaves).
+constexpr int kTreeSingleRows = 64;
 // Row tiles (own and border) a node may have: a lane group of a workgroup
 // stages four own rows and up to eight in all, and a leaf's products fit the
 // waves' registers.

@@ -159,7 +159,7 @@ def test_full_hessian_into_a_padded_buffer(solved, k_block):
 # one node (up to 448 states), two tiers, three tiers; sizes that end within
 # and at a tile
 @pytest.mark.gpu
-@pytest.mark.parametrize("n_bus", [9, 60, 75, 120, 260, 1000, 2600])
+@pytest.mark.parametrize("n_bus", [9, 60, 75, 120, 200, 260, 1000, 2100, 2600])
 def test_device_factors_by_fronts(n_bus):
     torch = pytest.importorskip("torch")
     if not torch.cuda.is_available():

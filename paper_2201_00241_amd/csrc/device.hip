@@ -2712,16 +2712,18 @@ rh_status upload_groups(Network &net, DeviceNet *dn, const std::function<rh_stat
 // the same whatever the network's size, while the one-workgroup path takes as
 // long as its longest chain of dependent steps; neither depends on k until the
 // chip is full.  Measured in us, one-workgroup | tree:
-//   states           4,749       9,499       13,299      18,999      38,571
-//   FP64, k = 1      98 | 109   160 | 116   216 | 124   288 | 148  1627 | 204
-//   FP64, k = 256   103 | 154   169 | 187   221 | 214   296 | 262      -
-//   refined, k = 1  201 | 287   363 | 290   492 | 305   671 | 340  1321 | 470
-//   refined, k = 256 216 | 414  370 | 504   511 | 575   711 | 711      -
-// (256 directions are one workgroup per CU, the other path's best case.)  The
-// choice cannot depend on k, as a direction's bits may not, and both
-// precisions go one way, so that only one path's arrays are uploaded: the line
-// is where no case is slower.
-constexpr int32_t kTreeMinStates = 18000;
+//   states            7,599       9,499      11,399      13,299      18,999
+//   FP64, k = 1      131 | 107   163 | 114   189 | 116   217 | 121   288 | 146
+//   FP64, k = 128    129 | 140   160 | 156   186 | 163   211 | 169   280 | 210
+//   FP64, k = 256    135 | 166   168 | 184   193 | 197   221 | 208   296 | 262
+//   refined, k = 1   292 | 249   364 | 254   425 | 254   492 | 262   671 | 290
+//   refined, k = 128 284 | 328   350 | 381   410 | 397   473 | 386   649 | 473
+//   refined, k = 256 307 | 386   375 | 445   442 | 473   511 | 496   711 | 599
+// (256 directions are one workgroup per CU, the other path's best case; 257
+// take it twice as long.)  The choice cannot depend on k, as a direction's
+// bits may not, and both precisions go one way, so that only one path's arrays
+// are uploaded: the line is where no case is slower.
+constexpr int32_t kTreeMinStates = 13000;
 
 bool tree_wanted(const Network &net) {
   return net.n_x >= kTreeMinStates && !std::getenv("RH_DIRS_PER_GROUP") && !std::getenv("RH_NO_LDS");

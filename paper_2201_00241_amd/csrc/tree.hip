@@ -47,9 +47,9 @@ constexpr int kTileVals = kT * kT;  // a tile in operand order: value [s][lane] 
                                     // (lane mod 16, 4 s + lane / 16)
 // Workgroups a tier's launch has at most where a node has several chunks to
 // take: what the chip holds at once, twice over.
-constexpr uint32_t kLeafGroups = 2048, kProjGroups = 8192;
-// Chunks a leaf workgroup takes in turn at most (it keeps a bit for each).
-constexpr int32_t kLeafChunks = 64;
+constexpr uint32_t kLeafGroups = 2048, kProjGroups = 8192, kResGroups = 1024;
+// Chunks a workgroup takes in turn at most (it keeps a bit for each).
+constexpr int32_t kChunkRun = 64;
 // Dynamic LDS of a workgroup: 160 KB less the little that is static.
 constexpr size_t kTreeLds = 159 * 1024;
 
@@ -193,21 +193,34 @@ __device__ __forceinline__ double w_of(const TreeItem &it, const ChunkBuf &m, in
   return get<double>(m, (uint32_t)q * kRow64 + (uint32_t)l16 * 8);
 }
 
-// Refined mode: whether the lane's direction still takes corrections in
-// iteration `iter` of solve `which` (0: Z, 1: Psi), from the norms of the
-// iterations before: {max |r|, max |x|} per iteration and direction.
+// Refined mode: {max |r|, max |x|} of a chunk's directions after iteration
+// `iter` of solve `which` (0: Z, 1: Psi).  Zero for a direction that took no
+// correction in it.
 __device__ __forceinline__ const double *norms_at(const TreeArgs &a, int32_t chunk, int which, int iter) {
   return a.norms + (((int64_t)chunk * 2 + which) * a.norm_iters + iter) * 2 * kD;
 }
+// Whether direction l16 of the chunk still takes corrections in iteration
+// `iter`: the iteration before left it a residual above the tolerance (one
+// that had stopped earlier has zero norms there, and zero is not above zero).
 __device__ __forceinline__ bool still_active(const TreeArgs &a, const TreeDesc AS4 &td, int32_t chunk, int which,
                                              int iter, int l16) {
-  bool act = true;
-  const double an = which ? td.norm_t : td.norm_n;
-  for (int i = 0; i < iter; ++i) {
-    const double *nm = norms_at(a, chunk, which, i);
-    act = act && !(nm[l16] <= a.tol * (an * nm[kD + l16]));
+  if (iter == 0) return true;
+  const double *nm = norms_at(a, chunk, which, iter - 1);
+  return !(nm[l16] <= a.tol * ((which ? td.norm_t : td.norm_n) * nm[kD + l16]));
+}
+// Bit c: whether chunk first + c has such directions, up to chunk end - 1 (at
+// most kChunkRun of them); the same in every lane.  Four chunks a trip.
+__device__ __forceinline__ uint64_t active_chunks(const TreeArgs &a, const TreeDesc AS4 &td, int32_t first, int32_t end,
+                                                  int which, int iter) {
+  if (iter == 0) return ~uint64_t(0);
+  const int lane = threadIdx.x & 63;
+  uint64_t active = 0;
+  for (int32_t c = 0; c < end - first; c += 4) {
+    const int32_t chunk = first + c + (lane >> 4);
+    const uint64_t b = __ballot(chunk < end && still_active(a, td, min(chunk, end - 1), which, iter, lane & 15));
+    for (int g = 0; g < 4; ++g) active |= (uint64_t)((b >> (16 * g) & 0xffff) != 0) << (c + g);
   }
-  return act;
+  return active;
 }
 
 // The matrices of sweep `s` (0: L, 1: U, 2: U^T, 3: L^T) in operand order.
@@ -282,6 +295,53 @@ __device__ __forceinline__ void row_fma(double &acc, const W (&w)[AT], double v,
     row_fma<J + 1, AT, W>(acc, w, v, n);
   }
 }
+// The same for columns whose values lie at base + bytes * column in a chunk's
+// memory (S: their type; l16: added per lane): every row's first AT loads are
+// issued without a test, those past the row's end reading zero (kNone), so
+// that nothing but the sum depends on the rows' lengths.  rows_at turns the
+// columns into offsets.
+template <int N>
+__device__ __forceinline__ void rows_at(SparseRows<N> &s, uint32_t base, uint32_t bytes, int l16) {
+#pragma unroll
+  for (int j = 0; j < N; ++j) s.c[j] = (int32_t)(l16 < s.n[j] ? base + (uint32_t)s.c[j] * bytes : kNone);
+}
+template <int J, int AT, class S>
+__device__ __forceinline__ void row_values(S (&w)[AT], int32_t c, const ChunkBuf &m, uint32_t lane_off) {
+  if constexpr (J < AT) {
+    w[J] = get<S>(m, (uint32_t)row_bcast<J>(c) + lane_off);
+    row_values<J + 1, AT, S>(w, c, m, lane_off);
+  }
+}
+template <int J, int AT, class S>
+__device__ __forceinline__ void row_dot(double &acc, const S (&w)[AT], double v) {
+  if constexpr (J < AT) {
+    acc = fma(row_bcast<J>(v), (double)w[J], acc);
+    row_dot<J + 1, AT, S>(acc, w, v);
+  }
+}
+template <int AT, class S, int N>
+__device__ __forceinline__ void rows_sum_at(const SparseRows<N> &s, const int32_t *col, const double *val, uint32_t base,
+                                            uint32_t bytes, const ChunkBuf &m, int l16, double (&acc)[N]) {
+  const uint32_t lane_off = (uint32_t)l16 * (uint32_t)sizeof(S);
+  S w[N][AT];
+#pragma unroll
+  for (int j = 0; j < N; ++j) row_values<0, AT, S>(w[j], s.c[j], m, lane_off);
+#pragma unroll
+  for (int j = 0; j < N; ++j) {
+    acc[j] = 0.0;
+    row_dot<0, AT, S>(acc[j], w[j], s.v[j]);
+  }
+#pragma unroll
+  for (int j = 0; j < N; ++j) {
+    if (s.n[j] <= AT) continue;
+    row_rest<AT>(acc[j], s.v[j], s.c[j], min(16, s.n[j]), [&](int32_t o) { return get<S>(m, (uint32_t)o + lane_off); });
+    for (int32_t e = 16; e < s.n[j]; ++e) {
+      const int32_t at = s.e[j] + e;
+      acc[j] = fma(val[at], (double)get<S>(m, base + (uint32_t)col[at] * bytes + lane_off), acc[j]);
+    }
+  }
+}
+
 template <int AT, int N, class F>
 __device__ __forceinline__ void rows_sum(const SparseRows<N> &s, const int32_t *col, const double *val, int l16, F x,
                                          double (&acc)[N]) {
@@ -490,7 +550,8 @@ __global__ __launch_bounds__(kLeafWaves * 64, 4) void tree_leaf(const TreeArgs a
     const TreeItem it = item_of(a, chunk);
     const TreeDesc AS4 &td = desc_of(it);
     const int32_t end = min(c1, it.chunk0 + it.chunks);
-    if (td.n_tiers < 2 || (int32_t)blockIdx.x >= td.tier[1]) {  // no such leaf in this network
+    uint64_t active = kRef ? active_chunks(a, td, chunk, end, which, iter) : ~uint64_t(0);
+    if (td.n_tiers < 2 || (int32_t)blockIdx.x >= td.tier[1] || !active) {  // no such leaf in this network
       chunk = end;
       continue;
     }
@@ -550,18 +611,6 @@ __global__ __launch_bounds__(kLeafWaves * 64, 4) void tree_leaf(const TreeArgs a
       // stores in flight.
 #pragma unroll
       for (int o = 0; o < 8; ++o) put(m, kNone, T(0));
-    }
-    // Refined mode: the chunks (at most kLeafChunks) with directions that
-    // still take corrections.
-    uint64_t active = ~uint64_t(0);
-    if (kRef && iter > 0) {
-      active = 0;
-      for (int32_t c = chunk; c < end; ++c)
-        active |= (uint64_t)(__any(still_active(a, td, c, which, iter, l16)) != 0) << (c - chunk);
-      if (!active) {
-        chunk = end;
-        continue;
-      }
     }
     for (; chunk < end; ++chunk, active >>= 1) {
       const ChunkBuf m = chunk_buf(a, chunk);
@@ -926,7 +975,8 @@ __global__ __launch_bounds__(256) void tree_out(const TreeArgs a) {
   }
   SparseRows<kRows> gt;
   rows_load(gt, td.gpt_ptr, td.gpt_row, td.gpt_val, l16, par);
-  rows_sum<4>(gt, td.gpt_row, td.gpt_val, l16, [&](int32_t r) { return get<double>(m, psi + (uint32_t)(r * kD + l16) * 8u); }, acc);
+  rows_at(gt, psi, kRow64, l16);
+  rows_sum_at<8, double>(gt, td.gpt_row, td.gpt_val, psi, kRow64, m, l16, acc);
 #pragma unroll
   for (int j = 0; j < kRows; ++j) s[slot + j * 16][l16] = (__builtin_isnan(c2[j]) ? p[j] : __dmul_rn(c2[j], w[j])) + acc[j];
   __syncthreads();
@@ -959,57 +1009,79 @@ __global__ __launch_bounds__(256) void tree_out(const TreeArgs a) {
 // corrections (d the FP32 correction just solved for, x in Z, r in Y, both
 // FP64), and the norms max |r|, max |x| of the iteration (non-negative
 // doubles compare as their bits).
-constexpr int kResRows = 128, kResAt = 8;
-__global__ __launch_bounds__(512) void tree_residual(const TreeArgs a, int which, int iter) {
-  __shared__ double s_m[32][2][kD];
-  const int32_t chunk = blockIdx.y;
-  const TreeItem it = item_of(a, chunk);
-  const TreeDesc AS4 &td = desc_of(it);
+//
+// A workgroup takes its rows for several chunks in turn, so that the rows'
+// entries are read once, and stops at once where none of them takes a
+// correction (the norms of four chunks are read in one trip).  Bound by the
+// chunks' traffic: 16 chunks at 10k buses move 133 MB (171 from the second
+// iteration on) in 39 to 47 us, 53 with a chunk per workgroup; with nothing to
+// do a launch takes 4 us, 10 before.
+constexpr int kResRows = 64, kResAt = 8;
+__global__ __launch_bounds__(512) void tree_residual(const TreeArgs a, int which, int iter, int per) {
+  __shared__ double s_m[2][8][2][kD];
+  const int tid = threadIdx.x, slot = tid >> 4, l16 = tid & 15, wave = tid >> 6;
   const int32_t r0 = blockIdx.x * kResRows;
-  if (r0 >= td.n_x) return;
-  const ChunkBuf m = chunk_buf(a, chunk);
-  const ChunkOff off = chunk_off(td);
-  const int tid = threadIdx.x, slot = tid >> 4, l16 = tid & 15;
-  const bool act = still_active(a, td, chunk, which, iter, l16);
-  if (!__syncthreads_or(act ? 1 : 0)) return;
-  const int32_t *ptr = which ? td.at_ptr : td.an_ptr, *col = which ? td.at_col : td.an_col;
-  const double *val = which ? td.at_val : td.an_val;
-  double rm = 0.0, xm = 0.0;
-  constexpr int kRows = kResRows / 32;
-  auto row = [&](int j) { return r0 + slot + j * 32 < td.n_x ? r0 + slot + j * 32 : -1; };
-  double y[kRows], z[kRows], acc[kRows];
-  float d[kRows];
-  uint32_t at[kRows];
+  const int32_t c1 = min((int32_t)blockIdx.y * per + per, a.n_chunks);
+  int buf = 0;
+  for (int32_t chunk = (int32_t)blockIdx.y * per; chunk < c1;) {
+    const TreeItem it = item_of(a, chunk);
+    const TreeDesc AS4 &td = desc_of(it);
+    const int32_t end = min(c1, it.chunk0 + it.chunks);
+    const uint64_t active = active_chunks(a, td, chunk, end, which, iter);
+    if (r0 >= td.n_x || !active) {
+      chunk = end;
+      continue;
+    }
+    const ChunkOff off = chunk_off(td);
+    const int32_t *ptr = which ? td.at_ptr : td.an_ptr, *col = which ? td.at_col : td.an_col;
+    const double *val = which ? td.at_val : td.an_val;
+    constexpr int kRows = kResRows / 32;
+    auto row = [&](int j) { return r0 + slot + j * 32 < td.n_x ? r0 + slot + j * 32 : -1; };
+    SparseRows<kRows> s;
+    rows_load(s, ptr, col, val, l16, row);
+    rows_at(s, off.U, kRow32, l16);
+    const int32_t first = chunk;
+    for (; chunk < end; ++chunk) {
+      if (!(active >> (chunk - first) & 1)) continue;
+      const bool act = still_active(a, td, chunk, which, iter, l16);
+      const ChunkBuf m = chunk_buf(a, chunk);
+      double y[kRows], z[kRows], acc[kRows], rm = 0.0, xm = 0.0;
+      float d[kRows];
 #pragma unroll
-  for (int j = 0; j < kRows; ++j) {
-    at[j] = row(j) >= 0 ? (uint32_t)(row(j) * kD + l16) : kNone / 8;
-    y[j] = get<double>(m, at[j] == kNone / 8 ? kNone : off.Y + at[j] * 8u);
-    z[j] = get<double>(m, at[j] == kNone / 8 || iter == 0 ? kNone : off.Z + at[j] * 8u);
-    d[j] = get<float>(m, at[j] == kNone / 8 ? kNone : off.U + at[j] * 4u);
-  }
-  SparseRows<kRows> s;
-  rows_load(s, ptr, col, val, l16, row);
-  rows_sum<kResAt>(
-      s, col, val, l16, [&](int32_t c) { return get<float>(m, off.U + (uint32_t)(c * kD + l16) * 4u); }, acc);
+      for (int j = 0; j < kRows; ++j) {
+        const uint32_t at = (uint32_t)(row(j) * kD + l16);
+        y[j] = get<double>(m, row(j) < 0 ? kNone : off.Y + at * 8u);
+        z[j] = get<double>(m, row(j) < 0 || iter == 0 ? kNone : off.Z + at * 8u);
+        d[j] = get<float>(m, row(j) < 0 ? kNone : off.U + at * 4u);
+      }
+      rows_sum_at<kResAt, float>(s, col, val, off.U, kRow32, m, l16, acc);
 #pragma unroll
-  for (int j = 0; j < kRows; ++j) {
-    if (!act || row(j) < 0) continue;
-    const double r = y[j] - acc[j], x = z[j] + (double)d[j];
-    put(m, off.Y + at[j] * 8u, r);
-    put(m, off.Z + at[j] * 8u, x);
-    rm = fmax(rm, fabs(r));
-    xm = fmax(xm, fabs(x));
-  }
-  s_m[slot][0][l16] = rm;
-  s_m[slot][1][l16] = xm;
-  __syncthreads();
-  if (tid < 2 * kD) {
-    const int w = tid >> 4;
-    double v = 0.0;
-    for (int s = 0; s < 32; ++s) v = fmax(v, s_m[s][w][l16]);
-    if (act) {
-      double *nm = const_cast<double *>(norms_at(a, chunk, which, iter)) + w * kD + l16;
-      atomicMax(reinterpret_cast<unsigned long long *>(nm), (unsigned long long)__double_as_longlong(v));
+      for (int j = 0; j < kRows; ++j) {
+        if (!act || row(j) < 0) continue;
+        const uint32_t at = (uint32_t)(row(j) * kD + l16);
+        const double r = y[j] - acc[j], x = z[j] + (double)d[j];
+        put(m, off.Y + at * 8u, r);
+        put(m, off.Z + at * 8u, x);
+        rm = fmax(rm, fabs(r));
+        xm = fmax(xm, fabs(x));
+      }
+      for (int o = 16; o <= 32; o <<= 1) {
+        rm = fmax(rm, __shfl_xor(rm, o));
+        xm = fmax(xm, __shfl_xor(xm, o));
+      }
+      if ((tid & 63) < kD) {
+        s_m[buf][wave][0][l16] = rm;
+        s_m[buf][wave][1][l16] = xm;
+      }
+      __syncthreads();  // (the buffer after the next is this one again: one barrier is enough)
+      if (tid < 2 * kD && act) {
+        const int w = tid >> 4;
+        double v = 0.0;
+        for (int q = 0; q < 8; ++q) v = fmax(v, s_m[buf][q][w][l16]);
+        double *nm = const_cast<double *>(norms_at(a, chunk, which, iter)) + w * kD + l16;
+        atomicMax(reinterpret_cast<unsigned long long *>(nm), (unsigned long long)__double_as_longlong(v));
+      }
+      buf ^= 1;
     }
   }
 }
@@ -1634,7 +1706,7 @@ rh_status tree_launch(const std::vector<TreeRequest> &req, const std::vector<Tre
       // grid is a multiple of eight: its matrices stay in that XCD's L2
       const uint32_t gx = q == 0 ? (uint32_t)((nodes[0] + 7) & ~7) : (uint32_t)nodes[q];
       const uint32_t most = q == 0 ? std::max<uint32_t>(1, kLeafGroups / gx) : nc;
-      const int per = std::min<int>(kLeafChunks, (int)((nc + most - 1) / most));
+      const int per = std::min<int>(kChunkRun, (int)((nc + most - 1) / most));
       const dim3 grid(gx, (nc + per - 1) / per), block((q == 0 ? kLeafWaves : kUpperWaves) * 64);
       a.lds_rows = (q == 0 ? leaf : upper) * kT;
       const size_t lds = (per > 1 ? 2 : 1) * (size_t)a.lds_rows * kD * el + (q == 0 ? 0 : parts);
@@ -1677,8 +1749,11 @@ rh_status tree_launch(const std::vector<TreeRequest> &req, const std::vector<Tre
       else
         hipLaunchKernelGGL((tree_top<double, false>), dim3(nc), tb, top_lds, s, a, which, iter);
       for (int32_t q = tiers - 1; q >= 0; --q) tier_launch(q, false, which, iter);
-      if (ref)
-        hipLaunchKernelGGL(tree_residual, dim3((n_x + kResRows - 1) / kResRows, nc), dim3(512), 0, s, a, which, iter);
+      if (ref) {
+        const uint32_t gx = (uint32_t)((n_x + kResRows - 1) / kResRows), most = std::max<uint32_t>(1, kResGroups / gx);
+        const int per = std::min<int>(kChunkRun, (int)((nc + most - 1) / most));
+        hipLaunchKernelGGL(tree_residual, dim3(gx, (nc + per - 1) / per), dim3(512), 0, s, a, which, iter, per);
+      }
     };
     if (dirs || ref || stamps)
       hipLaunchKernelGGL(tree_in, dim3((n_p + kMoveRows - 1) / kMoveRows, nc), dim3(256), 0, s, a);

@@ -2712,18 +2712,18 @@ rh_status upload_groups(Network &net, DeviceNet *dn, const std::function<rh_stat
 // the same whatever the network's size, while the one-workgroup path takes as
 // long as its longest chain of dependent steps; neither depends on k until the
 // chip is full.  Measured in us, one-workgroup | tree:
-//   states            7,599       9,499      11,399      13,299      18,999
-//   FP64, k = 1      131 | 107   163 | 114   189 | 116   217 | 121   288 | 146
-//   FP64, k = 128    129 | 140   160 | 156   186 | 163   211 | 169   280 | 210
-//   FP64, k = 256    135 | 166   168 | 184   193 | 197   221 | 208   296 | 262
-//   refined, k = 1   292 | 249   364 | 254   425 | 254   492 | 262   671 | 290
-//   refined, k = 128 284 | 328   350 | 381   410 | 397   473 | 386   649 | 473
-//   refined, k = 256 307 | 386   375 | 445   442 | 473   511 | 496   711 | 599
+//   states            9,499      11,399      13,299      15,199      17,099
+//   FP64, k = 1      163 | 114   189 | 116   213 | 121   232 | 132   264 | 135
+//   FP64, k = 128    160 | 156   186 | 163   209 | 170   228 | 184   257 | 189
+//   FP64, k = 256    168 | 184   193 | 197   220 | 210   240 | 225   272 | 231
+//   refined, k = 1   -           -           491 | 272   534 | 289   610 | 297
+//   refined, k = 128 -           -           474 | 421   520 | 451   597 | 480
+//   refined, k = 256 -           -           511 | 535   561 | 571   643 | 613
 // (256 directions are one workgroup per CU, the other path's best case; 257
 // take it twice as long.)  The choice cannot depend on k, as a direction's
 // bits may not, and both precisions go one way, so that only one path's arrays
 // are uploaded: the line is where no case is slower.
-constexpr int32_t kTreeMinStates = 13000;
+constexpr int32_t kTreeMinStates = 16000;
 
 bool tree_wanted(const Network &net) {
   return net.n_x >= kTreeMinStates && !std::getenv("RH_DIRS_PER_GROUP") && !std::getenv("RH_NO_LDS");

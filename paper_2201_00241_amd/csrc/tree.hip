@@ -54,32 +54,43 @@ constexpr int32_t kChunkRun = 64;
 constexpr size_t kTreeLds = 159 * 1024;
 
 typedef double v4d __attribute__((ext_vector_type(4)));
-typedef float v4f __attribute__((ext_vector_type(4)));
 
-template <class T>
-struct Vec4;
-template <>
-struct Vec4<double> {
-  typedef v4d type;
-};
-template <>
-struct Vec4<float> {
-  typedef v4f type;
-};
+typedef float v4f __attribute__((ext_vector_type(4)));
 
 __device__ __forceinline__ v4d mfma16(double a, double b, v4d c) {
   return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
 }
-__device__ __forceinline__ v4f mfma16(float a, float b, v4f c) {
-  return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
-}
-// Row of output register q of a lane in group g = lane / 16: the FP64
-// instruction interleaves the groups, the FP32 one keeps a group's four rows
-// together.
+// Row of output register q of a lane in group g = lane / 16.
+__device__ __forceinline__ int mfma_row(int q, int g) { return 4 * q + g; }
+
+// The refined mode: the leaves multiply and sum in FP64, with the FP64
+// matrices; FP32 sums there left the results twice as far from exact as the
+// substitutions of the one-workgroup path.  Above the leaves FP64 gains nothing
+// more: the matrices are FP32, and so is an output tile's sum, in four parts
+// (one per four columns of the tiles) that need not wait for each other.
 template <class T>
-__device__ __forceinline__ int mfma_row(int q, int g) {
-  return sizeof(T) == 8 ? 4 * q + g : 4 * g + q;
-}
+struct UpperTile;
+template <>
+struct UpperTile<double> {
+  v4d a;
+  __device__ __forceinline__ void clear() { a = v4d{0.0, 0.0, 0.0, 0.0}; }
+  __device__ __forceinline__ void take(int, double m, double x) { a = mfma16(m, x, a); }
+  __device__ __forceinline__ v4d sum() const { return a; }
+  static __device__ __forceinline__ int row(int q, int g) { return mfma_row(q, g); }
+};
+template <>
+struct UpperTile<float> {
+  v4f a[4];
+  __device__ __forceinline__ void clear() {
+#pragma unroll
+    for (int s = 0; s < 4; ++s) a[s] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
+  }
+  __device__ __forceinline__ void take(int s, float m, float x) {
+    a[s] = __builtin_amdgcn_mfma_f32_16x16x4f32(m, x, a[s], 0, 0, 0);
+  }
+  __device__ __forceinline__ v4f sum() const { return (a[0] + a[1]) + (a[2] + a[3]); }
+  static __device__ __forceinline__ int row(int q, int g) { return 4 * g + q; }  // (a group's rows together)
+};
 
 // Lane J of each group of 16 lanes to all its lanes.
 template <int J>
@@ -448,9 +459,9 @@ __device__ __forceinline__ void ring_start(const T *mat, int32_t p0, int32_t n, 
 template <class T, int RING, class G, class F>
 __device__ __forceinline__ void products(T (&H)[RING][4], int32_t ents, int32_t p0, int32_t n, const T *mat, const T *X,
                                          T *parts, int wave, int lane, G done, F out) {
-  typedef typename Vec4<T>::type V;
   const T *Xl = X + (lane >> 4) * kD + (lane & 15);
-  V acc = {T(0), T(0), T(0), T(0)};
+  UpperTile<T> acc;
+  acc.clear();
   int32_t more = 0, last = 0;
   for (int32_t p = 0; p < n; p += RING) {
 #pragma unroll
@@ -459,20 +470,21 @@ __device__ __forceinline__ void products(T (&H)[RING][4], int32_t ents, int32_t 
       const int32_t e = __builtin_amdgcn_readlane(ents, p + h);
       const T *x = Xl + (e & kProdMask) * (kT * kD);
 #pragma unroll
-      for (int s = 0; s < 4; ++s) acc = mfma16(H[h][s], x[4 * s * kD], acc);
+      for (int s = 0; s < 4; ++s) acc.take(s, H[h][s], x[4 * s * kD]);
       if (e & kProdLast) {
         more = e >> kProdMore;
         if (more) {  // (the wave's last product)
           last = e;
           break;
         }
+        const auto v = acc.sum();
         if (e & kProdPart) {
 #pragma unroll
-          for (int q = 0; q < 4; ++q) parts[(wave * 4 + q) * 64 + lane] = acc[q];
+          for (int q = 0; q < 4; ++q) parts[(wave * 4 + q) * 64 + lane] = v[q];
         } else {
-          out((e >> kProdBits) & kProdMask, acc);
+          out((e >> kProdBits) & kProdMask, v);
         }
-        acc = V{T(0), T(0), T(0), T(0)};
+        acc.clear();
       }
       if (p + h + RING < n) tile_load<T>(mat, p0 + p + h + RING, lane, H[h]);
     }
@@ -480,10 +492,11 @@ __device__ __forceinline__ void products(T (&H)[RING][4], int32_t ents, int32_t 
   done();
   lds_barrier();
   if (more) {
+    auto v = acc.sum();
     for (int w = wave + 1; w <= wave + more; ++w)
 #pragma unroll
-      for (int q = 0; q < 4; ++q) acc[q] += parts[(w * 4 + q) * 64 + lane];
-    out((last >> kProdBits) & kProdMask, acc);
+      for (int q = 0; q < 4; ++q) v[q] += parts[(w * 4 + q) * 64 + lane];
+    out((last >> kProdBits) & kProdMask, v);
   }
 }
 
@@ -537,7 +550,6 @@ __global__ __launch_bounds__(kLeafWaves * 64, 4) void tree_leaf(const TreeArgs a
   extern __shared__ __align__(16) char lds_raw[];
   typedef SweepIo<T, FWD> Io;
   typedef typename Io::S S;
-  typedef typename Vec4<T>::type V;
   constexpr bool kRef = Io::kRef;
   constexpr int kSlots = kLeafWaves * 4, kStage = FWD ? kStageFwd : kLeafStage;
   const int tid = threadIdx.x, slot = tid >> 4, l16 = tid & 15, lane = tid & 63;
@@ -561,8 +573,8 @@ __global__ __launch_bounds__(kLeafWaves * 64, 4) void tree_leaf(const TreeArgs a
     const int32_t ns = nd.ns, mt = nd.mt, rows = (FWD ? mt : mt + nd.bt) * kT;
     const ChunkOff off = chunk_off(td);
     const int32_t ents = lane < np ? (FWD ? td.fwd : td.bwd)[p0 + lane] : 0;
-    T H[kLeafProds][4];
-    ring_start(sweep_mat<T>(td, which == 0 ? (FWD ? 0 : 1) : (FWD ? 2 : 3)), p0, np, lane, H);
+    double H[kLeafProds][4];
+    ring_start(sweep_mat<double>(td, which == 0 ? (FWD ? 0 : 1) : (FWD ? 2 : 3)), p0, np, lane, H);
     // where the staged rows are
     uint32_t at[kStage];
     SparseRows<SP ? kStageFwd : 1> gp;
@@ -597,7 +609,7 @@ __global__ __launch_bounds__(kLeafWaves * 64, 4) void tree_leaf(const TreeArgs a
       const bool used = o ? np > n0 : n0 > 0;
 #pragma unroll
       for (int q = 0; q < 4; ++q)
-        to[o][q] = used ? out_off<T, FWD>(nd, r * kT + mfma_row<T>(q, lane >> 4), Io::out(off, which),
+        to[o][q] = used ? out_off<T, FWD>(nd, r * kT + mfma_row(q, lane >> 4), Io::out(off, which),
                                           upd_off<T>(td, off), l16)
                         : kNone;
     }
@@ -614,18 +626,18 @@ __global__ __launch_bounds__(kLeafWaves * 64, 4) void tree_leaf(const TreeArgs a
     }
     for (; chunk < end; ++chunk, active >>= 1) {
       const ChunkBuf m = chunk_buf(a, chunk);
-      T *X = reinterpret_cast<T *>(lds_raw) + buf * a.lds_rows * kD;
+      double *X = reinterpret_cast<double *>(lds_raw) + buf * a.lds_rows * kD;
       buf ^= 1;
-      T x[kStage];
+      double x[kStage];
       if constexpr (SP) {
         const int32_t dir = (chunk - it.chunk0) * kD + l16;
         double b[kStageFwd];
         rows_sum<2>(gp, td.gp_col, td.gp_val, l16, [&](int32_t q) { return w_of(it, m, q, dir, l16); }, b);
 #pragma unroll
-        for (int j = 0; j < kStageFwd; ++j) x[j] = (T)-b[j];
+        for (int j = 0; j < kStageFwd; ++j) x[j] = -b[j];
       } else {
 #pragma unroll
-        for (int j = 0; j < kStage; ++j) x[j] = (T)v[j];
+        for (int j = 0; j < kStage; ++j) x[j] = (double)v[j];
       }
 #pragma unroll
       for (int j = 0; j < kStage; ++j)
@@ -637,12 +649,12 @@ __global__ __launch_bounds__(kLeafWaves * 64, 4) void tree_leaf(const TreeArgs a
         for (int j = 0; j < kStage; ++j) v[j] = get<S>(next, at[j]);
       }
       const bool skip = kRef && !(active & 1);
-      const T *Xl = X + (lane >> 4) * kD + l16;
-      V acc[2] = {{T(0), T(0), T(0), T(0)}, {T(0), T(0), T(0), T(0)}};
+      const double *Xl = X + (lane >> 4) * kD + l16;
+      v4d acc[2] = {{0.0, 0.0, 0.0, 0.0}, {0.0, 0.0, 0.0, 0.0}};
 #pragma unroll
       for (int h = 0; h < kLeafProds; ++h) {
         if (h >= np || skip) break;
-        T xs[4];
+        double xs[4];
 #pragma unroll
         for (int s = 0; s < 4; ++s) xs[s] = Xl[in[h] + 4 * s * kD];
         if (h < n0) {
@@ -656,7 +668,7 @@ __global__ __launch_bounds__(kLeafWaves * 64, 4) void tree_leaf(const TreeArgs a
 #pragma unroll
       for (int o = 0; o < 2; ++o)
 #pragma unroll
-        for (int q = 0; q < 4; ++q) put(m, skip ? kNone : to[o][q], acc[o][q]);
+        for (int q = 0; q < 4; ++q) put(m, skip ? kNone : to[o][q], (T)acc[o][q]);
     }
   }
 }
@@ -724,10 +736,10 @@ __global__ __launch_bounds__(kUpperWaves * 64, 4) void tree_upper(const TreeArgs
     if (slot + j * kSlots < rows) X[(slot + j * kSlots) * kD + l16] = x[j];
   lds_barrier();
   const uint32_t own = Io::out(off, which), upd = upd_off<T>(td, off);
-  products(H, ents, p0, np, mat, X, X + a.lds_rows * kD, wave, lane, [] {}, [&](int32_t r, const typename Vec4<T>::type &acc) {
+  products(H, ents, p0, np, mat, X, X + a.lds_rows * kD, wave, lane, [] {}, [&](int32_t r, const auto &acc) {
 #pragma unroll
     for (int q = 0; q < 4; ++q)
-      put(m, out_off<T, FWD>(nd, r * kT + mfma_row<T>(q, lane >> 4), own, upd, l16), acc[q]);
+      put(m, out_off<T, FWD>(nd, r * kT + UpperTile<T>::row(q, lane >> 4), own, upd, l16), (T)acc[q]);
   });
 }
 
@@ -749,7 +761,8 @@ __global__ __launch_bounds__(kUpperWaves * 64, 4) void tree_top(const TreeArgs a
   const ChunkOff off = chunk_off(td);
   const ChunkBuf m = chunk_buf(a, chunk);
   const int32_t ns = nd.ns, mt = nd.mt, row0 = nd.row0, dir = (chunk - it.chunk0) * kD + l16;
-  T *X = reinterpret_cast<T *>(lds_raw), *X2 = X + mt * kT * kD, *parts = X2 + mt * kT * kD;
+  T *X = reinterpret_cast<T *>(lds_raw), *X2 = X + mt * kT * kD;
+  T *parts = X2 + mt * kT * kD;
   const int32_t np = nd.fwd_at[wave + 1] - nd.fwd_at[wave], p0 = nd.fwd0 + nd.fwd_at[wave];
   const int32_t nq = nd.bwd_at[wave + 1] - nd.bwd_at[wave], q0 = nd.bwd0 + nd.bwd_at[wave];
   const int32_t ents = lane < np ? td.fwd[p0 + lane] : 0, ents2 = lane < nq ? td.bwd[q0 + lane] : 0;
@@ -787,16 +800,16 @@ __global__ __launch_bounds__(kUpperWaves * 64, 4) void tree_top(const TreeArgs a
   if constexpr (SP) ring_start(mat, p0, np, lane, H);  // (the registers are taken before)
   lds_barrier();
   auto second = [&] { ring_start(mat2, q0, nq, lane, H); };
-  products(H, ents, p0, np, mat, X, parts, wave, lane, second, [&](int32_t r, const typename Vec4<T>::type &acc) {
+  products(H, ents, p0, np, mat, X, parts, wave, lane, second, [&](int32_t r, const auto &acc) {
 #pragma unroll
-    for (int q = 0; q < 4; ++q) X2[(r * kT + mfma_row<T>(q, lane >> 4)) * kD + l16] = acc[q];
+    for (int q = 0; q < 4; ++q) X2[(r * kT + UpperTile<T>::row(q, lane >> 4)) * kD + l16] = (T)acc[q];
   });
   lds_barrier();
   if (a.stamps && chunk == 0 && tid == 0) a.stamps[which == 0 ? 2 : 5] = wall_clock64();
-  products(H, ents2, q0, nq, mat2, X2, parts, wave, lane, [] {}, [&](int32_t r, const typename Vec4<T>::type &acc) {
+  products(H, ents2, q0, nq, mat2, X2, parts, wave, lane, [] {}, [&](int32_t r, const auto &acc) {
 #pragma unroll
     for (int q = 0; q < 4; ++q)
-      put(m, out_off<T, false>(nd, r * kT + mfma_row<T>(q, lane >> 4), own, 0, l16), acc[q]);
+      put(m, out_off<T, false>(nd, r * kT + UpperTile<T>::row(q, lane >> 4), own, 0, l16), (T)acc[q]);
   });
 }
 
@@ -1682,7 +1695,7 @@ rh_status tree_launch(const std::vector<TreeRequest> &req, const std::vector<Tre
   const size_t el = ref ? sizeof(float) : sizeof(double), row = kT * kD * el;  // a row tile of one chunk
   const size_t parts = kUpperWaves * kTileVals * el;  // sums that span waves
   const size_t top_lds = 2 * (size_t)top * row + parts;
-  if (std::max({2 * leaf * row, upper * row + parts, top_lds}) > kTreeLds) {
+  if (std::max({2 * leaf * kT * kD * sizeof(double), upper * row + parts, top_lds}) > kTreeLds) {
     err = "internal: node larger than the LDS";
     return RH_EDEVICE;
   }
@@ -1709,7 +1722,8 @@ rh_status tree_launch(const std::vector<TreeRequest> &req, const std::vector<Tre
       const int per = std::min<int>(kChunkRun, (int)((nc + most - 1) / most));
       const dim3 grid(gx, (nc + per - 1) / per), block((q == 0 ? kLeafWaves : kUpperWaves) * 64);
       a.lds_rows = (q == 0 ? leaf : upper) * kT;
-      const size_t lds = (per > 1 ? 2 : 1) * (size_t)a.lds_rows * kD * el + (q == 0 ? 0 : parts);
+      const size_t lds = q == 0 ? (per > 1 ? 2 : 1) * (size_t)a.lds_rows * kD * sizeof(double)
+                                : (size_t)a.lds_rows * kD * el + parts;
       const bool sp = fwd && !ref && which == 0;
       if (q == 0) {
 #define TREE_LEAF(T, F, S) hipLaunchKernelGGL((tree_leaf<T, F, S>), grid, block, lds, s, a, which, iter, per)

@@ -64,7 +64,7 @@ def solved():
     from oracle import solve
     from paper_2201_00241_amd import rh
 
-    g = gridgen.config_grid("c2", 0)  # 18,999 states: above the path's smallest network (13,000)
+    g = gridgen.config_grid("c2", 0)  # 18,999 states: above the path's smallest network (16,000)
     ctx = rh.Context(0)
     net = rh.Network(ctx, g)
     net.solve()

@@ -1524,6 +1524,10 @@ struct Runner {
   TreeItem *titems_dev = nullptr, *titems_host = nullptr;  // the tree path's work list
   int32_t titems_cap = 0;
   hipEvent_t titems_done = nullptr;
+  // a stream beside this one, for batches with networks of both paths, and the
+  // events that order it
+  hipStream_t side = nullptr;
+  hipEvent_t fork = nullptr, join = nullptr;
   int32_t launches = 0, last_c = 0;
   long long *step_stamps = nullptr;  // debug (RH_STEP_STAMPS)
   bool step_stamps_pending = false;
@@ -1555,6 +1559,9 @@ void runner_free(Runner &r) {
   if (r.titems_dev) (void)hipFree(r.titems_dev);
   if (r.titems_host) (void)hipHostFree(r.titems_host);
   if (r.titems_done) (void)hipEventDestroy(r.titems_done);
+  if (r.fork) (void)hipEventDestroy(r.fork);
+  if (r.join) (void)hipEventDestroy(r.join);
+  if (r.side) (void)hipStreamDestroy(r.side);
   if (r.step_stamps) (void)hipFree(r.step_stamps);
   r = Runner();
 }
@@ -2974,15 +2981,38 @@ rh_status device_hvp_batch(Context &ctx, int32_t n, Network *const *nets, const 
     max_nx = std::max(max_nx, net.n_x);
   }
   const int32_t refine = prec == RH_FP32_REFINED ? ctx.refine : -1;
-  Runner &r = ctx.dev->on(stream);
-  if (!req.empty()) {
-    // (phase stamps are those of one kind of launch: the other's, if there is one)
-    const rh_status s = run_tree(r, items.empty() ? ctx.timing : std::min(ctx.timing, 1), refine, ctx.refine_tol, req,
-                                 (hipStream_t)stream, err);
-    if (s != RH_OK) return s;
+  if (req.empty() && items.empty()) return RH_OK;
+  hipStream_t s = (hipStream_t)stream;
+  if (req.empty())
+    return run_items(ctx.dev->info, ctx.dev->on(stream), ctx.timing, refine, ctx.refine_tol, items, max_nx, s, err);
+  if (items.empty()) return run_tree(ctx.dev->on(stream), ctx.timing, refine, ctx.refine_tol, req, s, err);
+  // Networks of both paths: the one-workgroup path's launch, which takes as
+  // long as its longest chain and leaves much of the chip idle, on a stream
+  // beside the tree path's sequence (networks of 1k, 10k, 9, 1k and 10k buses:
+  // 341 us one after the other, 291 side by side, 364 all on the one-workgroup
+  // path; a refined batch that takes 1146 us there 1164 and 928).
+  {
+    Runner &r = ctx.dev->on(stream);
+    if (!r.side) HIP_TRY(hipStreamCreateWithFlags(&r.side, hipStreamNonBlocking));
+    if (!r.fork) HIP_TRY(hipEventCreateWithFlags(&r.fork, hipEventDisableTiming));
+    if (!r.join) HIP_TRY(hipEventCreateWithFlags(&r.join, hipEventDisableTiming));
   }
-  if (items.empty()) return RH_OK;
-  return run_items(ctx.dev->info, r, ctx.timing, refine, ctx.refine_tol, items, max_nx, (hipStream_t)stream, err);
+  hipStream_t side = ctx.dev->on(stream).side;
+  (void)ctx.dev->on(side);  // (adding a runner moves the others)
+  Runner &r = ctx.dev->on(stream);
+  HIP_TRY(hipEventRecord(r.fork, s));
+  HIP_TRY(hipStreamWaitEvent(side, r.fork, 0));
+  // (phase stamps are those of one kind of launch: the other's)
+  const rh_status si = run_items(ctx.dev->info, ctx.dev->on(side), ctx.timing, refine, ctx.refine_tol, items, max_nx,
+                                 side, err);
+  std::string err_t;
+  const rh_status st = si == RH_OK ? run_tree(r, std::min(ctx.timing, 1), refine, ctx.refine_tol, req, s, err_t) : RH_OK;
+  // whatever came of it, the caller's stream waits for what is under way
+  HIP_TRY(hipEventRecord(r.join, side));
+  HIP_TRY(hipStreamWaitEvent(s, r.join, 0));
+  if (si != RH_OK) return si;
+  if (st != RH_OK) err = err_t;
+  return st;
 }
 
 bool device_tree(const Network &net) { return net.dev && tree_path(net); }
@@ -3062,9 +3092,11 @@ rh_status batch_build(DeviceBatch &b, const DeviceInfo &info, int32_t refine, do
   if (ps != RH_OK) return ps;
   b.C = pl.n_chunks > 0 ? pl.C : kTreeDirs;
   b.groups = pl.groups + sh.chunks;
-  // the two kinds of launches follow each other and share the scratch
-  HIP_TRY(hipMalloc(&b.scratch, std::max<size_t>({256, (size_t)pl.groups * pl.stride * sizeof(double),
-                                                  sh.scratch_bytes()})));
+  // the two kinds of launches run side by side, with scratch of their own
+  const size_t gs_bytes = ((size_t)pl.groups * pl.stride * sizeof(double) + 255) / 256 * 256;
+  const size_t ts_bytes = sh.chunks > 0 ? sh.scratch_bytes() : 0;
+  HIP_TRY(hipMalloc(&b.scratch, std::max<size_t>(256, gs_bytes + ts_bytes)));
+  double *tree_scratch = b.scratch + gs_bytes / sizeof(double);
   LaunchArgs la{};
   la.refine = refine;
   la.refine_tol = refine_tol;
@@ -3088,12 +3120,42 @@ rh_status batch_build(DeviceBatch &b, const DeviceInfo &info, int32_t refine, do
     const rh_status as = launch_plan(pl, pl.groups, nullptr, la, err, kAttrsOnly);
     if (as != RH_OK) return as;
   }
+  // with both kinds, a second stream and the events that make it a branch
+  struct Side {
+    hipStream_t s = nullptr;
+    hipEvent_t fork = nullptr, join = nullptr;
+    ~Side() {
+      if (fork) (void)hipEventDestroy(fork);
+      if (join) (void)hipEventDestroy(join);
+      if (s) (void)hipStreamDestroy(s);
+    }
+  } side;
+  const bool both = sh.chunks > 0 && pl.n_chunks > 0;
+  if (both) {
+    HIP_TRY(hipStreamCreateWithFlags(&side.s, hipStreamNonBlocking));
+    HIP_TRY(hipEventCreateWithFlags(&side.fork, hipEventDisableTiming));
+    HIP_TRY(hipEventCreateWithFlags(&side.join, hipEventDisableTiming));
+  }
   HIP_TRY(hipStreamCreateWithFlags(&b.cap, hipStreamNonBlocking));
   HIP_TRY(hipStreamBeginCapture(b.cap, hipStreamCaptureModeThreadLocal));
   rh_status ls = RH_OK;
-  if (sh.chunks > 0)
-    ls = tree_launch(req, titems, b.titems_dev, sh, b.scratch, refine, refine_tol, nullptr, b.cap, e2);
-  if (ls == RH_OK && pl.n_chunks > 0) ls = launch_plan(pl, pl.groups, b.cap, la, e2, kLaunchOnly);
+  auto check = [&](hipError_t e) {
+    if (e == hipSuccess || ls != RH_OK) return;
+    ls = RH_EDEVICE;
+    e2 = std::string("recording a batch: ") + hipGetErrorString(e);
+  };
+  hipStream_t gs = both ? side.s : b.cap;
+  if (both) {
+    check(hipEventRecord(side.fork, b.cap));
+    check(hipStreamWaitEvent(side.s, side.fork, 0));
+  }
+  if (ls == RH_OK && pl.n_chunks > 0) ls = launch_plan(pl, pl.groups, gs, la, e2, kLaunchOnly);
+  if (ls == RH_OK && sh.chunks > 0)
+    ls = tree_launch(req, titems, b.titems_dev, sh, tree_scratch, refine, refine_tol, nullptr, b.cap, e2);
+  if (both) {
+    check(hipEventRecord(side.join, side.s));
+    check(hipStreamWaitEvent(b.cap, side.join, 0));
+  }
   hipGraph_t g = nullptr;
   const hipError_t ce = hipStreamEndCapture(b.cap, &g);
   b.graph = g;

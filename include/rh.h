@@ -281,8 +281,9 @@ rh_status rh_hvp_batch_device(rh_context *ctx, int32_t n, rh_network *const *net
  * blocks of Algorithm 2 are independent, across instances as across
  * directions; Sec. 6: many operating points of one grid).  rh_batch_create
  * takes the arguments of rh_hvp_batch_device, uploads the work list,
- * allocates the launch scratch and records the single batched kernel launch
- * as a HIP graph; rh_batch_launch replays it on hip_stream (one graph launch,
+ * allocates the launch scratch and records the batched kernel launches (one
+ * for the networks below 16,000 states, and beside it the sequence that the
+ * larger ones take) as a HIP graph; rh_batch_launch replays it on hip_stream (one graph launch,
  * no host-side work list and no allocation).  The device buffers dW/dHW are
  * bound at creation: every replay reads their current contents and overwrites
  * the products.  A network re-solved or given new loads or parameters since

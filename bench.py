@@ -289,7 +289,8 @@ def run_refined(net, g, H, k, steps, warmup, stream):
     fig = net.refinement_report(n_p)
     pz = 1.0 + float(np.mean(fig["steps_z"]))
     pp = 1.0 + float(np.mean(fig["steps_psi"]))
-    kbs = [min(k, n_p - j0) for j0 in range(0, n_p, k)]
+    per = -(-n_p // max(1, rep["last_launches"] // steps))  # directions of a launch (blocks may share one)
+    kbs = [min(per, n_p - j0) for j0 in range(0, n_p, per)]
     bytes_launch = sum(refined_launch_bytes(rep, g, kb, pz, pp, rep["nnz_gx"]) for kb in kbs) / len(kbs)
     avg_launch_ms = rep["last_kernel_ms"] / rep["last_launches"]
     achieved = bytes_launch / (avg_launch_ms / 1e3) / 1e9
@@ -304,7 +305,7 @@ def run_refined(net, g, H, k, steps, warmup, stream):
                                   "psi": np.bincount(fig["steps_psi"]).tolist()},
         "max_backward_error": {"z": float(fig["berr_z"].max()), "psi": float(fig["berr_psi"].max())},
         "roofline": {"bound": "hbm", "achieved": achieved, "peak": PEAK_HBM_GBS, "unit": "GB/s",
-                     "frac": achieved / PEAK_HBM_GBS, "kernel": "refined_kernel",
+                     "frac": achieved / PEAK_HBM_GBS, "kernel": "tree path" if rep["dirs_per_group"] == 16 else "refined_kernel",
                      "avg_launch_ms": avg_launch_ms, "algorithmic_bytes_per_launch": bytes_launch},
         "what": "same workload, FP32 sweeps with FP64 residual refinement (each direction stops "
                 "at a backward error of 1e-13 or after 4 corrections)",
@@ -656,7 +657,9 @@ def main():
     rep = trep
     launches = trep["last_launches"]
     avg_launch_ms = trep["last_kernel_ms"] / launches
-    bytes_launch = mean_bytes_per_launch(rep, g, n_p, k)
+    # directions of a launch: the k blocks of a Hessian may share one
+    dirs = -(-n_p // max(1, launches // args.steps))
+    bytes_launch = mean_bytes_per_launch(rep, g, n_p, dirs)
     achieved = bytes_launch / (avg_launch_ms / 1e3) / 1e9
     traffic = measured_traffic()
     phase_names = ["spmul", "L", "U", "projection", "Ut", "Lt", "spmuladd"]
@@ -695,7 +698,7 @@ def main():
             "bound": "hbm", "achieved": achieved, "peak": PEAK_HBM_GBS, "unit": "GB/s",
             "frac": achieved / PEAK_HBM_GBS, "traffic": traffic,
             "traffic_unit": "HBM bytes per launch (rocprofv3 FETCH_SIZE + WRITE_SIZE, copy-scaled)",
-            "kernel": "block_kernel", "avg_launch_ms": avg_launch_ms,
+            "kernel": "tree path" if rep["dirs_per_group"] == 16 else "block_kernel", "avg_launch_ms": avg_launch_ms,
             "algorithmic_bytes_per_launch": bytes_launch,
         },
         "setup_s": setup_s,
@@ -703,12 +706,12 @@ def main():
         "tuned_k_full_hessian": {"k": tile["k"], "ms_per_step": tuned_ms, "value": n_p / (tuned_ms / 1e3),
                                  "what": "the same full Hessian with the tuner's launch size"},
     }
-    # per-phase roofline fractions: each phase's algorithmic bytes (k directions)
+    # per-phase roofline fractions: each phase's algorithmic bytes (a launch's directions)
     # over its mean time per workgroup
     n_x = rep["n_x"]
-    ph_bytes = {"L": 2 * n_x * k * 8 + rep["nnz_l"] * 12, "U": 2 * n_x * k * 8 + rep["nnz_u"] * 12,
-                "Ut": 2 * n_x * k * 8 + rep["nnz_u"] * 12, "Lt": 2 * n_x * k * 8 + rep["nnz_l"] * 12,
-                "projection": 2 * (n_x + n_p) * k * 8}
+    ph_bytes = {"L": 2 * n_x * dirs * 8 + rep["nnz_l"] * 12, "U": 2 * n_x * dirs * 8 + rep["nnz_u"] * 12,
+                "Ut": 2 * n_x * dirs * 8 + rep["nnz_u"] * 12, "Lt": 2 * n_x * dirs * 8 + rep["nnz_l"] * 12,
+                "projection": 2 * (n_x + n_p) * dirs * 8}
     out["phase_roofline_frac"] = {
         p: round(b / (out["phase_us"][p] * 1e-6) / 1e9 / PEAK_HBM_GBS, 4)
         for p, b in ph_bytes.items() if out["phase_us"].get(p, 0) > 0}

@@ -19,7 +19,8 @@ struct FrontIo {
   double *x;             // the state
 };
 
-// Builds the fronts; null in *out where the plan does not take the network.
+// Builds the fronts; null in *out where the plan does not take the network, or
+// there is no memory for them.
 // maps: the factors' flat layout and the entries of G_x in it.
 rh_status fronts_build(const LuPlan &lu, const LuMaps &maps, DevFronts **out, std::string &err);
 void fronts_free(DevFronts *f);

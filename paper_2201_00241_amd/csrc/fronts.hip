@@ -676,10 +676,13 @@ rh_status fronts_build(const LuPlan &lu, const LuMaps &mp, DevFronts **out, std:
   for (const TreeNode &nd : p.nodes) total += front_values(nd.mt + nd.bt);
   if (total * (int64_t)sizeof(double) > kMostFrontBytes) return RH_OK;
   DevFronts *f = new DevFronts();
-  const rh_status s = fill(*f, lu, mp, p, err);
-  if (s != RH_OK) {
+  if (fill(*f, lu, mp, p, err) != RH_OK) {
+    // no memory for them: row by row, as for a network that the plan does not
+    // take (an error of the device itself comes up there again)
     fronts_free(f);
-    return s;
+    (void)hipGetLastError();
+    err.clear();
+    return RH_OK;
   }
   *out = f;
   return RH_OK;

@@ -438,7 +438,7 @@ __global__ __launch_bounds__(kThreads, 2) void chol_panel(Aug M, int32_t j, int3
                                                          int32_t tiles, int32_t *info, double *diag) {
   __shared__ PanelLds L;
   if (*info) return;
-  double *mine = diag + (j / kNB & 1) * kNB * kNB, *before = diag + (j / kNB & 1 ^ 1) * kNB * kNB;
+  double *mine = diag + (j / kNB & 1) * kNB * kNB, *before = diag + ((j / kNB & 1) ^ 1) * kNB * kNB;
   const int32_t strips_before = (M.rows - j + kNB - 1) / kNB;  // of the panel before
   if ((int32_t)blockIdx.x < strips) {
     panel_strip(M, j, blockIdx.x, strips, info, mine, L);

@@ -661,8 +661,7 @@ rh_status fill(DevFronts &f, const LuPlan &lu, const LuMaps &mp, const TreePlan 
   f.xt = static_cast<double *>(m);
   for (const void *kernel : {reinterpret_cast<const void *>(&front_factor<kLeafWaves, true>),
                              reinterpret_cast<const void *>(&front_factor<kUpperWaves, false>)})
-    HIP_TRY(hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                (int)front_lds(*std::max_element(f.most.begin(), f.most.end()))));
+    if ((s = lds_bound(kernel, front_lds(*std::max_element(f.most.begin(), f.most.end())), err)) != RH_OK) return s;
   return RH_OK;
 }
 

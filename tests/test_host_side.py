@@ -1,0 +1,62 @@
+"""The library's host side without a GPU: a stand-in for the HIP runtime
+(native/fake_hip.cpp: device memory is the host's, kernels do not run) takes
+the real one's place in a process of its own, and is told what to refuse.
+"""
+import subprocess
+import sys
+from pathlib import Path
+
+import pytest
+
+ROOT = Path(__file__).resolve().parents[1]
+
+PRELUDE = """
+import ctypes, os, sys, types
+sys.modules["torch"] = types.ModuleType("torch")  # (the binding loads it for its HIP runtime)
+hip = ctypes.CDLL(sys.argv[1], mode=ctypes.RTLD_GLOBAL)
+for f in ("live", "peak", "allocs", "launches", "streams"):
+    getattr(hip, "fake_" + f).restype = ctypes.c_int64
+hip.fake_limit.argtypes = [ctypes.c_int64, ctypes.c_int64]
+import numpy as np
+import gridgen
+from paper_2201_00241_amd import rh
+
+def geo(n, seed=1):
+    return gridgen.geometric(n, int(1.35 * n), max(3, n // 10), seed=seed, alpha=0.1, kappa=0.0085)
+
+def solved_on_device(net):
+    # kernels do not run, so the factors come back as zeros: every status but
+    # the device's is as good as any
+    try:
+        net.solve_device()
+    except rh.RhError as e:
+        if e.status == rh.RH_EDEVICE:
+            raise
+"""
+
+
+@pytest.fixture(scope="module")
+def fake(tmp_path_factory):
+    out = tmp_path_factory.mktemp("native") / "libfake_hip.so"
+    subprocess.run(["g++", "-O1", "-std=c++17", "-shared", "-fPIC", "-I/opt/rocm/include",
+                    str(ROOT / "tests/native/fake_hip.cpp"), "-o", str(out)], check=True)
+
+    def run(code):
+        res = subprocess.run([sys.executable, "-c", PRELUDE + code, str(out)], cwd=ROOT, capture_output=True, text=True,
+                             timeout=300)
+        assert res.returncode == 0, res.stdout + res.stderr
+        return res.stdout
+
+    return run
+
+
+def test_a_small_networks_fronts_leave_a_large_ones_bound(fake):
+    """The dynamic LDS that a kernel may use is the kernel's, not a network's:
+    a network built later, with smaller fronts, must not lower it."""
+    fake("""
+ctx = rh.Context(0)
+large, small = rh.Network(ctx, geo(3000)), rh.Network(ctx, gridgen.ring9())
+solved_on_device(large)
+solved_on_device(small)
+solved_on_device(large)
+""")

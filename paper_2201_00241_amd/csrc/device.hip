@@ -3278,6 +3278,15 @@ rh_status device_alloc(void **p, size_t bytes, std::string &err) {
   return RH_OK;
 }
 
+rh_status device_try_alloc(void **p, size_t bytes, std::string &err) {
+  *p = nullptr;
+  const hipError_t e = hipMalloc(p, bytes);
+  if (e == hipSuccess) return RH_OK;
+  (void)hipGetLastError();
+  err = std::string("hipMalloc of ") + std::to_string(bytes) + " bytes: " + hipGetErrorString(e);
+  return e == hipErrorOutOfMemory ? RH_ENOMEM : RH_EDEVICE;
+}
+
 void device_release(void *p) {
   if (p) (void)hipFree(p);
 }

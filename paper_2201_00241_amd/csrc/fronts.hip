@@ -25,6 +25,7 @@
 #include <algorithm>
 #include <cmath>
 #include <limits>
+#include <memory>
 
 #include "fronts.h"
 #include "tree.h"
@@ -485,7 +486,8 @@ namespace {
 template <class T>
 rh_status f_up(DevFronts &f, const std::vector<T> &v, const T **out, std::string &err) {
   void *p = nullptr;
-  HIP_TRY(hipMalloc(&p, std::max<size_t>(sizeof(T), v.size() * sizeof(T))));
+  const rh_status s = device_try_alloc(&p, std::max<size_t>(sizeof(T), v.size() * sizeof(T)), err);
+  if (s != RH_OK) return s;
   f.allocs.push_back(p);
   if (!v.empty()) HIP_TRY(hipMemcpy(p, v.data(), v.size() * sizeof(T), hipMemcpyHostToDevice));
   *out = static_cast<const T *>(p);
@@ -653,10 +655,10 @@ rh_status fill(DevFronts &f, const LuPlan &lu, const LuMaps &mp, const TreePlan 
       (s = f_up(f, mp.a_src, &f.row_src, err)) != RH_OK)
     return s;
   void *m = nullptr;
-  HIP_TRY(hipMalloc(&m, std::max<size_t>(1, (size_t)f.values) * sizeof(double)));
+  if ((s = device_try_alloc(&m, std::max<size_t>(1, (size_t)f.values) * sizeof(double), err)) != RH_OK) return s;
   f.allocs.push_back(m);
   f.fronts = static_cast<double *>(m);
-  HIP_TRY(hipMalloc(&m, std::max<size_t>(1, n) * sizeof(double)));
+  if ((s = device_try_alloc(&m, std::max<size_t>(1, n) * sizeof(double), err)) != RH_OK) return s;
   f.allocs.push_back(m);
   f.xt = static_cast<double *>(m);
   for (const void *kernel : {reinterpret_cast<const void *>(&front_factor<kLeafWaves, true>),
@@ -674,17 +676,15 @@ rh_status fronts_build(const LuPlan &lu, const LuMaps &mp, DevFronts **out, std:
   int64_t total = 0;
   for (const TreeNode &nd : p.nodes) total += front_values(nd.mt + nd.bt);
   if (total * (int64_t)sizeof(double) > kMostFrontBytes) return RH_OK;
-  DevFronts *f = new DevFronts();
-  if (fill(*f, lu, mp, p, err) != RH_OK) {
-    // no memory for them: row by row, as for a network that the plan does not
-    // take (an error of the device itself comes up there again)
-    fronts_free(f);
-    (void)hipGetLastError();
+  std::unique_ptr<DevFronts, void (*)(DevFronts *)> f(new DevFronts(), fronts_free);
+  const rh_status s = fill(*f, lu, mp, p, err);
+  if (s == RH_ENOMEM) {
+    // no memory for them: row by row, as for a network that the plan does not take
     err.clear();
     return RH_OK;
   }
-  *out = f;
-  return RH_OK;
+  if (s == RH_OK) *out = f.release();
+  return s;
 }
 
 void fronts_free(DevFronts *f) {

@@ -433,6 +433,9 @@ int64_t device_network_bytes(const Network &net);
 int64_t device_scratch_per_direction(const Network &net, rh_precision prec);
 bool device_tree(const Network &net);  // whether the products take the tree path (tree.hip)
 rh_status device_alloc(void **p, size_t bytes, std::string &err);
+// Device memory for a caller that can do with less: RH_ENOMEM where there is
+// none, with no error left for the next call to find.
+rh_status device_try_alloc(void **p, size_t bytes, std::string &err);
 void device_release(void *p);
 rh_status device_sync(void *stream, std::string &err);
 

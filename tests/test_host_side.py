@@ -60,3 +60,28 @@ solved_on_device(large)
 solved_on_device(small)
 solved_on_device(large)
 """)
+
+
+@pytest.mark.parametrize("call,after", [("hipFuncSetAttribute", 0), ("hipMemcpy", 20), ("hipMalloc", 20)])
+def test_an_error_of_the_device_is_not_taken_for_a_lack_of_memory(fake, call, after):
+    """Only fronts that there is no memory for give way to the row-by-row
+    factorisation; any other error ends the call."""
+    fake(f"""
+net = rh.Network(rh.Context(0), geo(1000))
+before = hip.fake_live()
+hip.fake_refuse(b"{call}", {after})  # the fronts' arrays are among the first of the device Newton
+try:
+    net.solve_device()
+    assert False, "the refused call went unnoticed"
+except rh.RhError as e:
+    assert e.status == rh.RH_EDEVICE, e
+assert hip.fake_live() == before
+""")
+
+
+def test_no_memory_for_the_fronts(fake):
+    fake("""
+net = rh.Network(rh.Context(0), geo(1000))
+hip.fake_limit(-1, 8 << 20)  # the fronts of 1,000 buses take 14 MB, no other array more than 2
+solved_on_device(net)
+""")

@@ -316,7 +316,10 @@ rh_status rh_refinement_report(const rh_network *net, int32_t n, double *berr_z,
  * G_x, descriptors, and its own launch scratch), `scratch_per_direction` =
  * launch scratch one direction of this network may take in precision `prec`
  * (a launch holds it for each direction it runs at once, up to the
- * workgroups it keeps resident).  Either output may be NULL. */
+ * workgroups it keeps resident).  A launch may take a request's directions in
+ * whole chunks of RH_CHUNK_DIRS: for a bound, count them rounded up to a
+ * multiple of it.  Either output may be NULL. */
+#define RH_CHUNK_DIRS 16
 rh_status rh_network_device_bytes(const rh_network *net, rh_precision prec, int64_t *resident,
                                   int64_t *scratch_per_direction);
 

@@ -1841,26 +1841,21 @@ rh_status grow_stamps(Runner &r, int32_t groups, hipStream_t s, std::string &err
 // counts as one launch of the reduction).
 rh_status run_tree(Runner &r, int32_t timing, int32_t refine, double refine_tol, const std::vector<TreeRequest> &req,
                    hipStream_t s, std::string &err, const FixedScratch *fixed = nullptr) {
-  TreeShape sh = tree_shape(req, refine);
-  if (sh.chunks == 0) return RH_OK;
+  // (in more rounds when a fixed range is short)
+  const TreeWork work = fixed ? tree_work(req, refine, (size_t)fixed->bytes) : tree_work(req, refine);
+  if (work.chunks == 0) return RH_OK;
   if (fixed) {
-    // chunks in more rounds when the fixed range is short
-    TreeShape one = sh;
-    one.round = 1;
-    const int64_t fit = fixed->bytes / (int64_t)one.scratch_bytes();
-    if (fit < 1) {
-      err = "network too large for the fixed scratch: 16 directions need " + std::to_string(one.scratch_bytes()) +
-            " bytes, " + std::to_string(fixed->bytes) + " available";
+    if ((int64_t)work.bytes() > fixed->bytes) {
+      err = "network too large for the fixed scratch: a round needs " + std::to_string(work.bytes()) + " bytes, " +
+            std::to_string(fixed->bytes) + " available";
       return RH_EINVAL;
     }
-    sh.round = (int32_t)std::min<int64_t>(sh.round, fit);
     timing = 0;
   } else {
-    const rh_status gs = grow_scratch(r, sh.scratch_bytes(), s, err);
+    const rh_status gs = grow_scratch(r, work.bytes(), s, err);
     if (gs != RH_OK) return gs;
   }
-  std::vector<TreeItem> items;
-  tree_items(req, sh, items);
+  const std::vector<TreeItem> &items = work.items;
   if (req.size() > 1) {  // (a single request travels by value)
     if ((int32_t)items.size() > r.titems_cap) {
       HIP_TRY(hipStreamSynchronize(s));
@@ -1890,8 +1885,8 @@ rh_status run_tree(Runner &r, int32_t timing, int32_t refine, double refine_tol,
     if (es != RH_OK) return es;
     HIP_TRY(hipEventRecord(e0, s));
   }
-  const rh_status st = tree_launch(req, items, r.titems_dev, sh, fixed ? fixed->ptr : r.scratch, refine, refine_tol,
-                                   stamps, s, err);
+  const rh_status st = tree_launch(req, work, r.titems_dev, fixed ? fixed->ptr : r.scratch, refine, refine_tol, stamps, s,
+                                   err);
   if (st != RH_OK) return st;
   if (req.size() > 1) HIP_TRY(hipEventRecord(r.titems_done, s));
   if (timing >= 1) HIP_TRY(hipEventRecord(e1, s));
@@ -3080,9 +3075,8 @@ namespace {
 rh_status batch_build(DeviceBatch &b, const DeviceInfo &info, int32_t refine, double refine_tol,
                       std::vector<WorkItem> &items, int32_t max_nx, const std::vector<TreeRequest> &req,
                       std::string &err) {
-  const TreeShape sh = tree_shape(req, refine);
-  std::vector<TreeItem> titems;
-  tree_items(req, sh, titems);
+  const TreeWork work = tree_work(req, refine);
+  const std::vector<TreeItem> &titems = work.items;
   if (req.size() > 1) {
     HIP_TRY(hipMalloc(&b.titems_dev, titems.size() * sizeof(TreeItem)));
     HIP_TRY(hipMemcpy(b.titems_dev, titems.data(), titems.size() * sizeof(TreeItem), hipMemcpyHostToDevice));
@@ -3091,10 +3085,10 @@ rh_status batch_build(DeviceBatch &b, const DeviceInfo &info, int32_t refine, do
   rh_status ps = plan_launch(info, refine, items, max_nx, pl, err);
   if (ps != RH_OK) return ps;
   b.C = pl.n_chunks > 0 ? pl.C : kTreeDirs;
-  b.groups = pl.groups + sh.chunks;
+  b.groups = pl.groups + work.chunks;
   // the two kinds of launches run side by side, with scratch of their own
   const size_t gs_bytes = ((size_t)pl.groups * pl.stride * sizeof(double) + 255) / 256 * 256;
-  const size_t ts_bytes = sh.chunks > 0 ? sh.scratch_bytes() : 0;
+  const size_t ts_bytes = work.chunks > 0 ? work.bytes() : 0;
   HIP_TRY(hipMalloc(&b.scratch, std::max<size_t>(256, gs_bytes + ts_bytes)));
   double *tree_scratch = b.scratch + gs_bytes / sizeof(double);
   LaunchArgs la{};
@@ -3112,7 +3106,7 @@ rh_status batch_build(DeviceBatch &b, const DeviceInfo &info, int32_t refine, do
     HIP_TRY(hipMemcpy(b.items_dev, items.data(), items.size() * sizeof(WorkItem), hipMemcpyHostToDevice));
     la.items = b.items_dev;
   }
-  if (pl.n_chunks == 0 && sh.chunks == 0) return RH_OK;  // nothing to record: replays do nothing
+  if (pl.n_chunks == 0 && work.chunks == 0) return RH_OK;  // nothing to record: replays do nothing
   // kernel attributes first (not stream work), then the launches alone in the
   // graph (the tree path's kernels have theirs since the upload)
   std::string e2;
@@ -3130,7 +3124,7 @@ rh_status batch_build(DeviceBatch &b, const DeviceInfo &info, int32_t refine, do
       if (s) (void)hipStreamDestroy(s);
     }
   } side;
-  const bool both = sh.chunks > 0 && pl.n_chunks > 0;
+  const bool both = work.chunks > 0 && pl.n_chunks > 0;
   if (both) {
     HIP_TRY(hipStreamCreateWithFlags(&side.s, hipStreamNonBlocking));
     HIP_TRY(hipEventCreateWithFlags(&side.fork, hipEventDisableTiming));
@@ -3150,8 +3144,8 @@ rh_status batch_build(DeviceBatch &b, const DeviceInfo &info, int32_t refine, do
     check(hipStreamWaitEvent(side.s, side.fork, 0));
   }
   if (ls == RH_OK && pl.n_chunks > 0) ls = launch_plan(pl, pl.groups, gs, la, e2, kLaunchOnly);
-  if (ls == RH_OK && sh.chunks > 0)
-    ls = tree_launch(req, titems, b.titems_dev, sh, tree_scratch, refine, refine_tol, nullptr, b.cap, e2);
+  if (ls == RH_OK && work.chunks > 0)
+    ls = tree_launch(req, work, b.titems_dev, tree_scratch, refine, refine_tol, nullptr, b.cap, e2);
   if (both) {
     check(hipEventRecord(side.join, side.s));
     check(hipStreamWaitEvent(b.cap, side.join, 0));
@@ -3262,10 +3256,11 @@ int64_t device_network_bytes(const Network &net) {
 int64_t device_scratch_per_direction(const Network &net, rh_precision prec) {
   const int32_t n_x = net.n_x;
   if (net.dev && tree_path(net)) {
-    // a chunk's share (chunks are padded to kTreeDirs directions)
-    const TreeShape sh = tree_shape({TreeRequest{net.dtree, nullptr, nullptr, 0, 0, 1, -1, nullptr}},
+    // a chunk's share (callers count whole chunks)
+    static_assert(kTreeDirs == RH_CHUNK_DIRS, "the chunks of the figure");
+    const TreeWork work = tree_work({TreeRequest{net.dtree, nullptr, nullptr, 0, 0, 1, -1, nullptr}},
                                     prec == RH_FP32_REFINED ? net.ctx->refine : -1);
-    return (int64_t)(sh.scratch_bytes() + kTreeDirs - 1) / kTreeDirs;
+    return (int64_t)(work.bytes() + kTreeDirs - 1) / kTreeDirs;
   }
   // per-workgroup scratch of run_items, per direction it owns, with the
   // vector in global memory (the larger case): FP64 Y_x and X; refined V1,

@@ -143,6 +143,8 @@ __device__ __forceinline__ TreeItem item_of(const TreeArgs &a, int32_t chunk) {
   it.identity_from = s.identity_from;
   it.chunk0 = s.chunk0;
   it.chunks = s.chunks;
+  it.at = s.at;
+  it.stride = s.stride;
   it.rinfo = s.rinfo;
   return it;
 }
@@ -180,9 +182,12 @@ constexpr uint32_t kNone = 0x80000000u;
 struct ChunkBuf {
   __amdgpu_buffer_rsrc_t r;
 };
-__device__ __forceinline__ ChunkBuf chunk_buf(const TreeArgs &a, int32_t chunk) {
-  double *p = a.scratch + (int64_t)chunk * a.stride;
-  return ChunkBuf{__builtin_amdgcn_make_buffer_rsrc(p, 0, (int)(a.stride * (int64_t)sizeof(double)), 0x00027000)};
+__device__ __forceinline__ double *chunk_mem(const TreeArgs &a, const TreeItem &it, int32_t chunk) {
+  return a.scratch + (int64_t)(it.at + chunk * it.stride) * kTreeLine;
+}
+__device__ __forceinline__ ChunkBuf chunk_buf(const TreeArgs &a, const TreeItem &it, int32_t chunk) {
+  return ChunkBuf{__builtin_amdgcn_make_buffer_rsrc(chunk_mem(a, it, chunk), 0,
+                                                    it.stride * kTreeLine * (int)sizeof(double), 0x00027000)};
 }
 template <class S>
 __device__ __forceinline__ S get(const ChunkBuf &m, uint32_t off) {
@@ -615,7 +620,7 @@ __global__ __launch_bounds__(kLeafWaves * 64, 4) void tree_leaf(const TreeArgs a
     }
     S v[kStage];
     if constexpr (!SP) {
-      const ChunkBuf m = chunk_buf(a, chunk);
+      const ChunkBuf m = chunk_buf(a, it, chunk);
 #pragma unroll
       for (int j = 0; j < kStage; ++j) v[j] = get<S>(m, at[j]);
       // As many stores (to nowhere) as a chunk's follow its loads in the loop:
@@ -625,7 +630,7 @@ __global__ __launch_bounds__(kLeafWaves * 64, 4) void tree_leaf(const TreeArgs a
       for (int o = 0; o < 8; ++o) put(m, kNone, T(0));
     }
     for (; chunk < end; ++chunk, active >>= 1) {
-      const ChunkBuf m = chunk_buf(a, chunk);
+      const ChunkBuf m = chunk_buf(a, it, chunk);
       double *X = reinterpret_cast<double *>(lds_raw) + buf * a.lds_rows * kD;
       buf ^= 1;
       double x[kStage];
@@ -644,7 +649,7 @@ __global__ __launch_bounds__(kLeafWaves * 64, 4) void tree_leaf(const TreeArgs a
         if (slot + j * kSlots < rows) X[(slot + j * kSlots) * kD + l16] = x[j];
       lds_barrier();
       if constexpr (!SP) {
-        const ChunkBuf next = chunk_buf(a, min(chunk + 1, end - 1));
+        const ChunkBuf next = chunk_buf(a, it, min(chunk + 1, end - 1));
 #pragma unroll
         for (int j = 0; j < kStage; ++j) v[j] = get<S>(next, at[j]);
       }
@@ -696,7 +701,7 @@ __global__ __launch_bounds__(kUpperWaves * 64, 4) void tree_upper(const TreeArgs
   const int32_t np = wave_at[wave + 1] - wave_at[wave], p0 = (FWD ? nd.fwd0 : nd.bwd0) + wave_at[wave];
   const int32_t ns = nd.ns, mt = nd.mt, rows = (FWD ? mt : mt + nd.bt) * kT;
   const ChunkOff off = chunk_off(td);
-  const ChunkBuf m = chunk_buf(a, chunk);
+  const ChunkBuf m = chunk_buf(a, it, chunk);
   const int32_t ents = lane < np ? (FWD ? td.fwd : td.bwd)[p0 + lane] : 0;
   const T *mat = sweep_mat<T>(td, which == 0 ? (FWD ? 0 : 1) : (FWD ? 2 : 3));
   T x[kStage];
@@ -759,7 +764,7 @@ __global__ __launch_bounds__(kUpperWaves * 64, 4) void tree_top(const TreeArgs a
   if (kRef && !__any(still_active(a, td, chunk, which, iter, l16))) return;
   const TreeNode AS4 &nd = *(const TreeNode AS4 *)(td.nodes + td.tier[td.n_tiers - 1]);
   const ChunkOff off = chunk_off(td);
-  const ChunkBuf m = chunk_buf(a, chunk);
+  const ChunkBuf m = chunk_buf(a, it, chunk);
   const int32_t ns = nd.ns, mt = nd.mt, row0 = nd.row0, dir = (chunk - it.chunk0) * kD + l16;
   T *X = reinterpret_cast<T *>(lds_raw), *X2 = X + mt * kT * kD;
   T *parts = X2 + mt * kT * kD;
@@ -825,7 +830,7 @@ __global__ __launch_bounds__(256) void tree_in(const TreeArgs a) {
   const int32_t chunk = blockIdx.y;
   const TreeItem it = item_of(a, chunk);
   const TreeDesc AS4 &td = desc_of(it);
-  double *mem = a.scratch + (int64_t)chunk * a.stride;
+  double *mem = chunk_mem(a, it, chunk);
   const int tid = threadIdx.x;
   if (a.stamps && blockIdx.x == 0 && blockIdx.y == 0 && tid == 0) a.stamps[0] = wall_clock64();
   if (a.norms) {
@@ -858,7 +863,7 @@ __global__ __launch_bounds__(256) void tree_spmul(const TreeArgs a) {
   const int32_t chunk = blockIdx.y;
   const TreeItem it = item_of(a, chunk);
   const TreeDesc AS4 &td = desc_of(it);
-  const ChunkBuf m = chunk_buf(a, chunk);
+  const ChunkBuf m = chunk_buf(a, it, chunk);
   const uint32_t y = chunk_off(td).Y;
   const int slot = threadIdx.x >> 4, l16 = threadIdx.x & 15;
   const int32_t dir = (chunk - it.chunk0) * kD + l16;
@@ -914,7 +919,7 @@ __global__ __launch_bounds__(256) void tree_project(const TreeArgs a, int per) {
     const uint32_t yv_at = B.vs >= 0 ? off.Y + (uint32_t)(B.vs * kD + l16) * 8u
                                      : off.P + (uint32_t)((-B.vs - 1) * kD + l16) * 8u;
     for (; chunk < end; ++chunk) {
-      const ChunkBuf m = chunk_buf(a, chunk);
+      const ChunkBuf m = chunk_buf(a, it, chunk);
       const int32_t dir = (chunk - it.chunk0) * kD + l16;
       // identity directions are not stored
       auto one = [&](double v, int32_t vs) {
@@ -970,7 +975,7 @@ __global__ __launch_bounds__(256) void tree_out(const TreeArgs a) {
   const TreeDesc AS4 &td = desc_of(it);
   const int32_t q0 = blockIdx.x * kMoveRows;
   if (q0 >= td.n_p) return;
-  const ChunkBuf m = chunk_buf(a, chunk);
+  const ChunkBuf m = chunk_buf(a, it, chunk);
   const ChunkOff off = chunk_off(td);
   const int tid = threadIdx.x, slot = tid >> 4, l16 = tid & 15;
   const int32_t d0 = (chunk - it.chunk0) * kD, dir = d0 + l16;
@@ -1057,7 +1062,7 @@ __global__ __launch_bounds__(512) void tree_residual(const TreeArgs a, int which
     for (; chunk < end; ++chunk) {
       if (!(active >> (chunk - first) & 1)) continue;
       const bool act = still_active(a, td, chunk, which, iter, l16);
-      const ChunkBuf m = chunk_buf(a, chunk);
+      const ChunkBuf m = chunk_buf(a, it, chunk);
       double y[kRows], z[kRows], acc[kRows], rm = 0.0, xm = 0.0;
       float d[kRows];
 #pragma unroll
@@ -1602,75 +1607,82 @@ void device_tree_free(Network &net) {
 
 int64_t tree_bytes(const DevTree *t) { return t ? t->bytes : 0; }
 
-size_t TreeShape::scratch_bytes() const {
-  const size_t norms = (size_t)norm_iters * 4 * kD;
-  return ((size_t)stride + norms) * sizeof(double) * (size_t)round;
-}
-
 // A round's scratch and chunks at most.  A round costs its launches' chains
 // (13 of 5 to 25 us at 10k buses) besides its traffic, so the fewer the better,
 // even though its vectors then leave the caches: the full Hessian at 10k
 // buses (175 chunks of 6 MB) takes 4.39 ms in rounds of 8, 2.04 in rounds of
 // 32, 1.75 in rounds of 64 and 1.59 in one; four batches of 128 at 70k (32
 // chunks of 50 MB) 4.17 ms in rounds of 256 MB, 2.93 of 1 GB, 2.61 in one.
-constexpr int64_t kRoundBytes = int64_t(2) << 30;
+constexpr size_t kRoundBytes = size_t(2) << 30;
 constexpr int32_t kRoundChunks = 256;
 
-TreeShape tree_shape(const std::vector<TreeRequest> &req, int32_t refine) {
-  TreeShape sh;
-  int64_t chunks = 0;
-  for (const TreeRequest &r : req) {
-    const TreeDesc &d = r.t->d;
-    // FP64: Z, Y, the update rows, W and Y_p; refined: FP64 residual and
-    // solution, the FP32 correction and its update rows
-    const int64_t u = refine >= 0 ? ((int64_t)d.n_x + d.n_u + 1) / 2 : d.n_u;
-    const int64_t rows = 2 * (int64_t)d.n_x + u + 2 * (int64_t)d.n_p;
-    sh.stride = std::max(sh.stride, (rows * kD + 31) / 32 * 32);
-    chunks += (r.k + kD - 1) / kD;
-  }
-  sh.norm_iters = refine >= 0 ? refine + 1 : 0;
-  sh.chunks = (int32_t)chunks;
-  const int64_t fit = std::max<int64_t>(1, kRoundBytes / std::max<int64_t>(1, sh.stride * 8));
-  // as many rounds as that takes, of equal length
-  const int64_t most = std::min<int64_t>(fit, kRoundChunks), rounds = std::max<int64_t>(1, (chunks + most - 1) / most);
-  sh.round = (int32_t)std::max<int64_t>(1, (chunks + rounds - 1) / rounds);
-  return sh;
-}
+size_t TreeWork::bytes() const { return (size_t)(data + (int64_t)round * norm_doubles()) * sizeof(double); }
+int64_t TreeWork::norm_doubles() const { return (int64_t)norm_iters * 4 * kD; }
 
-void tree_items(const std::vector<TreeRequest> &req, const TreeShape &sh, std::vector<TreeItem> &out) {
-  // the requests' chunks in rounds of sh.round, a request split where a round
-  // ends
-  out.clear();
-  int32_t used = 0, round = 0;
-  for (const TreeRequest &r : req)
-    for (int32_t d0 = 0; d0 < r.k;) {
-      if (used == sh.round) {
-        ++round;
-        used = 0;
+TreeWork tree_work(const std::vector<TreeRequest> &req, int32_t refine, size_t most) {
+  TreeWork w;
+  w.norm_iters = refine >= 0 ? refine + 1 : 0;
+  for (const TreeRequest &r : req) w.chunks += (r.k + kD - 1) / kD;
+  const int64_t room = (int64_t)(std::min(most, kRoundBytes) / sizeof(double));
+  // the requests' chunks in rounds of at most `per`, a request split where a
+  // round ends; the number of rounds
+  auto fill = [&](int32_t per) {
+    w.items.clear();
+    w.round = 0;
+    w.data = 0;
+    int32_t used = 0, round = 0;
+    int64_t data = 0;
+    for (const TreeRequest &r : req) {
+      const TreeDesc &d = r.t->d;
+      // FP64: Z, Y, the update rows, W and Y_p; refined: FP64 residual and
+      // solution, the FP32 correction and its update rows
+      const int64_t u = refine >= 0 ? ((int64_t)d.n_x + d.n_u + 1) / 2 : d.n_u;
+      const int64_t rows = 2 * (int64_t)d.n_x + u + 2 * (int64_t)d.n_p,
+                    size = (rows * kD + kTreeLine - 1) / kTreeLine * kTreeLine;
+      bool open = false;  // the last item is this request's, of this round
+      for (int32_t d0 = 0; d0 < r.k; d0 += kD) {
+        if (used == per || (used > 0 && data + size + (used + 1) * w.norm_doubles() > room)) {
+          ++round;
+          used = 0;
+          data = 0;
+          open = false;
+        }
+        if (!open) {
+          TreeItem it{};
+          it.td = r.t->dd;
+          it.W = r.W ? r.W + (int64_t)d0 * r.ldw : nullptr;
+          it.HW = r.HW + (int64_t)d0 * r.ldhw;
+          it.ldw = r.ldw;
+          it.ldhw = r.ldhw;
+          it.identity_from = r.identity_from < 0 ? -1 : r.identity_from + d0;
+          it.chunk0 = used;
+          it.round = round;
+          it.at = (int32_t)((data - used * size) / kTreeLine);
+          it.stride = (int32_t)(size / kTreeLine);
+          it.rinfo = r.rinfo ? r.rinfo + 4 * (int64_t)d0 : nullptr;
+          w.items.push_back(it);
+          open = true;
+        }
+        w.items.back().k += std::min(kD, r.k - d0);
+        w.items.back().chunks += 1;
+        data += size;
+        ++used;
+        w.data = std::max(w.data, data);
+        w.round = std::max(w.round, used);
       }
-      const int32_t chunks = std::min((r.k - d0 + kD - 1) / kD, sh.round - used);
-      TreeItem it{};
-      it.td = r.t->dd;
-      it.W = r.W ? r.W + (int64_t)d0 * r.ldw : nullptr;
-      it.HW = r.HW + (int64_t)d0 * r.ldhw;
-      it.ldw = r.ldw;
-      it.ldhw = r.ldhw;
-      it.k = std::min(r.k - d0, chunks * kD);
-      it.identity_from = r.identity_from < 0 ? -1 : r.identity_from + d0;
-      it.chunk0 = used;
-      it.chunks = chunks;
-      it.round = round;
-      it.rinfo = r.rinfo ? r.rinfo + 4 * (int64_t)d0 : nullptr;
-      out.push_back(it);
-      used += chunks;
-      d0 += it.k;
     }
+    return round + 1;
+  };
+  // as many rounds as that takes, of equal length
+  const int32_t rounds = fill(kRoundChunks);
+  if (rounds > 1) fill((w.chunks + rounds - 1) / rounds);
+  return w;
 }
 
-rh_status tree_launch(const std::vector<TreeRequest> &req, const std::vector<TreeItem> &host_items,
-                      const TreeItem *items, const TreeShape &sh, double *scratch, int32_t refine, double tol,
-                      long long *stamps, hipStream_t s, std::string &err) {
-  if (sh.chunks <= 0) return RH_OK;
+rh_status tree_launch(const std::vector<TreeRequest> &req, const TreeWork &work, const TreeItem *items, double *scratch,
+                      int32_t refine, double tol, long long *stamps, hipStream_t s, std::string &err) {
+  if (work.chunks <= 0) return RH_OK;
+  const std::vector<TreeItem> &host_items = work.items;
   // the largest of every network's dimensions shapes the launches
   std::vector<int32_t> nodes(kTreeTiers, 0);
   int32_t tiers = 0, n_p = 0, n_x = 0, n_bus = 0, n_gp = 0, leaf = 0, upper = 0, top = 0;
@@ -1702,9 +1714,8 @@ rh_status tree_launch(const std::vector<TreeRequest> &req, const std::vector<Tre
   TreeArgs a{};
   a.tol = tol;
   a.scratch = scratch;
-  a.stride = sh.stride;
-  a.norm_iters = sh.norm_iters;
-  a.norms = ref ? scratch + (int64_t)sh.stride * sh.round : nullptr;
+  a.norm_iters = work.norm_iters;
+  a.norms = ref ? scratch + work.data : nullptr;
   a.stamps = stamps;
   for (size_t i0 = 0, i1; i0 < host_items.size(); i0 = i1) {
     uint32_t nc = 0;

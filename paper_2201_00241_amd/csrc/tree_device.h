@@ -24,6 +24,8 @@ struct TreeInc {
 };
 
 constexpr int kTreeTiers = 12;
+// Doubles of a line: chunks start and end at lines.
+constexpr int kTreeLine = 32;
 // Directions a full Hessian gives one call: the rounds within it keep the
 // chip busy, and a call's launches are paid once.
 constexpr int32_t kTreeLaunchDirs = 4096;
@@ -58,8 +60,10 @@ struct TreeItem {
   const double *W;
   double *HW;
   int64_t ldw, ldhw;
-  int32_t k, identity_from, chunk0, chunks, round, pad;
-  double *rinfo;  // refined mode: 4 doubles per column, or null
+  int32_t k, identity_from, chunk0, chunks, round;
+  int32_t at, stride;  // chunk c's place in the scratch is at + c stride, its length stride (in lines of kTreeLine)
+  int32_t pad;
+  double *rinfo;       // refined mode: 4 doubles per column, or null
 };
 
 struct TreeArgs {
@@ -68,7 +72,6 @@ struct TreeArgs {
   int32_t n_items, n_chunks, norm_iters, lds_rows;
   double tol;
   double *scratch, *norms;
-  int64_t stride;  // doubles per chunk
   long long *stamps;
 };
 
@@ -91,19 +94,20 @@ struct TreeRequest {
   int32_t k, identity_from;
   double *rinfo;
 };
-// Doubles of scratch one chunk of the requests takes, and the chunks worth
-// running at once.
-struct TreeShape {
-  int64_t stride = 0;
-  int32_t chunks = 0, round = 0, norm_iters = 0;
-  size_t scratch_bytes() const;  // of one round
+// The requests' chunks in rounds of launches, and the scratch that the
+// longest takes: no more than `most` bytes unless one chunk does.  A chunk
+// takes what its own network needs, whatever others are in the round.
+struct TreeWork {
+  std::vector<TreeItem> items;
+  int32_t chunks = 0, round = 0, norm_iters = 0;  // round: the most chunks of one
+  int64_t data = 0;                               // doubles of a round's chunks; their norms follow
+  int64_t norm_doubles() const;                   // of a chunk
+  size_t bytes() const;
 };
-TreeShape tree_shape(const std::vector<TreeRequest> &req, int32_t refine);
-// The work list (first chunks set), and the launches.  `items`: the list on
-// the device (null for a single request, which travels by value).
-void tree_items(const std::vector<TreeRequest> &req, const TreeShape &sh, std::vector<TreeItem> &out);
-rh_status tree_launch(const std::vector<TreeRequest> &req, const std::vector<TreeItem> &host_items,
-                      const TreeItem *items, const TreeShape &sh, double *scratch, int32_t refine, double tol,
-                      long long *stamps, hipStream_t s, std::string &err);
+TreeWork tree_work(const std::vector<TreeRequest> &req, int32_t refine, size_t most = SIZE_MAX);
+// The launches.  `items`: the work list on the device (null for a single
+// request, whose items travel by value).
+rh_status tree_launch(const std::vector<TreeRequest> &req, const TreeWork &work, const TreeItem *items, double *scratch,
+                      int32_t refine, double tol, long long *stamps, hipStream_t s, std::string &err);
 
 }  // namespace rh

@@ -18,6 +18,7 @@ LIB_PATH = Path(__file__).resolve().parent / "librh.so"
 RH_OK, RH_EINVAL, RH_ENOMEM, RH_ENOCONV, RH_ESINGULAR, RH_ESTATE, RH_EDEVICE, RH_EBUSY = (
     0, -1, -2, -3, -4, -5, -6, -7)
 RH_FP64, RH_FP32_REFINED = 0, 1
+RH_CHUNK_DIRS = 16
 
 _i32p = ctypes.POINTER(ctypes.c_int32)
 _f64p = ctypes.POINTER(ctypes.c_double)

@@ -97,12 +97,17 @@ class Server:
 
     def footprint_bytes(self, req: Request) -> int:
         """Device bytes a request holds while admitted: W and H W, and the launch
-        scratch of as many of its directions as one launch may run."""
+        scratch of as many of its directions as one launch may run, in whole
+        chunks."""
         net = self.nets[req.key]
         kk = req.k if req.k else net.n_p
         _, per_dir = net.device_bytes(req.prec)
         bufs = (2 * req.k if req.k else net.n_p) * net.n_p * 8
-        return bufs + min(kk, self.dirs_per_launch) * per_dir
+        chunk = rh.RH_CHUNK_DIRS
+        # each block that the directions are split into ends in a chunk of its own
+        blocks = [min(self.block, kk - j0) for j0 in range(0, kk, self.block)]
+        dirs = sum(-(-b // chunk) * chunk for b in blocks)
+        return bufs + min(dirs, -(-self.dirs_per_launch // chunk) * chunk) * per_dir
 
     # ---- request life cycle -------------------------------------------------
     def _admit(self, req: Request) -> bool:

@@ -85,3 +85,41 @@ net = rh.Network(rh.Context(0), geo(1000))
 hip.fake_limit(-1, 8 << 20)  # the fronts of 1,000 buses take 14 MB, no other array more than 2
 solved_on_device(net)
 """)
+
+
+@pytest.mark.parametrize("prec", ["RH_FP64", "RH_FP32_REFINED"])
+def test_scratch_per_direction_holds_for_every_call(fake, prec):
+    """A call's launch scratch is at most rh_network_device_bytes' figure for
+    each of its directions, counted in whole chunks, on both paths, also
+    beside a larger network (a batch's work list is extra); and the server's
+    footprint holds it."""
+    fake(f"prec = rh.{prec}" + """
+grids = [geo(1000), geo(8600), geo(12000)]  # states: 1,899; 16,339; 22,799 (the tree path's from 16,000 on)
+W = np.zeros(1)
+whole = lambda k: -(-k // rh.RH_CHUNK_DIRS) * rh.RH_CHUNK_DIRS
+for k in (1, 3, 15, 16, 17, 40):
+    for g in grids[:2]:
+        net = rh.Network(rh.Context(0), g)
+        net.solve()
+        per, before = net.device_bytes(prec)[1], hip.fake_live()
+        figures = 32 * 64 if prec else 0  # the refined mode's report
+        rh.rh_hvp_device(net.h, k, W.ctypes.data, net.n_p, W.ctypes.data, net.n_p, prec)
+        assert 0 < hip.fake_live() - before - figures <= whole(k) * per, (k, net.n_x)
+ctx = rh.Context(0)
+nets = [rh.Network(ctx, g) for g in grids[1:]]
+for net in nets:
+    net.solve()
+per = [net.device_bytes(prec)[1] for net in nets]
+ptr = [W.ctypes.data] * 2
+for ks in ((1, 1), (40, 2), (200, 1)):
+    before = hip.fake_live()
+    b = rh.rh_batch_create(ctx.h, [n.h for n in nets], ks, ptr, [n.n_p for n in nets], ptr, [n.n_p for n in nets], prec=prec)
+    assert hip.fake_live() - before <= sum(whole(k) * p for k, p in zip(ks, per)) + 8192, ks
+    rh.rh_batch_destroy(b)
+from paper_2201_00241_amd.serving import Request, Server
+server = Server.__new__(Server)
+server.nets, server.dirs_per_launch, server.block = {"a": nets[1]}, 4096, 100
+for k, dirs in ((1, 16), (16, 16), (17, 32), (100, 112), (101, 128)):
+    W = 2 * k * nets[1].n_p * 8
+    assert server.footprint_bytes(Request(0, "a", k, prec=prec)) == W + dirs * per[1]
+""")

@@ -1807,10 +1807,23 @@ rh_status grow_scratch(Runner &r, size_t need, hipStream_t s, std::string &err) 
   r.scratch = nullptr;
   r.scratch_bytes = 0;
   void *p = nullptr;
-  HIP_TRY(hipMalloc(&p, need));
+  const rh_status as = device_try_alloc(&p, need, err);
+  if (as != RH_OK) return as;
   r.scratch = (double *)p;
   r.scratch_bytes = need;
   return RH_OK;
+}
+
+// Where there is no memory for the longest rounds of a tree path's work, with
+// `alloc(bytes)` giving RH_ENOMEM, shorter ones do: half as much each time,
+// down to a chunk.
+template <class A>
+rh_status fit_tree_work(const std::vector<TreeRequest> &req, int32_t refine, TreeWork &work, A alloc) {
+  for (;;) {
+    const rh_status s = alloc(work.bytes());
+    if (s != RH_ENOMEM || work.round <= 1) return s;
+    work = tree_work(req, refine, work.bytes() / 2);
+  }
 }
 
 // The next pair of timing events of a runner.
@@ -1842,7 +1855,7 @@ rh_status grow_stamps(Runner &r, int32_t groups, hipStream_t s, std::string &err
 rh_status run_tree(Runner &r, int32_t timing, int32_t refine, double refine_tol, const std::vector<TreeRequest> &req,
                    hipStream_t s, std::string &err, const FixedScratch *fixed = nullptr) {
   // (in more rounds when a fixed range is short)
-  const TreeWork work = fixed ? tree_work(req, refine, (size_t)fixed->bytes) : tree_work(req, refine);
+  TreeWork work = fixed ? tree_work(req, refine, (size_t)fixed->bytes) : tree_work(req, refine);
   if (work.chunks == 0) return RH_OK;
   if (fixed) {
     if ((int64_t)work.bytes() > fixed->bytes) {
@@ -1852,7 +1865,7 @@ rh_status run_tree(Runner &r, int32_t timing, int32_t refine, double refine_tol,
     }
     timing = 0;
   } else {
-    const rh_status gs = grow_scratch(r, work.bytes(), s, err);
+    const rh_status gs = fit_tree_work(req, refine, work, [&](size_t n) { return grow_scratch(r, n, s, err); });
     if (gs != RH_OK) return gs;
   }
   const std::vector<TreeItem> &items = work.items;
@@ -3075,12 +3088,7 @@ namespace {
 rh_status batch_build(DeviceBatch &b, const DeviceInfo &info, int32_t refine, double refine_tol,
                       std::vector<WorkItem> &items, int32_t max_nx, const std::vector<TreeRequest> &req,
                       std::string &err) {
-  const TreeWork work = tree_work(req, refine);
-  const std::vector<TreeItem> &titems = work.items;
-  if (req.size() > 1) {
-    HIP_TRY(hipMalloc(&b.titems_dev, titems.size() * sizeof(TreeItem)));
-    HIP_TRY(hipMemcpy(b.titems_dev, titems.data(), titems.size() * sizeof(TreeItem), hipMemcpyHostToDevice));
-  }
+  TreeWork work = tree_work(req, refine);
   LaunchPlan pl;
   rh_status ps = plan_launch(info, refine, items, max_nx, pl, err);
   if (ps != RH_OK) return ps;
@@ -3088,9 +3096,19 @@ rh_status batch_build(DeviceBatch &b, const DeviceInfo &info, int32_t refine, do
   b.groups = pl.groups + work.chunks;
   // the two kinds of launches run side by side, with scratch of their own
   const size_t gs_bytes = ((size_t)pl.groups * pl.stride * sizeof(double) + 255) / 256 * 256;
-  const size_t ts_bytes = work.chunks > 0 ? work.bytes() : 0;
-  HIP_TRY(hipMalloc(&b.scratch, std::max<size_t>(256, gs_bytes + ts_bytes)));
+  const rh_status ss = fit_tree_work(req, refine, work, [&](size_t n) {
+    void *p = nullptr;
+    const rh_status as = device_try_alloc(&p, std::max<size_t>(256, gs_bytes + n), err);
+    b.scratch = (double *)p;
+    return as;
+  });
+  if (ss != RH_OK) return ss;
   double *tree_scratch = b.scratch + gs_bytes / sizeof(double);
+  const std::vector<TreeItem> &titems = work.items;
+  if (req.size() > 1) {
+    HIP_TRY(hipMalloc(&b.titems_dev, titems.size() * sizeof(TreeItem)));
+    HIP_TRY(hipMemcpy(b.titems_dev, titems.data(), titems.size() * sizeof(TreeItem), hipMemcpyHostToDevice));
+  }
   LaunchArgs la{};
   la.refine = refine;
   la.refine_tol = refine_tol;

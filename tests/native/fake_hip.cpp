@@ -20,7 +20,7 @@ std::map<void *, size_t> live;
 size_t live_bytes = 0, peak_bytes = 0;
 int64_t n_allocs = 0, n_launches = 0, n_streams = 0, max_bytes = -1, max_one = -1;
 std::map<const void *, size_t> bound;
-std::map<std::string, int> refuse;  // calls to let through before one is refused
+std::map<std::string, int> refuse;  // calls to let through before one is refused (memory: an allocation, for lack of it)
 hipError_t last = hipSuccess;
 constexpr size_t kDefaultLds = 64 * 1024, kLds = 160 * 1024;
 char symbol[(size_t)128 << 20];
@@ -38,7 +38,7 @@ bool refused(const char *name) {
 }
 hipError_t alloc(void **p, size_t n) {
   std::lock_guard<std::recursive_mutex> l(mu);
-  if ((max_bytes >= 0 && live_bytes + n > (size_t)max_bytes) || (max_one >= 0 && n > (size_t)max_one))
+  if ((max_bytes >= 0 && live_bytes + n > (size_t)max_bytes) || (max_one >= 0 && n > (size_t)max_one) || refused("memory"))
     return done(hipErrorOutOfMemory);
   if (refused("hipMalloc")) return done(hipErrorInvalidValue);
   *p = std::calloc(1, n ? n : 1);

@@ -123,3 +123,39 @@ for k, dirs in ((1, 16), (16, 16), (17, 32), (100, 112), (101, 128)):
     W = 2 * k * nets[1].n_p * 8
     assert server.footprint_bytes(Request(0, "a", k, prec=prec)) == W + dirs * per[1]
 """)
+
+
+@pytest.mark.parametrize("prec", ["RH_FP64", "RH_FP32_REFINED"])
+def test_rounds_shorten_where_memory_is_short(fake, prec):
+    """A call whose directions' scratch is not to be had runs in shorter
+    rounds, eager and recorded, down to a chunk."""
+    fake(f"prec = rh.{prec}" + """
+ctx = rh.Context(0)
+net = rh.Network(ctx, geo(8600))
+net.solve()
+W = np.zeros(1)
+per = net.device_bytes(prec)[1]
+args = [ctx.h, [net.h], [1024], [W.ctypes.data], [net.n_p], [W.ctypes.data], [net.n_p]]
+def call():
+    before = hip.fake_launches()
+    rh.rh_hvp_device(net.h, 1024, W.ctypes.data, net.n_p, W.ctypes.data, net.n_p, prec)
+    rounds = hip.fake_launches() - before
+    before = hip.fake_launches()
+    rh.rh_batch_destroy(rh.rh_batch_create(*args, prec=prec))
+    assert hip.fake_launches() - before == rounds
+    return rounds
+hip.fake_limit(-1, 17 * per)  # a chunk
+one = call() // 64
+hip.fake_limit(-1, 16 * 20 * per)  # 64 chunks, halved to 16
+assert call() == 4 * one
+hip.fake_limit(-1, -1)
+assert call() == one
+net2 = rh.Network(rh.Context(0), geo(8600))
+net2.solve()
+hip.fake_limit(-1, 15 * per)
+try:
+    rh.rh_hvp_device(net2.h, 16, W.ctypes.data, net.n_p, W.ctypes.data, net.n_p, prec)
+    assert False, "no chunk fits"
+except rh.RhError as e:
+    assert e.status == rh.RH_ENOMEM, e
+""")

@@ -2807,7 +2807,9 @@ rh_status device_upload(Network &net, std::string &err, const std::function<rh_s
     }
     bool used = false;
     rh_status s = tree_upload(net, device_newton_factors(net), &used, err);
-    if (s != RH_OK) return s;
+    // (without the memory for the nodes' matrices the other path takes the
+    // network, until a solve finds it)
+    if (s != RH_OK && s != RH_ENOMEM) return s;
     if (used) {
       dn->tree = true;
       if ((s = upload_common(net, dn, err)) != RH_OK) return s;

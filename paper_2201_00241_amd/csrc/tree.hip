@@ -1259,7 +1259,8 @@ template <class T>
 rh_status t_alloc(DevTree &t, size_t n, T **out, std::string &err) {
   void *p = nullptr;
   const size_t nb = std::max<size_t>(16, n * sizeof(T));
-  HIP_TRY(hipMalloc(&p, nb));
+  const rh_status s = device_try_alloc(&p, nb, err);
+  if (s != RH_OK) return s;
   t.allocs.push_back(p);
   t.bytes += (int64_t)nb;
   *out = static_cast<T *>(p);

@@ -79,7 +79,8 @@ struct DevTree;  // a network's plan and device arrays (tree.hip)
 
 // Builds the plan on the first call (false in *used: not for this network),
 // and uploads or refreshes the operating point's values.  d_factors: the flat
-// factors when they are on the device already, else null.
+// factors when they are on the device already, else null.  RH_ENOMEM: there is
+// no memory for it, and nothing is kept.
 rh_status tree_upload(Network &net, const double *d_factors, bool *used, std::string &err);
 // Barrier-separated steps of a forward and a backward sweep, along the
 // tiers' longest nodes.

@@ -159,3 +159,29 @@ try:
 except rh.RhError as e:
     assert e.status == rh.RH_ENOMEM, e
 """)
+
+
+def test_no_memory_for_the_nodes_matrices(fake):
+    """The one-workgroup path takes a network whose nodes' matrices find no
+    memory, and gives it back with the next solve that finds it; an error of the
+    device is none of this."""
+    fake("""
+net = rh.Network(rh.Context(0), geo(8600))
+W = np.zeros(1)
+def launches():
+    before = hip.fake_launches()
+    rh.rh_hvp_device(net.h, 16, W.ctypes.data, net.n_p, W.ctypes.data, net.n_p)
+    return hip.fake_launches() - before
+hip.fake_refuse(b"memory", 10)
+net.solve()
+assert launches() == 1
+net.solve()
+assert launches() > 10
+hip.fake_refuse(b"hipMalloc", 10)
+net = rh.Network(rh.Context(0), geo(8600))
+try:
+    net.solve()
+    assert False, "the refused call went unnoticed"
+except rh.RhError as e:
+    assert e.status == rh.RH_EDEVICE, e
+""")

@@ -2946,11 +2946,10 @@ rh_status device_hvp_noalloc(Network &net, int32_t k, const double *dW, int64_t 
   it.rinfo = nullptr;  // no per-column refinement figures
   const FixedScratch fx{static_cast<double *>(fp), (int64_t)RH_NOALLOC_SCRATCH_BYTES};
   const int32_t refine = prec == RH_FP32_REFINED ? net.ctx->refine : -1;
-  if (tree_path(net))
+  // (a forced launch shape whose arrays are not there yet would allocate them)
+  if (tree_path(net) || !dn->groups)
     return run_tree(dn->run, 0, refine, net.ctx->refine_tol,
                     {TreeRequest{net.dtree, dW, dHW, ldw, ldhw, k, -1, nullptr}}, (hipStream_t)stream, err, &fx);
-  const rh_status gs = need_groups(net, err);
-  if (gs != RH_OK) return gs;
   const rh_tile &t = net.tile[prec == RH_FP32_REFINED ? 1 : 0];
   return run_items(dn->info, dn->run, 0, refine, net.ctx->refine_tol, items, net.n_x, (hipStream_t)stream, err,
                    &fx, t.k > 0 ? t.dirs_per_group : 0);

@@ -185,3 +185,21 @@ try:
 except rh.RhError as e:
     assert e.status == rh.RH_EDEVICE, e
 """)
+
+
+@pytest.mark.parametrize("force", ["RH_NO_LDS", "RH_DIRS_PER_GROUP"])
+@pytest.mark.parametrize("n_bus", [1000, 8600])
+def test_the_allocation_free_call_never_allocates(fake, n_bus, force):
+    """Not for a launch shape forced after the solve either, whose arrays a
+    network of the tree path does not hold."""
+    fake(f"""
+net = rh.Network(rh.Context(0), geo({n_bus}))
+net.solve()
+os.environ["{force}"] = "1"
+W = np.zeros(1)
+before = hip.fake_allocs(), hip.fake_launches()
+for prec in (rh.RH_FP64, rh.RH_FP32_REFINED):
+    for k in (1, 300):
+        rh.rh_hvp_device_noalloc(net.h, k, W.ctypes.data, net.n_p, W.ctypes.data, net.n_p, prec)
+assert hip.fake_allocs() == before[0] and hip.fake_launches() >= before[1] + 4
+""")

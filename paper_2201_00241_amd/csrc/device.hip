@@ -1501,12 +1501,33 @@ namespace {
     }                                                                          \
   } while (0)
 
+// A stream beside the caller's, for batches with networks of both paths, and the
+// events that order it.
+struct Side {
+  hipStream_t s = nullptr;
+  hipEvent_t fork = nullptr, join = nullptr;
+  ~Side() {
+    if (fork) (void)hipEventDestroy(fork);
+    if (join) (void)hipEventDestroy(join);
+    if (s) (void)hipStreamDestroy(s);
+  }
+};
+
 struct DeviceInfo {
   int device = -1;
   int cus = 0;
   size_t lds_max = 0;  // dynamic LDS a workgroup may use
   double wall_khz = 0.0;
 };
+
+rh_status side_create(std::unique_ptr<Side> &out, std::string &err) {
+  std::unique_ptr<Side> d(new Side());
+  HIP_TRY(hipStreamCreateWithFlags(&d->s, hipStreamNonBlocking));
+  HIP_TRY(hipEventCreateWithFlags(&d->fork, hipEventDisableTiming));
+  HIP_TRY(hipEventCreateWithFlags(&d->join, hipEventDisableTiming));
+  out = std::move(d);
+  return RH_OK;
+}
 
 // Launch resources: per-workgroup scratch, timing events, phase stamps and the
 // device copy of a work list.  A network owns one (its own calls); a context
@@ -1524,10 +1545,7 @@ struct Runner {
   TreeItem *titems_dev = nullptr, *titems_host = nullptr;  // the tree path's work list
   int32_t titems_cap = 0;
   hipEvent_t titems_done = nullptr;
-  // a stream beside this one, for batches with networks of both paths, and the
-  // events that order it
-  hipStream_t side = nullptr;
-  hipEvent_t fork = nullptr, join = nullptr;
+  Side *side = nullptr;
   int32_t launches = 0, last_c = 0;
   long long *step_stamps = nullptr;  // debug (RH_STEP_STAMPS)
   bool step_stamps_pending = false;
@@ -1559,9 +1577,7 @@ void runner_free(Runner &r) {
   if (r.titems_dev) (void)hipFree(r.titems_dev);
   if (r.titems_host) (void)hipHostFree(r.titems_host);
   if (r.titems_done) (void)hipEventDestroy(r.titems_done);
-  if (r.fork) (void)hipEventDestroy(r.fork);
-  if (r.join) (void)hipEventDestroy(r.join);
-  if (r.side) (void)hipStreamDestroy(r.side);
+  delete r.side;
   if (r.step_stamps) (void)hipFree(r.step_stamps);
   r = Runner();
 }
@@ -1731,12 +1747,13 @@ int32_t choose_c(int64_t k, int32_t cus, int64_t n_x, size_t lds_max, bool lds, 
 
 // Launch the reduction over a list of work items (host copies; their nd
 // pointers are device descriptors).  max_nx is the largest n_x among them.
-// A caller-independent scratch range (the fixed array of the allocation-free
-// entry point): the launch runs at most bytes / (workgroup scratch) workgroups
-// and records no timing.
+// A scratch range that is there already: the launch runs at most bytes /
+// (workgroup scratch) workgroups.  quiet: the fixed array of the
+// allocation-free entry point, whose one item records no timing.
 struct FixedScratch {
   double *ptr;
   int64_t bytes;
+  bool quiet = true;
 };
 
 // Shape of one batched launch: directions per workgroup, where the working
@@ -1851,23 +1868,9 @@ rh_status grow_stamps(Runner &r, int32_t groups, hipStream_t s, std::string &err
 }
 
 // The tree path's launches for a list of requests (a sequence of kernels that
-// counts as one launch of the reduction).
-rh_status run_tree(Runner &r, int32_t timing, int32_t refine, double refine_tol, const std::vector<TreeRequest> &req,
-                   hipStream_t s, std::string &err, const FixedScratch *fixed = nullptr) {
-  // (in more rounds when a fixed range is short)
-  TreeWork work = fixed ? tree_work(req, refine, (size_t)fixed->bytes) : tree_work(req, refine);
-  if (work.chunks == 0) return RH_OK;
-  if (fixed) {
-    if ((int64_t)work.bytes() > fixed->bytes) {
-      err = "network too large for the fixed scratch: a round needs " + std::to_string(work.bytes()) + " bytes, " +
-            std::to_string(fixed->bytes) + " available";
-      return RH_EINVAL;
-    }
-    timing = 0;
-  } else {
-    const rh_status gs = fit_tree_work(req, refine, work, [&](size_t n) { return grow_scratch(r, n, s, err); });
-    if (gs != RH_OK) return gs;
-  }
+// counts as one launch of the reduction), their scratch at hand.
+rh_status run_tree_at(Runner &r, int32_t timing, int32_t refine, double refine_tol, const std::vector<TreeRequest> &req,
+                      const TreeWork &work, double *scratch, hipStream_t s, std::string &err) {
   const std::vector<TreeItem> &items = work.items;
   if (req.size() > 1) {  // (a single request travels by value)
     if ((int32_t)items.size() > r.titems_cap) {
@@ -1898,14 +1901,31 @@ rh_status run_tree(Runner &r, int32_t timing, int32_t refine, double refine_tol,
     if (es != RH_OK) return es;
     HIP_TRY(hipEventRecord(e0, s));
   }
-  const rh_status st = tree_launch(req, work, r.titems_dev, fixed ? fixed->ptr : r.scratch, refine, refine_tol, stamps, s,
-                                   err);
+  const rh_status st = tree_launch(req, work, r.titems_dev, scratch, refine, refine_tol, stamps, s, err);
   if (st != RH_OK) return st;
   if (req.size() > 1) HIP_TRY(hipEventRecord(r.titems_done, s));
   if (timing >= 1) HIP_TRY(hipEventRecord(e1, s));
   r.launches += 1;
   r.last_c = kTreeDirs;
   return RH_OK;
+}
+
+rh_status run_tree(Runner &r, int32_t timing, int32_t refine, double refine_tol, const std::vector<TreeRequest> &req,
+                   hipStream_t s, std::string &err, const FixedScratch *fixed = nullptr) {
+  // (in more rounds when a fixed range is short)
+  TreeWork work = fixed ? tree_work(req, refine, (size_t)fixed->bytes) : tree_work(req, refine);
+  if (work.chunks == 0) return RH_OK;
+  if (fixed) {
+    if ((int64_t)work.bytes() > fixed->bytes) {
+      err = "network too large for the fixed scratch: a round needs " + std::to_string(work.bytes()) + " bytes, " +
+            std::to_string(fixed->bytes) + " available";
+      return RH_EINVAL;
+    }
+    return run_tree_at(r, 0, refine, refine_tol, req, work, fixed->ptr, s, err);
+  }
+  const rh_status gs = fit_tree_work(req, refine, work, [&](size_t n) { return grow_scratch(r, n, s, err); });
+  if (gs != RH_OK) return gs;
+  return run_tree_at(r, timing, refine, refine_tol, req, work, r.scratch, s, err);
 }
 
 rh_status run_items(const DeviceInfo &info, Runner &r, int32_t timing, int32_t refine, double refine_tol,
@@ -1927,12 +1947,12 @@ rh_status run_items(const DeviceInfo &info, Runner &r, int32_t timing, int32_t r
             " available";
       return RH_EINVAL;
     }
-    if (items.size() != 1) {
+    if (fixed->quiet && items.size() != 1) {
       err = "internal: the fixed scratch takes one work item";
       return RH_EDEVICE;
     }
     groups = (int32_t)std::min<int64_t>(groups, fit);
-    timing = 0;
+    if (fixed->quiet) timing = 0;
   }
   if (!fixed) {
     const rh_status gs = grow_scratch(r, (size_t)groups * stride * sizeof(double), s, err);
@@ -1968,7 +1988,7 @@ rh_status run_items(const DeviceInfo &info, Runner &r, int32_t timing, int32_t r
     la.items = r.items_dev;
   }
   la.step_stamps = nullptr;
-  if (!fixed && std::getenv("RH_STEP_STAMPS")) {
+  if (!(fixed && fixed->quiet) && std::getenv("RH_STEP_STAMPS")) {
     if (!r.step_stamps) HIP_TRY(hipMalloc(&r.step_stamps, 4 * kSweepStamps * sizeof(long long)));
     HIP_TRY(hipMemsetAsync(r.step_stamps, 0, 4 * kSweepStamps * sizeof(long long), s));
     la.step_stamps = r.step_stamps;
@@ -2999,29 +3019,42 @@ rh_status device_hvp_batch(Context &ctx, int32_t n, Network *const *nets, const 
   // long as its longest chain and leaves much of the chip idle, on a stream
   // beside the tree path's sequence (networks of 1k, 10k, 9, 1k and 10k buses:
   // 341 us one after the other, 291 side by side, 364 all on the one-workgroup
-  // path; a refined batch that takes 1146 us there 1164 and 928).
-  {
-    Runner &r = ctx.dev->on(stream);
-    if (!r.side) HIP_TRY(hipStreamCreateWithFlags(&r.side, hipStreamNonBlocking));
-    if (!r.fork) HIP_TRY(hipEventCreateWithFlags(&r.fork, hipEventDisableTiming));
-    if (!r.join) HIP_TRY(hipEventCreateWithFlags(&r.join, hipEventDisableTiming));
-  }
-  hipStream_t side = ctx.dev->on(stream).side;
-  (void)ctx.dev->on(side);  // (adding a runner moves the others)
+  // path; a refined batch that takes 1146 us there 1164 and 928).  Their
+  // scratch is one allocation, of two parts.
   Runner &r = ctx.dev->on(stream);
-  HIP_TRY(hipEventRecord(r.fork, s));
-  HIP_TRY(hipStreamWaitEvent(side, r.fork, 0));
+  if (!r.side) {
+    std::unique_ptr<Side> made;
+    const rh_status ms = side_create(made, err);
+    if (ms != RH_OK) return ms;
+    r.side = made.release();
+  }
+  LaunchPlan pl;
+  const rh_status ps = plan_launch(ctx.dev->info, refine, items, max_nx, pl, err);
+  if (ps != RH_OK) return ps;
+  const size_t gs_bytes = ((size_t)pl.groups * pl.stride * sizeof(double) + 255) / 256 * 256;
+  TreeWork work = tree_work(req, refine);
+  const rh_status ws =
+      fit_tree_work(req, refine, work, [&](size_t b) { return grow_scratch(r, gs_bytes + b, s, err); });
+  if (ws != RH_OK) return ws;
+  const FixedScratch gs{r.scratch, (int64_t)gs_bytes, false};
+  HIP_TRY(hipEventRecord(r.side->fork, s));
+  HIP_TRY(hipStreamWaitEvent(r.side->s, r.side->fork, 0));
+  // whatever comes of them, the caller's stream waits for what is under way
+  auto join = [&](std::string &e) {
+    hipError_t h = hipEventRecord(r.side->join, r.side->s);
+    if (h == hipSuccess) h = hipStreamWaitEvent(s, r.side->join, 0);
+    if (h != hipSuccess) e = std::string("joining the side stream: ") + hipGetErrorString(h);
+    return h == hipSuccess ? RH_OK : RH_EDEVICE;
+  };
   // (phase stamps are those of one kind of launch: the other's)
-  const rh_status si = run_items(ctx.dev->info, ctx.dev->on(side), ctx.timing, refine, ctx.refine_tol, items, max_nx,
-                                 side, err);
-  std::string err_t;
-  const rh_status st = si == RH_OK ? run_tree(r, std::min(ctx.timing, 1), refine, ctx.refine_tol, req, s, err_t) : RH_OK;
-  // whatever came of it, the caller's stream waits for what is under way
-  HIP_TRY(hipEventRecord(r.join, side));
-  HIP_TRY(hipStreamWaitEvent(s, r.join, 0));
-  if (si != RH_OK) return si;
-  if (st != RH_OK) err = err_t;
-  return st;
+  rh_status st = run_items(ctx.dev->info, r, ctx.timing, refine, ctx.refine_tol, items, max_nx, r.side->s, err, &gs);
+  if (st == RH_OK)
+    st = run_tree_at(r, std::min(ctx.timing, 1), refine, ctx.refine_tol, req, work, r.scratch + gs_bytes / sizeof(double),
+                     s, err);
+  std::string e;
+  const rh_status js = join(e);
+  if (st == RH_OK && js != RH_OK) err = e;
+  return st != RH_OK ? st : js;
 }
 
 bool device_tree(const Network &net) { return net.dev && tree_path(net); }
@@ -3134,20 +3167,11 @@ rh_status batch_build(DeviceBatch &b, const DeviceInfo &info, int32_t refine, do
     if (as != RH_OK) return as;
   }
   // with both kinds, a second stream and the events that make it a branch
-  struct Side {
-    hipStream_t s = nullptr;
-    hipEvent_t fork = nullptr, join = nullptr;
-    ~Side() {
-      if (fork) (void)hipEventDestroy(fork);
-      if (join) (void)hipEventDestroy(join);
-      if (s) (void)hipStreamDestroy(s);
-    }
-  } side;
+  std::unique_ptr<Side> side;
   const bool both = work.chunks > 0 && pl.n_chunks > 0;
   if (both) {
-    HIP_TRY(hipStreamCreateWithFlags(&side.s, hipStreamNonBlocking));
-    HIP_TRY(hipEventCreateWithFlags(&side.fork, hipEventDisableTiming));
-    HIP_TRY(hipEventCreateWithFlags(&side.join, hipEventDisableTiming));
+    const rh_status ms = side_create(side, err);
+    if (ms != RH_OK) return ms;
   }
   HIP_TRY(hipStreamCreateWithFlags(&b.cap, hipStreamNonBlocking));
   HIP_TRY(hipStreamBeginCapture(b.cap, hipStreamCaptureModeThreadLocal));
@@ -3157,17 +3181,17 @@ rh_status batch_build(DeviceBatch &b, const DeviceInfo &info, int32_t refine, do
     ls = RH_EDEVICE;
     e2 = std::string("recording a batch: ") + hipGetErrorString(e);
   };
-  hipStream_t gs = both ? side.s : b.cap;
+  hipStream_t gs = both ? side->s : b.cap;
   if (both) {
-    check(hipEventRecord(side.fork, b.cap));
-    check(hipStreamWaitEvent(side.s, side.fork, 0));
+    check(hipEventRecord(side->fork, b.cap));
+    check(hipStreamWaitEvent(side->s, side->fork, 0));
   }
   if (ls == RH_OK && pl.n_chunks > 0) ls = launch_plan(pl, pl.groups, gs, la, e2, kLaunchOnly);
   if (ls == RH_OK && work.chunks > 0)
     ls = tree_launch(req, work, b.titems_dev, tree_scratch, refine, refine_tol, nullptr, b.cap, e2);
   if (both) {
-    check(hipEventRecord(side.join, side.s));
-    check(hipStreamWaitEvent(b.cap, side.join, 0));
+    check(hipEventRecord(side->join, side->s));
+    check(hipStreamWaitEvent(b.cap, side->join, 0));
   }
   hipGraph_t g = nullptr;
   const hipError_t ce = hipStreamEndCapture(b.cap, &g);

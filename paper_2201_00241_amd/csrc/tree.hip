@@ -1642,7 +1642,7 @@ TreeWork tree_work(const std::vector<TreeRequest> &req, int32_t refine, size_t m
                     size = (rows * kD + kTreeLine - 1) / kTreeLine * kTreeLine;
       bool open = false;  // the last item is this request's, of this round
       for (int32_t d0 = 0; d0 < r.k; d0 += kD) {
-        if (used == per || (used > 0 && data + size + (used + 1) * w.norm_doubles() > room)) {
+        if (used == per || (used > 0 && std::max(w.data, data + size) + std::max(w.round, used + 1) * w.norm_doubles() > room)) {
           ++round;
           used = 0;
           data = 0;

@@ -11,6 +11,7 @@
 #include <cstring>
 #include <map>
 #include <mutex>
+#include <new>
 #include <string>
 
 namespace {
@@ -20,6 +21,7 @@ std::map<void *, size_t> live;
 size_t live_bytes = 0, peak_bytes = 0;
 int64_t n_allocs = 0, n_launches = 0, n_streams = 0, max_bytes = -1, max_one = -1;
 std::map<const void *, size_t> bound;
+std::map<void *, int64_t> waits;
 std::map<std::string, int> refuse;  // calls to let through before one is refused (memory: an allocation, for lack of it)
 hipError_t last = hipSuccess;
 constexpr size_t kDefaultLds = 64 * 1024, kLds = 160 * 1024;
@@ -71,6 +73,7 @@ void fake_peak_reset() { peak_bytes = live_bytes; }
 int64_t fake_allocs() { return n_allocs; }
 int64_t fake_launches() { return n_launches; }
 int64_t fake_streams() { return n_streams; }
+int64_t fake_waits(void *stream) { return waits[stream]; }
 
 // ---- the runtime
 hipError_t hipSetDevice(int) { return hipSuccess; }
@@ -103,7 +106,10 @@ hipError_t hipMemcpy(void *d, const void *s, size_t n, hipMemcpyKind) {
   if (refused("hipMemcpy")) return done(hipErrorInvalidValue);
   return std::memcpy(d, s, n), hipSuccess;
 }
-hipError_t hipMemcpyAsync(void *d, const void *s, size_t n, hipMemcpyKind k, hipStream_t) { return hipMemcpy(d, s, n, k); }
+hipError_t hipMemcpyAsync(void *d, const void *s, size_t n, hipMemcpyKind k, hipStream_t) {
+  if (refused("hipMemcpyAsync")) throw std::bad_alloc();  // (as a vector of the library's own would)
+  return hipMemcpy(d, s, n, k);
+}
 hipError_t hipMemcpy2D(void *d, size_t dp, const void *s, size_t sp, size_t w, size_t h, hipMemcpyKind) {
   for (size_t i = 0; i < h; ++i) std::memcpy((char *)d + i * dp, (const char *)s + i * sp, w);
   return hipSuccess;
@@ -143,7 +149,10 @@ hipError_t hipStreamCreateWithFlags(hipStream_t *s, unsigned) {
 }
 hipError_t hipStreamDestroy(hipStream_t s) { return std::free((void *)s), hipSuccess; }
 hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
-hipError_t hipStreamWaitEvent(hipStream_t, hipEvent_t, unsigned) { return hipSuccess; }
+hipError_t hipStreamWaitEvent(hipStream_t s, hipEvent_t, unsigned) {
+  std::lock_guard<std::recursive_mutex> l(mu);
+  return ++waits[(void *)s], hipSuccess;
+}
 hipError_t hipStreamBeginCapture(hipStream_t, hipStreamCaptureMode) { return hipSuccess; }
 hipError_t hipStreamEndCapture(hipStream_t, hipGraph_t *g) { return *g = (hipGraph_t)std::malloc(1), hipSuccess; }
 hipError_t hipGraphInstantiate(hipGraphExec_t *e, hipGraph_t, hipGraphNode_t *, char *, size_t) {

@@ -17,6 +17,7 @@ hip = ctypes.CDLL(sys.argv[1], mode=ctypes.RTLD_GLOBAL)
 for f in ("live", "peak", "allocs", "launches", "streams"):
     getattr(hip, "fake_" + f).restype = ctypes.c_int64
 hip.fake_limit.argtypes = [ctypes.c_int64, ctypes.c_int64]
+hip.fake_waits.argtypes, hip.fake_waits.restype = [ctypes.c_void_p], ctypes.c_int64
 import numpy as np
 import gridgen
 from paper_2201_00241_amd import rh
@@ -43,7 +44,7 @@ def fake(tmp_path_factory):
 
     def run(code):
         res = subprocess.run([sys.executable, "-c", PRELUDE + code, str(out)], cwd=ROOT, capture_output=True, text=True,
-                             timeout=300)
+                             timeout=100)
         assert res.returncode == 0, res.stdout + res.stderr
         return res.stdout
 
@@ -202,4 +203,33 @@ for prec in (rh.RH_FP64, rh.RH_FP32_REFINED):
     for k in (1, 300):
         rh.rh_hvp_device_noalloc(net.h, k, W.ctypes.data, net.n_p, W.ctypes.data, net.n_p, prec)
 assert hip.fake_allocs() == before[0] and hip.fake_launches() >= before[1] + 4
+""")
+
+
+MIXED = """
+ctx = rh.Context(0)
+nets = [rh.Network(ctx, g) for g in (geo(60), geo(8600), geo(100), geo(8700, 2))]
+for net in nets:
+    net.solve()
+W = np.zeros(1)
+ptr = [W.ctypes.data] * 4
+def batch(stream, prec=rh.RH_FP64):
+    n_p = [n.n_p for n in nets]
+    rh.rh_hvp_batch_device(ctx.h, [n.h for n in nets], [5, 17, 1, 3], ptr, n_p, ptr, n_p, None, prec, stream)
+"""
+
+
+def test_the_first_batch_of_both_paths_sets_up_little(fake):
+    """Its scratch is one allocation, as that of other batches, and it has one
+    side stream for each of the caller's."""
+    fake(MIXED + """
+streams, allocs = hip.fake_streams(), hip.fake_allocs()
+batch(0x100)
+assert hip.fake_streams() == streams + 1
+assert hip.fake_allocs() == allocs + 3  # the scratch and the two work lists
+batch(0x100)
+batch(0x100, rh.RH_FP32_REFINED)
+assert hip.fake_streams() == streams + 1
+batch(0x200)
+assert hip.fake_streams() == streams + 2
 """)

@@ -3046,11 +3046,18 @@ rh_status device_hvp_batch(Context &ctx, int32_t n, Network *const *nets, const 
     if (h != hipSuccess) e = std::string("joining the side stream: ") + hipGetErrorString(h);
     return h == hipSuccess ? RH_OK : RH_EDEVICE;
   };
-  // (phase stamps are those of one kind of launch: the other's)
-  rh_status st = run_items(ctx.dev->info, r, ctx.timing, refine, ctx.refine_tol, items, max_nx, r.side->s, err, &gs);
-  if (st == RH_OK)
-    st = run_tree_at(r, std::min(ctx.timing, 1), refine, ctx.refine_tol, req, work, r.scratch + gs_bytes / sizeof(double),
-                     s, err);
+  rh_status st;
+  try {
+    // (phase stamps are those of one kind of launch: the other's)
+    st = run_items(ctx.dev->info, r, ctx.timing, refine, ctx.refine_tol, items, max_nx, r.side->s, err, &gs);
+    if (st == RH_OK)
+      st = run_tree_at(r, std::min(ctx.timing, 1), refine, ctx.refine_tol, req, work, r.scratch + gs_bytes / sizeof(double),
+                       s, err);
+  } catch (...) {
+    std::string e;
+    (void)join(e);
+    throw;
+  }
   std::string e;
   const rh_status js = join(e);
   if (st == RH_OK && js != RH_OK) err = e;

@@ -233,3 +233,20 @@ assert hip.fake_streams() == streams + 1
 batch(0x200)
 assert hip.fake_streams() == streams + 2
 """)
+
+
+@pytest.mark.parametrize("list_of", [0, 1])
+def test_the_callers_stream_waits_for_what_is_under_way(fake, list_of):
+    """An exception between the two kinds of launches of a batch leaves none
+    of them running beside the caller's stream."""
+    fake(MIXED + f"""
+batch(0x100)
+before = hip.fake_waits(0x100)
+hip.fake_refuse(b"hipMemcpyAsync", {list_of})
+try:
+    batch(0x100)
+    assert False, "the exception went unnoticed"
+except rh.RhError as e:
+    assert e.status == rh.RH_ENOMEM, e
+assert hip.fake_waits(0x100) == before + 1
+""")

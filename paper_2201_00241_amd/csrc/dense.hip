@@ -14,7 +14,8 @@
 // by MFMA.  The other workgroups take the update of the panel before on the
 // columns right of the panel, in 64 x 64 tiles: a lookahead of one panel.
 // A failed pivot (not positive, or not finite) stores its column + 1 in a
-// status word; every later kernel reads it first and does nothing.
+// status word, which the first panel sets; every later kernel reads it first
+// and does nothing.
 // The forward sweep L Y = B rides along: the right-hand sides are extra rows
 // of the augmented matrix [A; B^T], so that at the end B holds Y.
 // chol_back_block then solves L^T X = Y a block of 64 unknowns per launch,
@@ -103,10 +104,6 @@ __device__ __forceinline__ void chol_tile(double (&d)[kSub], double (&rinv)[kSub
     for (int k = C + 1; k < kSub; ++k) asm volatile("" : "+v"(d[k]));
     chol_tile<C + 1>(d, rinv, bad);
   }
-}
-
-__global__ void dense_clear(int32_t *info) {
-  if (threadIdx.x == 0) *info = 0;
 }
 
 // F = A (lower triangle) with tau added on the diagonal; columns per block.
@@ -337,10 +334,8 @@ __device__ __forceinline__ void panel_strip(const Aug &M, int32_t j, int32_t blk
       }
   }
   __syncthreads();
-  if (L.bad >= 0) {
-    if (blk == 0 && tid == 0) *info = j + L.bad + 1;
-    return;
-  }
+  if (blk == 0 && tid == 0 && (L.bad >= 0 || j == 0)) *info = L.bad >= 0 ? j + L.bad + 1 : 0;
+  if (L.bad >= 0) return;
   const int i = tid & (kStrip - 1);
   const int32_t r = row_of(i);
   if (i < kNB) {
@@ -437,7 +432,7 @@ __device__ __forceinline__ void update_tile(const Aug &M, int32_t j, int32_t j1,
 __global__ __launch_bounds__(kThreads, 2) void chol_panel(Aug M, int32_t j, int32_t strips, int32_t T,
                                                          int32_t tiles, int32_t *info, double *diag) {
   __shared__ PanelLds L;
-  if (*info) return;
+  if (j > 0 && *info) return;  // (the first panel sets the word)
   double *mine = diag + (j / kNB & 1) * kNB * kNB, *before = diag + ((j / kNB & 1) ^ 1) * kNB * kNB;
   const int32_t strips_before = (M.rows - j + kNB - 1) / kNB;  // of the panel before
   if ((int32_t)blockIdx.x < strips) {
@@ -545,7 +540,6 @@ rh_status dense_cholesky(int32_t n, double *A, int64_t lda, double *B, int64_t l
   if (!B) nrhs = 0;
   const Aug M{A, B, lda, ldb, n, n + nrhs};
   double *diag = reinterpret_cast<double *>(dinfo) + kInfoWords;
-  hipLaunchKernelGGL(dense_clear, dim3(1), dim3(64), 0, st, dinfo);
   for (int32_t j = 0; j < n; j += kNB) {
     const int32_t below = M.rows - j - std::min(kNB, n - j);  // rows under the diagonal block
     const int32_t strips = std::max(1, (below + kNB - 1) / kNB);

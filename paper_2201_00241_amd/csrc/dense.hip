@@ -358,11 +358,6 @@ __device__ __forceinline__ void put_diag(const Aug &M, int32_t j, const double *
     if (i < nb && c <= i) M.A[(j + i) + (int64_t)(j + c) * M.lda] = diag[e];
   }
 }
-__global__ __launch_bounds__(256) void chol_last_diag(Aug M, int32_t j, const int32_t *info, const double *diag) {
-  if (*info) return;
-  put_diag(M, j, diag);
-}
-
 // Tile (ti, tk), ti >= tk, of a trailing matrix of T tile columns (and more
 // tile rows where there are many right-hand sides) from a linear index.
 __device__ __forceinline__ void tri_tile(int32_t b, int32_t T, int32_t &ti, int32_t &tk) {
@@ -456,19 +451,28 @@ __global__ __launch_bounds__(kThreads, 2) void chol_panel(Aug M, int32_t j, int3
 // z_r -= sum_c L(j0 + c, r) x_c, whose 64 entries are contiguous in column r:
 // 16 lanes take a column together, loaded before the triangle is solved.
 // Workgroup 0 stores the block's x in X (not in B, whose block rows the
-// other workgroups may still be reading).  Columns of B: grid y.
-__global__ __launch_bounds__(256) void chol_back_block(const double *A, int64_t lda, int32_t n, double *B,
-                                                       int64_t ldb, double *X, int32_t j0, const int32_t *info) {
+// other workgroups may still be reading).  Columns of B: grid y.  diag: the
+// block's triangle where it is not in the matrix yet (the last panel's, with
+// several strips), or null; the first workgroup then brings it there.
+__global__ __launch_bounds__(256) void chol_back_block(double *A, int64_t lda, int32_t n, double *B, int64_t ldb, double *X,
+                                                       int32_t j0, const int32_t *info, const double *diag) {
   if (*info) return;
   __shared__ double s_L[64][65];
   __shared__ double s_x[64];
   double *z = B + (int64_t)blockIdx.y * ldb;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, l16 = lane & 15, g = lane >> 4;
   const int32_t bs = min(64, n - j0);
+  const double *T = diag ? diag : A + j0 + (int64_t)j0 * lda;
+  const int64_t ldt = diag ? kNB : lda;
   for (int t = threadIdx.x; t < 64 * 64; t += 256) {
     const int i = t & 63, c = t >> 6;  // consecutive threads: consecutive rows of a column
-    s_L[i][c] = (i < bs && c <= i) ? A[(j0 + i) + (int64_t)(j0 + c) * lda] : 0.0;
+    s_L[i][c] = (i < bs && c <= i) ? T[i + c * ldt] : 0.0;
   }
+  if (diag && blockIdx.x == 0 && blockIdx.y == 0)
+    for (int t = threadIdx.x; t < 64 * 64; t += 256) {
+      const int i = t & 63, c = t >> 6;
+      if (i < bs && c <= i) A[(j0 + i) + (int64_t)(j0 + c) * lda] = diag[t];
+    }
   // the group's rows r (columns of L): entries l16 + 16 m of column r
   double v[4][4];
   const int32_t r0 = (int32_t)blockIdx.x * 64 + wave * 16 + g;
@@ -533,6 +537,12 @@ __global__ __launch_bounds__(256) void dense_copy_cols(const double *X, int32_t 
 // The status word's memory: the word (padded) and two diagonal blocks.
 constexpr size_t kInfoWords = 32;
 size_t dense_info_bytes() { return (kInfoWords + 2 * kNB * kNB) * sizeof(double); }
+namespace {
+// Panel j's diagonal block there.
+const double *diag_of(const int32_t *dinfo, int32_t j) {
+  return reinterpret_cast<const double *>(dinfo) + kInfoWords + (j / kNB & 1) * kNB * kNB;
+}
+}  // namespace
 
 rh_status dense_cholesky(int32_t n, double *A, int64_t lda, double *B, int64_t ldb, int32_t nrhs, int32_t *dinfo,
                          void *stream, std::string &err) {
@@ -549,22 +559,21 @@ rh_status dense_cholesky(int32_t n, double *A, int64_t lda, double *B, int64_t l
     hipLaunchKernelGGL(chol_panel, dim3((uint32_t)(strips + (tiles + 1) / 2 + (j > 0 ? 1 : 0))), dim3(kThreads), 0, st,
                        M, j, strips, (int32_t)T, (int32_t)tiles, dinfo, diag);
   }
-  const int32_t last = n > 0 ? (n - 1) / kNB * kNB : 0;
-  if (nrhs > kNB && n > 0)  // the last panel has several strips
-    hipLaunchKernelGGL(chol_last_diag, dim3(1), dim3(256), 0, st, M, last, (const int32_t *)dinfo,
-                       (const double *)(diag + (last / kNB & 1) * kNB * kNB));
   DENSE_TRY(hipGetLastError());
   return RH_OK;
 }
 
-rh_status dense_back_solve(int32_t n, const double *L, int64_t ldl, double *B, int64_t ldb, int32_t nrhs,
+rh_status dense_back_solve(int32_t n, double *L, int64_t ldl, double *B, int64_t ldb, int32_t nrhs,
                            double *work, const int32_t *dinfo, void *stream, std::string &err) {
   if (nrhs <= 0 || n <= 0) return RH_OK;
+  static_assert(kNB == 64, "a block of unknowns is a panel");
   hipStream_t st = static_cast<hipStream_t>(stream);
-  for (int32_t j0 = ((n - 1) / 64) * 64; j0 >= 0; j0 -= 64) {
-    const uint32_t groups = (uint32_t)std::max(1, (j0 + 63) / 64);
+  const int32_t last = (n - 1) / kNB * kNB;
+  for (int32_t j0 = last; j0 >= 0; j0 -= kNB) {
+    const uint32_t groups = (uint32_t)std::max(1, (j0 + kNB - 1) / kNB);
+    const double *diag = j0 == last && nrhs > kNB ? diag_of(dinfo, last) : nullptr;
     hipLaunchKernelGGL(chol_back_block, dim3(groups, (uint32_t)nrhs), dim3(256), 0, st, L, ldl, n, B, ldb, work, j0,
-                       dinfo);
+                       dinfo, diag);
   }
   const int64_t total = (int64_t)n * nrhs;
   hipLaunchKernelGGL(dense_copy_cols, dim3((uint32_t)((total + 255) / 256)), dim3(256), 0, st, (const double *)work,

@@ -286,14 +286,15 @@ inline bool newton_stalled(int32_t it, double r, double r_prev) {
 // ---- dense FP64 Cholesky (dense.hip) and the tracking update (track.hip)
 // A = L L^T in place on the lower triangle (column-major), and L Y = B in
 // place for the nrhs columns of B (B may be null); *dinfo = 0, or the first
-// failed column + 1.  dinfo: dense_info_bytes() of device memory.  Enqueued on
-// `stream`.
+// failed column + 1.  dinfo: dense_info_bytes() of device memory.  With more
+// than 64 columns the last 64 x 64 block of L stays there until
+// dense_back_solve.  Enqueued on `stream`.
 size_t dense_info_bytes();
 rh_status dense_cholesky(int32_t n, double *A, int64_t lda, double *B, int64_t ldb, int32_t nrhs, int32_t *dinfo,
                          void *stream, std::string &err);
-// L^T X = Y in place for nrhs columns (nothing if *dinfo != 0); work holds
-// n * nrhs doubles.
-rh_status dense_back_solve(int32_t n, const double *L, int64_t ldl, double *B, int64_t ldb, int32_t nrhs,
+// L^T X = Y in place for the nrhs columns of dense_cholesky (nothing if *dinfo
+// != 0); work holds n * nrhs doubles.
+rh_status dense_back_solve(int32_t n, double *L, int64_t ldl, double *B, int64_t ldb, int32_t nrhs,
                            double *work, const int32_t *dinfo, void *stream, std::string &err);
 // F = lower triangle of A with tau added on the diagonal.
 rh_status dense_shift_copy(int32_t n, const double *A, int64_t lda, double *F, int64_t ldf, double tau, void *stream,

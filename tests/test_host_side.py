@@ -252,11 +252,11 @@ assert hip.fake_waits(0x100) == before + 1
 """)
 
 
-@pytest.mark.parametrize("n,nrhs,launches", [(1, 1, 3), (30, 65, 4), (64, 64, 3), (65, 1, 5)])
+@pytest.mark.parametrize("n,nrhs,launches", [(1, 1, 3), (30, 65, 3), (64, 64, 3), (65, 1, 5)])
 def test_launches_of_a_dense_solve(fake, n, nrhs, launches):
-    """Panels, a block of the solution each, and the solution's way out; the
-    last diagonal block where there are more than 64 right-hand sides.  (From
-    eight enqueued operations on a call takes 40 us longer to return.)"""
+    """Panels, a block of the solution each, and the solution's way out, also
+    with more than 64 right-hand sides.  (From eight enqueued operations on a
+    call takes 40 us longer to return.)"""
     fake(f"""
 A = np.zeros(1)
 rh.rh_cholesky_solve_device(rh.Context(0).h, {n}, A.ctypes.data, {n}, A.ctypes.data, {n}, {nrhs})

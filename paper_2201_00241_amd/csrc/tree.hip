@@ -239,13 +239,18 @@ __device__ __forceinline__ uint64_t active_chunks(const TreeArgs &a, const TreeD
   return active;
 }
 
-// The matrices of sweep `s` (0: L, 1: U, 2: U^T, 3: L^T) in operand order.
+// The matrices of sweep `s` (0: L, 1: U, 2: U^T, 3: L^T) in operand order, from
+// product p0 of its list on.
 template <class T>
-__device__ __forceinline__ const T *sweep_mat(const TreeDesc AS4 &td, int s);
+__device__ __forceinline__ const T *sweep_mat(const TreeDesc AS4 &td, int s, int32_t p0);
 template <>
-__device__ __forceinline__ const double *sweep_mat<double>(const TreeDesc AS4 &td, int s) { return td.m64[s]; }
+__device__ __forceinline__ const double *sweep_mat<double>(const TreeDesc AS4 &td, int s, int32_t p0) {
+  return td.m64[s] + (int64_t)p0 * kTileVals;
+}
 template <>
-__device__ __forceinline__ const float *sweep_mat<float>(const TreeDesc AS4 &td, int s) { return td.m32[s]; }
+__device__ __forceinline__ const float *sweep_mat<float>(const TreeDesc AS4 &td, int s, int32_t p0) {
+  return td.m32[s] + (int64_t)(p0 - td.first32[s & 1]) * kTileVals;
+}
 
 // Sums over N sparse rows of val * x(col), x giving a column's value in the
 // lane's direction.  A row's first 16 entries are loaded one per lane of the
@@ -447,22 +452,22 @@ __device__ __forceinline__ void tile_load(const T *mat, int32_t p, int lane, T (
 #pragma unroll
   for (int s = 0; s < 4; ++s) a[s] = t[s * 64];
 }
-// The first RING matrix tiles of the n products from p0 on.
+// The first RING matrix tiles of n products (mat: their first).
 template <class T, int RING>
-__device__ __forceinline__ void ring_start(const T *mat, int32_t p0, int32_t n, int lane, T (&H)[RING][4]) {
+__device__ __forceinline__ void ring_start(const T *mat, int32_t n, int lane, T (&H)[RING][4]) {
 #pragma unroll
   for (int h = 0; h < RING; ++h)
-    if (h < n) tile_load<T>(mat, p0 + h, lane, H[h]);
+    if (h < n) tile_load<T>(mat, h, lane, H[h]);
 }
 
-// A wave's n products from p0 on (ents: the list, one per lane): sums of
+// A wave's n products (ents: the list, one per lane; mat: their matrix tiles): sums of
 // matrix tiles times input tiles of X (LDS, rows of kD), out(r, acc) per
 // finished output tile; done() once H is free.  H is a ring of the matrix tiles
 // in flight, its first ones loaded.  An output tile may span waves: the later ones leave their
 // sums in `parts` (LDS, a tile per wave), and after a barrier the first adds
 // them in their order.
 template <class T, int RING, class G, class F>
-__device__ __forceinline__ void products(T (&H)[RING][4], int32_t ents, int32_t p0, int32_t n, const T *mat, const T *X,
+__device__ __forceinline__ void products(T (&H)[RING][4], int32_t ents, int32_t n, const T *mat, const T *X,
                                          T *parts, int wave, int lane, G done, F out) {
   const T *Xl = X + (lane >> 4) * kD + (lane & 15);
   UpperTile<T> acc;
@@ -491,7 +496,7 @@ __device__ __forceinline__ void products(T (&H)[RING][4], int32_t ents, int32_t 
         }
         acc.clear();
       }
-      if (p + h + RING < n) tile_load<T>(mat, p0 + p + h + RING, lane, H[h]);
+      if (p + h + RING < n) tile_load<T>(mat, p + h + RING, lane, H[h]);
     }
   }
   done();
@@ -579,7 +584,7 @@ __global__ __launch_bounds__(kLeafWaves * 64, 4) void tree_leaf(const TreeArgs a
     const ChunkOff off = chunk_off(td);
     const int32_t ents = lane < np ? (FWD ? td.fwd : td.bwd)[p0 + lane] : 0;
     double H[kLeafProds][4];
-    ring_start(sweep_mat<double>(td, which == 0 ? (FWD ? 0 : 1) : (FWD ? 2 : 3)), p0, np, lane, H);
+    ring_start(sweep_mat<double>(td, which == 0 ? (FWD ? 0 : 1) : (FWD ? 2 : 3), p0), np, lane, H);
     // where the staged rows are
     uint32_t at[kStage];
     SparseRows<SP ? kStageFwd : 1> gp;
@@ -703,10 +708,10 @@ __global__ __launch_bounds__(kUpperWaves * 64, 4) void tree_upper(const TreeArgs
   const ChunkOff off = chunk_off(td);
   const ChunkBuf m = chunk_buf(a, it, chunk);
   const int32_t ents = lane < np ? (FWD ? td.fwd : td.bwd)[p0 + lane] : 0;
-  const T *mat = sweep_mat<T>(td, which == 0 ? (FWD ? 0 : 1) : (FWD ? 2 : 3));
+  const T *mat = sweep_mat<T>(td, which == 0 ? (FWD ? 0 : 1) : (FWD ? 2 : 3), p0);
   T x[kStage];
   T H[kRing][4];
-  ring_start(mat, p0, np, lane, H);
+  ring_start(mat, np, lane, H);
   Gat g[kStageFwd];
   int32_t row[kStage];
 #pragma unroll
@@ -741,7 +746,7 @@ __global__ __launch_bounds__(kUpperWaves * 64, 4) void tree_upper(const TreeArgs
     if (slot + j * kSlots < rows) X[(slot + j * kSlots) * kD + l16] = x[j];
   lds_barrier();
   const uint32_t own = Io::out(off, which), upd = upd_off<T>(td, off);
-  products(H, ents, p0, np, mat, X, X + a.lds_rows * kD, wave, lane, [] {}, [&](int32_t r, const auto &acc) {
+  products(H, ents, np, mat, X, X + a.lds_rows * kD, wave, lane, [] {}, [&](int32_t r, const auto &acc) {
 #pragma unroll
     for (int q = 0; q < 4; ++q)
       put(m, out_off<T, FWD>(nd, r * kT + UpperTile<T>::row(q, lane >> 4), own, upd, l16), (T)acc[q]);
@@ -772,8 +777,8 @@ __global__ __launch_bounds__(kUpperWaves * 64, 4) void tree_top(const TreeArgs a
   const int32_t nq = nd.bwd_at[wave + 1] - nd.bwd_at[wave], q0 = nd.bwd0 + nd.bwd_at[wave];
   const int32_t ents = lane < np ? td.fwd[p0 + lane] : 0, ents2 = lane < nq ? td.bwd[q0 + lane] : 0;
   T H[kRing][4];
-  const T *mat = sweep_mat<T>(td, which == 0 ? 0 : 2), *mat2 = sweep_mat<T>(td, which == 0 ? 1 : 3);
-  if constexpr (!SP) ring_start(mat, p0, np, lane, H);
+  const T *mat = sweep_mat<T>(td, which == 0 ? 0 : 2, p0), *mat2 = sweep_mat<T>(td, which == 0 ? 1 : 3, q0);
+  if constexpr (!SP) ring_start(mat, np, lane, H);
   const uint32_t src = SweepIo<T, true>::in(off, which), own = SweepIo<T, true>::out(off, which);
   for (int32_t r0 = slot; r0 < mt * kT; r0 += 4 * kSlots) {
     T v[4];
@@ -802,16 +807,16 @@ __global__ __launch_bounds__(kUpperWaves * 64, 4) void tree_top(const TreeArgs a
       X[r * kD + l16] = v[j];
     }
   }
-  if constexpr (SP) ring_start(mat, p0, np, lane, H);  // (the registers are taken before)
+  if constexpr (SP) ring_start(mat, np, lane, H);  // (the registers are taken before)
   lds_barrier();
-  auto second = [&] { ring_start(mat2, q0, nq, lane, H); };
-  products(H, ents, p0, np, mat, X, parts, wave, lane, second, [&](int32_t r, const auto &acc) {
+  auto second = [&] { ring_start(mat2, nq, lane, H); };
+  products(H, ents, np, mat, X, parts, wave, lane, second, [&](int32_t r, const auto &acc) {
 #pragma unroll
     for (int q = 0; q < 4; ++q) X2[(r * kT + UpperTile<T>::row(q, lane >> 4)) * kD + l16] = (T)acc[q];
   });
   lds_barrier();
   if (a.stamps && chunk == 0 && tid == 0) a.stamps[which == 0 ? 2 : 5] = wall_clock64();
-  products(H, ents2, q0, nq, mat2, X2, parts, wave, lane, [] {}, [&](int32_t r, const auto &acc) {
+  products(H, ents2, nq, mat2, X2, parts, wave, lane, [] {}, [&](int32_t r, const auto &acc) {
 #pragma unroll
     for (int q = 0; q < 4; ++q)
       put(m, out_off<T, false>(nd, r * kT + UpperTile<T>::row(q, lane >> 4), own, 0, l16), (T)acc[q]);
@@ -1132,11 +1137,13 @@ __device__ __forceinline__ Pair pair_add(Pair a, Pair b) {
 // FMA, two-sums) and rounded at the end, so that the matrix is as good as one
 // formed in extended precision.  Rows of y live in LDS.  Both operand orders
 // are written (M for the forward sweep, M^T for the backward one), in FP64
-// and FP32.  A row is a chain of LDS reads, so the next row's entries are
+// and from node node32 (above the leaves) on in FP32, whose lists start at
+// products first32.x and first32.y.  A row is a chain of LDS reads, so the next row's entries are
 // loaded meanwhile.
 __global__ __launch_bounds__(64) void tree_invert(const TreeNode *nodes, const int2 *cols, const int32_t *ent_ptr,
                                                   const uint16_t *col, const double *vl, const double *vu,
-                                                  const int2 *map, const double *f, const int32_t *dpos, double *fl, double *fu, double *bl, double *bu,
+                                                  const int2 *map, const double *f, const int32_t *dpos, double *fl,
+                                                  double *fu, double *bl, double *bu, int32_t node32, int2 first32,
                                                   float *fl32, float *fu32, float *bl32, float *bu32) {
   extern __shared__ __align__(16) char lds_raw[];
   const int2 w = cols[blockIdx.x];
@@ -1219,9 +1226,11 @@ __global__ __launch_bounds__(64) void tree_invert(const TreeNode *nodes, const i
       }
       const int64_t at_f = (int64_t)t.x * kTileVals + s * 64 + lane, b = (int64_t)t.y * kTileVals + s * 64 + lane;
       fo[at_f] = x;
-      fo32[at_f] = (float)x;
       bo[b] = y;
-      bo32[b] = (float)y;
+      if (w.x >= node32) {
+        fo32[at_f - (int64_t)first32.x * kTileVals] = (float)x;
+        bo32[b - (int64_t)first32.y * kTileVals] = (float)y;
+      }
     }
   }
 }
@@ -1248,7 +1257,7 @@ struct DevTree {
   const uint16_t *col = nullptr;
   const int2 *cols = nullptr, *map = nullptr;
   const int32_t *an_src = nullptr, *at_src = nullptr;
-  int32_t n_ents = 0, n_cols = 0, nnz_gx = 0;
+  int32_t n_ents = 0, n_cols = 0, nnz_gx = 0, node32 = 0;
   size_t n_flat = 0;
   std::vector<int32_t> row_ptr, bus_order, gp_src, gpt_src;
 };
@@ -1380,11 +1389,15 @@ rh_status tree_build(Network &net, DevTree &t, std::string &err) {
   T_TRY(t_alloc(t, p.col.size(), &t.vl, err));
   T_TRY(t_alloc(t, p.col.size(), &t.vu, err));
   const size_t p_fwd = p.fwd.size(), p_bwd = p.bwd.size();
+  t.node32 = d.n_tiers > 1 ? p.tier[1] : 0;  // (the leaves are FP64 in both modes)
+  d.first32[0] = p.nodes[t.node32].fwd0;
+  d.first32[1] = p.nodes[t.node32].bwd0;
   for (int q = 0; q < 4; ++q) {
     double *m = nullptr;
     float *m32 = nullptr;
-    T_TRY(t_alloc(t, (q == 0 || q == 2 ? p_fwd : p_bwd) * kTileVals, &m, err));
-    T_TRY(t_alloc(t, (q == 0 || q == 2 ? p_fwd : p_bwd) * kTileVals, &m32, err));
+    const size_t products = q & 1 ? p_bwd : p_fwd;
+    T_TRY(t_alloc(t, products * kTileVals, &m, err));
+    T_TRY(t_alloc(t, (products - d.first32[q & 1]) * kTileVals, &m32, err));
     d.m64[q] = m;
     d.m32[q] = m32;
   }
@@ -1457,7 +1470,7 @@ rh_status tree_build(Network &net, DevTree &t, std::string &err) {
       reinterpret_cast<const void *>(&tree_leaf<double, true, true>),
       reinterpret_cast<const void *>(&tree_upper<double, true, true>),
       reinterpret_cast<const void *>(&tree_top<double, true>),
-reinterpret_cast<const void *>(&tree_invert),
+      reinterpret_cast<const void *>(&tree_invert),
   };
   for (const void *k : kernels) T_TRY(lds_bound(k, kTreeLds, err));
   return RH_OK;
@@ -1492,8 +1505,8 @@ rh_status tree_refresh(Network &net, DevTree &t, const double *d_factors, std::s
   if (t.n_cols)
     hipLaunchKernelGGL(tree_invert, dim3(t.n_cols, 2), dim3(64), (size_t)p.max_rows * kD * 2 * sizeof(double), nullptr,
                        d.nodes, t.cols, t.ent_ptr, t.col, (const double *)t.vl, (const double *)t.vu, t.map, f,
-                       t.dpos, m[0], m[2],
-                       m[3], m[1], m32[0], m32[2], m32[3], m32[1]);
+                       t.dpos, m[0], m[2], m[3], m[1], t.node32, make_int2(d.first32[0], d.first32[1]), m32[0], m32[2],
+                       m32[3], m32[1]);
   HIP_TRY(hipGetLastError());
   // G_x, and its norms
   HIP_TRY(hipMemcpy(t.gxv, net.gx.val.data(), (size_t)t.nnz_gx * sizeof(double), hipMemcpyHostToDevice));

@@ -37,7 +37,8 @@ struct TreeDesc {
   const int32_t *border, *gat_more, *fwd, *bwd;
   const int4 *gat;
   const double *m64[4];  // the nodes' matrices for the sweeps L, U, U^T, L^T
-  const float *m32[4];
+  const float *m32[4];    // (above the leaves, from product first32 of the lists on)
+  int32_t first32[2];     // forward, backward
   const int4 *gp_rows;  // {row, first entry, end, 0} of the rows with entries, ascending
   const int32_t *gp_ptr, *gp_col;  // (all rows' pointers)
   const double *gp_val;

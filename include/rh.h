@@ -313,7 +313,8 @@ rh_status rh_refinement_report(const rh_network *net, int32_t n, double *berr_z,
 /* Device memory of a network, for admission control by callers that keep
  * several networks resident: `resident` = bytes the network holds now (LU
  * factors and sweep schedules in both precisions, branch coefficients, G_p,
- * G_x, descriptors, and its own launch scratch), `scratch_per_direction` =
+ * G_x, descriptors, its own launch scratch and, once it was solved on the
+ * device, the arrays and fronts of that solve), `scratch_per_direction` =
  * launch scratch one direction of this network may take in precision `prec`
  * (a launch holds it for each direction it runs at once, up to the
  * workgroups it keeps resident).  A launch may take a request's directions in

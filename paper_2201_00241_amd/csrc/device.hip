@@ -3300,7 +3300,8 @@ rh_status device_refinement_report(Network &net, int32_t n, std::vector<double> 
 int64_t device_network_bytes(const Network &net) {
   const DeviceNet *dn = net.dev;
   if (!dn) return 0;
-  return dn->bytes + tree_bytes(net.dtree) + dn->rinfo_cols * 4 * (int64_t)sizeof(double) + (int64_t)dn->run.scratch_bytes;
+  return dn->bytes + tree_bytes(net.dtree) + device_newton_bytes(net) + dn->rinfo_cols * 4 * (int64_t)sizeof(double) +
+         (int64_t)dn->run.scratch_bytes;
 }
 
 int64_t device_scratch_per_direction(const Network &net, rh_precision prec) {

@@ -24,6 +24,7 @@ struct FrontIo {
 // maps: the factors' flat layout and the entries of G_x in it.
 rh_status fronts_build(const LuPlan &lu, const LuMaps &maps, DevFronts **out, std::string &err);
 void fronts_free(DevFronts *f);
+int64_t fronts_bytes(const DevFronts *f);  // of device memory (null: 0)
 // All on the null stream: P G_x P^T = L U and L y = P g in the fronts;
 // x -= G_x^{-1} g, from them; the factors out of the fronts into io.lu.
 rh_status fronts_refactor(const DevFronts &f, const FrontIo &io, std::string &err);

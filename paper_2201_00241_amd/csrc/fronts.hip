@@ -466,6 +466,7 @@ __global__ __launch_bounds__(256) void front_out(const double *fronts, const int
 
 struct DevFronts {
   std::vector<void *> allocs;
+  int64_t bytes = 0;
   double *fronts = nullptr;
   int64_t leaf_values = 0, values = 0;
   const FrontNode *nodes = nullptr;
@@ -483,12 +484,19 @@ struct DevFronts {
 
 namespace {
 
+rh_status f_alloc(DevFronts &f, size_t n, void **out, std::string &err) {
+  const rh_status s = device_try_alloc(out, n, err);
+  if (s != RH_OK) return s;
+  f.allocs.push_back(*out);
+  f.bytes += (int64_t)n;
+  return RH_OK;
+}
+
 template <class T>
 rh_status f_up(DevFronts &f, const std::vector<T> &v, const T **out, std::string &err) {
   void *p = nullptr;
-  const rh_status s = device_try_alloc(&p, std::max<size_t>(sizeof(T), v.size() * sizeof(T)), err);
+  const rh_status s = f_alloc(f, std::max<size_t>(sizeof(T), v.size() * sizeof(T)), &p, err);
   if (s != RH_OK) return s;
-  f.allocs.push_back(p);
   if (!v.empty()) HIP_TRY(hipMemcpy(p, v.data(), v.size() * sizeof(T), hipMemcpyHostToDevice));
   *out = static_cast<const T *>(p);
   return RH_OK;
@@ -655,11 +663,9 @@ rh_status fill(DevFronts &f, const LuPlan &lu, const LuMaps &mp, const TreePlan 
       (s = f_up(f, mp.a_src, &f.row_src, err)) != RH_OK)
     return s;
   void *m = nullptr;
-  if ((s = device_try_alloc(&m, std::max<size_t>(1, (size_t)f.values) * sizeof(double), err)) != RH_OK) return s;
-  f.allocs.push_back(m);
+  if ((s = f_alloc(f, std::max<size_t>(1, (size_t)f.values) * sizeof(double), &m, err)) != RH_OK) return s;
   f.fronts = static_cast<double *>(m);
-  if ((s = device_try_alloc(&m, std::max<size_t>(1, n) * sizeof(double), err)) != RH_OK) return s;
-  f.allocs.push_back(m);
+  if ((s = f_alloc(f, std::max<size_t>(1, n) * sizeof(double), &m, err)) != RH_OK) return s;
   f.xt = static_cast<double *>(m);
   for (const void *kernel : {reinterpret_cast<const void *>(&front_factor<kLeafWaves, true>),
                              reinterpret_cast<const void *>(&front_factor<kUpperWaves, false>)})
@@ -692,6 +698,8 @@ void fronts_free(DevFronts *f) {
   for (void *p : f->allocs) (void)hipFree(p);
   delete f;
 }
+
+int64_t fronts_bytes(const DevFronts *f) { return f ? f->bytes : 0; }
 
 rh_status fronts_refactor(const DevFronts &f, const FrontIo &io, std::string &err) {
   const int32_t tiers = (int32_t)f.tier.size() - 1;

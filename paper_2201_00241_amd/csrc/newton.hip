@@ -674,6 +674,7 @@ struct DevNewton {
   DevFronts *fronts = nullptr;  // null: row by row
   bool current = false;  // w.lu holds the factors of the network's accepted state
   std::vector<void *> allocs;
+  int64_t bytes = 0;  // of allocs
   NtArgs args{};
   size_t lds_bytes = 0;
   std::vector<int32_t> row_ptr;  // host copy (unpacking the factors)
@@ -700,8 +701,10 @@ namespace {
 template <class T>
 rh_status nt_up(DevNewton &d, const std::vector<T> &v, const T **out, std::string &err) {
   void *p = nullptr;
-  HIP_TRY(hipMalloc(&p, std::max<size_t>(sizeof(T), v.size() * sizeof(T))));
+  const size_t nb = std::max<size_t>(sizeof(T), v.size() * sizeof(T));
+  HIP_TRY(hipMalloc(&p, nb));
   d.allocs.push_back(p);
+  d.bytes += (int64_t)nb;
   if (!v.empty()) HIP_TRY(hipMemcpy(p, v.data(), v.size() * sizeof(T), hipMemcpyHostToDevice));
   *out = static_cast<const T *>(p);
   return RH_OK;
@@ -709,8 +712,10 @@ rh_status nt_up(DevNewton &d, const std::vector<T> &v, const T **out, std::strin
 
 rh_status nt_alloc(DevNewton &d, size_t n, double **out, std::string &err) {
   void *p = nullptr;
-  HIP_TRY(hipMalloc(&p, std::max<size_t>(8, n * sizeof(double))));
+  const size_t nb = std::max<size_t>(8, n * sizeof(double));
+  HIP_TRY(hipMalloc(&p, nb));
   d.allocs.push_back(p);
+  d.bytes += (int64_t)nb;
   *out = static_cast<double *>(p);
   return RH_OK;
 }
@@ -1030,6 +1035,10 @@ rh_status device_newton(Network &net, double tol, int32_t max_iter, NewtonResult
   }
   d.current = true;
   return RH_OK;
+}
+
+int64_t device_newton_bytes(const Network &net) {
+  return net.dnewton ? net.dnewton->bytes + fronts_bytes(net.dnewton->fronts) : 0;
 }
 
 const double *device_newton_factors(const Network &net) {

@@ -272,6 +272,7 @@ struct NewtonResult {
 };
 rh_status device_newton(Network &net, double tol, int32_t max_iter, NewtonResult &res, std::string &err);
 void device_newton_free(Network &net);
+int64_t device_newton_bytes(const Network &net);  // device memory of its arrays and fronts
 // The flat factors of the accepted state on the device (row by row, L part
 // then U part), or null if the last solve was the host's.
 const double *device_newton_factors(const Network &net);

@@ -272,3 +272,18 @@ net = rh.Network(rh.Context(0), geo(8600))
 net.solve()
 assert net.device_bytes()[0] < 52e6, net.device_bytes()
 """)
+
+
+@pytest.mark.parametrize("n_bus", [60, 1000, 8600])
+def test_resident_bytes_are_all_that_is_held(fake, n_bus):
+    """Also the device solve's fronts, the largest part at 1,000 buses."""
+    fake(f"""
+net = rh.Network(rh.Context(0), geo({n_bus}))
+before = hip.fake_live()
+net.solve()
+assert net.device_bytes()[0] == hip.fake_live() - before
+net.solve_device()
+assert net.device_bytes()[0] == hip.fake_live() - before
+net.solve()
+assert net.device_bytes()[0] == hip.fake_live() - before
+""")

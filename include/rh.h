@@ -234,7 +234,8 @@ rh_status rh_hvp_device_noalloc(rh_network *net, int32_t k, const void *dW, int6
  * network's sweeps are re-planned and uploaded for each, so device data of
  * the network moves and recorded batches of it must be re-created), every
  * directions-per-workgroup count whose vectors fit, and launch sizes of 128,
- * 256, 512 and 1,024 directions (and n_p when smaller); one launch of
+ * 256, 512 and 1,024 directions (and n_p when smaller); from 16,000 states on
+ * the launch size alone, up to 4,096 directions; one launch of
  * identity columns is timed per candidate (the best of two after one
  * untimed) and the full Hessian estimated as that time x the launches it
  * needs.  The fastest shape is applied, reported in rh_report.tile, and

@@ -287,3 +287,29 @@ assert net.device_bytes()[0] == hip.fake_live() - before
 net.solve()
 assert net.device_bytes()[0] == hip.fake_live() - before
 """)
+
+
+def test_the_tuner_tries_a_whole_call_of_the_tree_path(fake, tmp_path):
+    """A full Hessian with k_block = 0 must not be slower than with any other:
+    calls of up to 4,096 directions are among the candidates, and a shape
+    cached before they were is not taken."""
+    fake(f"""
+os.environ["RH_TUNE_CACHE"] = "{tmp_path}/tiles.txt"
+""" + """
+net = rh.Network(rh.Context(0), geo(12000))
+net.solve()
+hip.fake_peak_reset()
+before = hip.fake_live()
+t = net.autotune()
+assert t["source"] == 1
+assert hip.fake_peak() - before >= net.n_p * net.n_p * 8, (net.n_p, hip.fake_peak() - before)
+path = os.environ["RH_TUNE_CACHE"]
+line = open(path).read().split()
+key = next(i for i, w in enumerate(line) if "-tree" in w)
+old = line[:key] + ["fp64-tree", "128"] + line[key + 2:]
+open(path, "w").write(" ".join(old) + "\\n")
+net = rh.Network(rh.Context(0), geo(12000))
+net.solve()
+assert net.autotune()["source"] == 1
+assert net.autotune()["source"] == 2
+""")

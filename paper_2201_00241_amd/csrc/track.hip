@@ -98,12 +98,13 @@ rh_status dense_spd_solve(int device, int32_t n, double *A, int64_t lda, double 
   TR_TRY(hipSetDevice(device));
   hipStream_t st = static_cast<hipStream_t>(stream);
   // one allocation: the status word's memory and the solution
-  char *work = nullptr;
+  void *p = nullptr;
   const size_t head = dense_info_bytes();
-  if (hipMalloc(&work, head + (size_t)n * std::max(1, nrhs) * sizeof(double)) != hipSuccess) {
-    err = "dense solve workspace: out of memory";
+  if (device_try_alloc(&p, head + (size_t)n * std::max(1, nrhs) * sizeof(double), err) != RH_OK) {
+    err = "dense solve workspace: " + err;
     return RH_ENOMEM;
   }
+  char *work = static_cast<char *>(p);
   int32_t *info = reinterpret_cast<int32_t *>(work);
   rh_status s = dense_cholesky(n, A, lda, B, ldb, nrhs, info, stream, err);
   if (s == RH_OK) s = dense_back_solve(n, A, lda, B, ldb, nrhs, reinterpret_cast<double *>(work + head), info, stream, err);

@@ -313,3 +313,19 @@ net.solve()
 assert net.autotune()["source"] == 1
 assert net.autotune()["source"] == 2
 """)
+
+
+def test_a_dense_solve_names_the_error_of_its_workspace(fake):
+    fake("""
+A = np.zeros(1)
+ctx = rh.Context(0)
+for call, says in ((b"memory", "out of memory"), (b"hipMalloc", "refused")):
+    hip.fake_refuse(call, 0)
+    try:
+        rh.rh_cholesky_solve_device(ctx.h, 9, A.ctypes.data, 9, A.ctypes.data, 9, 1)
+        assert False, "the refused call went unnoticed"
+    except rh.RhError as e:
+        assert e.status == rh.RH_ENOMEM and says in str(e), e
+# and none is left for the next call to find
+rh.rh_cholesky_solve_device(ctx.h, 9, A.ctypes.data, 9, A.ctypes.data, 9, 1)
+""")

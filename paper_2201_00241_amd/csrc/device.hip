@@ -1501,9 +1501,18 @@ namespace {
     }                                                                          \
   } while (0)
 
+struct DeviceInfo {
+  int device = -1;
+  int cus = 0;
+  size_t lds_max = 0;  // dynamic LDS a workgroup may use
+  double wall_khz = 0.0;
+};
+
 // A stream beside the caller's, for batches with networks of both paths, and the
 // events that order it.
 struct Side {
+  int device = -1;
+  bool taken = false;
   hipStream_t s = nullptr;
   hipEvent_t fork = nullptr, join = nullptr;
   ~Side() {
@@ -1513,20 +1522,60 @@ struct Side {
   }
 };
 
-struct DeviceInfo {
-  int device = -1;
-  int cus = 0;
-  size_t lds_max = 0;  // dynamic LDS a workgroup may use
-  double wall_khz = 0.0;
-};
-
-rh_status side_create(std::unique_ptr<Side> &out, std::string &err) {
+rh_status side_create(int device, std::unique_ptr<Side> &out, std::string &err) {
   std::unique_ptr<Side> d(new Side());
+  d->device = device;
   HIP_TRY(hipStreamCreateWithFlags(&d->s, hipStreamNonBlocking));
   HIP_TRY(hipEventCreateWithFlags(&d->fork, hipEventDisableTiming));
   HIP_TRY(hipEventCreateWithFlags(&d->join, hipEventDisableTiming));
   out = std::move(d);
   return RH_OK;
+}
+
+// The process' side streams.  Creating one takes 3 ms at first and 0.1 later,
+// more than what the first batch of a context gains by it, and every stream
+// more shares a hardware queue with others: contexts take turns.  A call holds
+// one while it enqueues; one that still runs an earlier call's launches is
+// left to them unless kMostSides do.  They last as long as the process.
+constexpr int kMostSides = 4;
+std::mutex g_side_mu;
+std::vector<Side *> &sides() {
+  static auto *v = new std::vector<Side *>();
+  return *v;
+}
+
+rh_status side_take(int device, hipStream_t caller, Side *&out, std::string &err) {
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(caller, &cap) != hipSuccess) (void)hipGetLastError();
+  std::lock_guard<std::mutex> lk(g_side_mu);
+  Side *idle = nullptr, *busy = nullptr;
+  int n = 0;
+  for (Side *d : sides()) {
+    if (d->device != device) continue;
+    ++n;
+    if (d->taken) continue;
+    // (an event must not be queried while the caller captures)
+    if (cap == hipStreamCaptureStatusNone && hipEventQuery(d->join) == hipErrorNotReady)
+      busy = busy ? busy : d;
+    else
+      idle = idle ? idle : d;
+  }
+  (void)hipGetLastError();  // (the queries')
+  out = idle ? idle : n >= kMostSides ? busy : nullptr;
+  if (!out) {
+    std::unique_ptr<Side> made;
+    const rh_status s = side_create(device, made, err);
+    if (s != RH_OK) return s;
+    sides().push_back(made.get());
+    out = made.release();
+  }
+  out->taken = true;
+  return RH_OK;
+}
+
+void side_give(Side *d) {
+  std::lock_guard<std::mutex> lk(g_side_mu);
+  d->taken = false;
 }
 
 // Launch resources: per-workgroup scratch, timing events, phase stamps and the
@@ -1545,7 +1594,6 @@ struct Runner {
   TreeItem *titems_dev = nullptr, *titems_host = nullptr;  // the tree path's work list
   int32_t titems_cap = 0;
   hipEvent_t titems_done = nullptr;
-  Side *side = nullptr;
   int32_t launches = 0, last_c = 0;
   long long *step_stamps = nullptr;  // debug (RH_STEP_STAMPS)
   bool step_stamps_pending = false;
@@ -1577,7 +1625,6 @@ void runner_free(Runner &r) {
   if (r.titems_dev) (void)hipFree(r.titems_dev);
   if (r.titems_host) (void)hipHostFree(r.titems_host);
   if (r.titems_done) (void)hipEventDestroy(r.titems_done);
-  delete r.side;
   if (r.step_stamps) (void)hipFree(r.step_stamps);
   r = Runner();
 }
@@ -3022,12 +3069,6 @@ rh_status device_hvp_batch(Context &ctx, int32_t n, Network *const *nets, const 
   // path; a refined batch that takes 1146 us there 1164 and 928).  Their
   // scratch is one allocation, of two parts.
   Runner &r = ctx.dev->on(stream);
-  if (!r.side) {
-    std::unique_ptr<Side> made;
-    const rh_status ms = side_create(made, err);
-    if (ms != RH_OK) return ms;
-    r.side = made.release();
-  }
   LaunchPlan pl;
   const rh_status ps = plan_launch(ctx.dev->info, refine, items, max_nx, pl, err);
   if (ps != RH_OK) return ps;
@@ -3037,19 +3078,23 @@ rh_status device_hvp_batch(Context &ctx, int32_t n, Network *const *nets, const 
       fit_tree_work(req, refine, work, [&](size_t b) { return grow_scratch(r, gs_bytes + b, s, err); });
   if (ws != RH_OK) return ws;
   const FixedScratch gs{r.scratch, (int64_t)gs_bytes, false};
-  HIP_TRY(hipEventRecord(r.side->fork, s));
-  HIP_TRY(hipStreamWaitEvent(r.side->s, r.side->fork, 0));
+  Side *side = nullptr;
+  const rh_status sts = side_take(ctx.device, s, side, err);
+  if (sts != RH_OK) return sts;
+  const std::unique_ptr<Side, void (*)(Side *)> held(side, side_give);
+  HIP_TRY(hipEventRecord(side->fork, s));
+  HIP_TRY(hipStreamWaitEvent(side->s, side->fork, 0));
   // whatever comes of them, the caller's stream waits for what is under way
   auto join = [&](std::string &e) {
-    hipError_t h = hipEventRecord(r.side->join, r.side->s);
-    if (h == hipSuccess) h = hipStreamWaitEvent(s, r.side->join, 0);
+    hipError_t h = hipEventRecord(side->join, side->s);
+    if (h == hipSuccess) h = hipStreamWaitEvent(s, side->join, 0);
     if (h != hipSuccess) e = std::string("joining the side stream: ") + hipGetErrorString(h);
     return h == hipSuccess ? RH_OK : RH_EDEVICE;
   };
   rh_status st;
   try {
     // (phase stamps are those of one kind of launch: the other's)
-    st = run_items(ctx.dev->info, r, ctx.timing, refine, ctx.refine_tol, items, max_nx, r.side->s, err, &gs);
+    st = run_items(ctx.dev->info, r, ctx.timing, refine, ctx.refine_tol, items, max_nx, side->s, err, &gs);
     if (st == RH_OK)
       st = run_tree_at(r, std::min(ctx.timing, 1), refine, ctx.refine_tol, req, work, r.scratch + gs_bytes / sizeof(double),
                        s, err);
@@ -3177,7 +3222,7 @@ rh_status batch_build(DeviceBatch &b, const DeviceInfo &info, int32_t refine, do
   std::unique_ptr<Side> side;
   const bool both = work.chunks > 0 && pl.n_chunks > 0;
   if (both) {
-    const rh_status ms = side_create(side, err);
+    const rh_status ms = side_create(b.device, side, err);
     if (ms != RH_OK) return ms;
   }
   HIP_TRY(hipStreamCreateWithFlags(&b.cap, hipStreamNonBlocking));

@@ -19,6 +19,7 @@ namespace {
 std::recursive_mutex mu;
 std::map<void *, size_t> live;
 size_t live_bytes = 0, peak_bytes = 0;
+bool busy = false;
 int64_t n_allocs = 0, n_launches = 0, n_streams = 0, max_bytes = -1, max_one = -1;
 std::map<const void *, size_t> bound;
 std::map<void *, int64_t> waits;
@@ -73,6 +74,7 @@ void fake_peak_reset() { peak_bytes = live_bytes; }
 int64_t fake_allocs() { return n_allocs; }
 int64_t fake_launches() { return n_launches; }
 int64_t fake_streams() { return n_streams; }
+void fake_busy(int all) { busy = all != 0; }  // whether work on a stream is under way
 int64_t fake_waits(void *stream) { return waits[stream]; }
 
 // ---- the runtime
@@ -166,6 +168,8 @@ hipError_t hipEventCreateWithFlags(hipEvent_t *e, unsigned) { return hipEventCre
 hipError_t hipEventDestroy(hipEvent_t e) { return std::free((void *)e), hipSuccess; }
 hipError_t hipEventRecord(hipEvent_t, hipStream_t) { return hipSuccess; }
 hipError_t hipEventSynchronize(hipEvent_t) { return hipSuccess; }
+hipError_t hipEventQuery(hipEvent_t) { return busy ? done(hipErrorNotReady) : hipSuccess; }
+hipError_t hipStreamIsCapturing(hipStream_t, hipStreamCaptureStatus *s) { return *s = hipStreamCaptureStatusNone, hipSuccess; }
 hipError_t hipEventElapsedTime(float *ms, hipEvent_t, hipEvent_t) { return *ms = 1.0f, hipSuccess; }
 
 }  // extern "C"

@@ -220,18 +220,38 @@ def batch(stream, prec=rh.RH_FP64):
 
 
 def test_the_first_batch_of_both_paths_sets_up_little(fake):
-    """Its scratch is one allocation, as that of other batches, and it has one
-    side stream for each of the caller's."""
+    """Its scratch is one allocation, as that of other batches."""
     fake(MIXED + """
-streams, allocs = hip.fake_streams(), hip.fake_allocs()
+allocs = hip.fake_allocs()
 batch(0x100)
-assert hip.fake_streams() == streams + 1
 assert hip.fake_allocs() == allocs + 3  # the scratch and the two work lists
 batch(0x100)
-batch(0x100, rh.RH_FP32_REFINED)
+assert hip.fake_allocs() == allocs + 3
+""")
+
+
+def test_contexts_take_turns_with_the_side_streams(fake):
+    """A stream takes from a tenth of a millisecond to several to create: a new
+    context's batches use one that is there, calls under way on other streams
+    keep theirs, and there are never more than four."""
+    fake(MIXED + """
+streams = hip.fake_streams()
+batch(0x100)
+batch(0x200, rh.RH_FP32_REFINED)
 assert hip.fake_streams() == streams + 1
-batch(0x200)
-assert hip.fake_streams() == streams + 2
+ctx = rh.Context(0)
+nets = [rh.Network(ctx, g) for g in (geo(60), geo(8600), geo(100), geo(8700, 2))]
+for net in nets:
+    net.solve()
+batch(0x100)
+assert hip.fake_streams() == streams + 1
+hip.fake_busy(1)
+for n in (2, 3, 4, 4, 4):
+    batch(0x100)
+    assert hip.fake_streams() == streams + n
+hip.fake_busy(0)
+batch(0x300)
+assert hip.fake_streams() == streams + 4
 """)
 
 

@@ -1,16 +1,16 @@
 """Benchmark: reduced-Hessian HVPs per second on the 10k-bus synthetic grid.
 
 One step = the full dense reduced Hessian (n_p = 2,799 directions) computed
-through the C ABI in k = 256 direction blocks, one kernel launch per block,
+through the C ABI in k = 256 direction blocks, which share a call's launches,
 with every input already resident on the GPU.  The timed region brackets
 exactly `--steps` steps with device synchronisations.  Prints one JSON line.
 
-Roofline: the block kernel is the only kernel of a step.  Its algorithmic HBM
-bytes per launch are (10 n_x + 5 n_p) * 8 per direction (every intermediate
-written and read once, W read twice, H written) plus the factor entries of
-the four triangular sweeps (12 bytes each), the per-incidence coefficients and
-G_p; achieved GB/s = those bytes / the average launch duration from HIP events
-recorded on the launch stream.  Peak: 8 TB/s (MI355X HBM3E).
+Roofline: a step is one call, a sequence of kernels (the tree path).  Its
+algorithmic HBM bytes are (10 n_x + 5 n_p) * 8 per direction (every
+intermediate written and read once, W read twice, H written) plus the factor
+entries of the four triangular sweeps (12 bytes each), the per-incidence
+coefficients and G_p; achieved GB/s = those bytes / the average call's duration
+from HIP events recorded on the launch stream.  Peak: 8 TB/s (MI355X HBM3E).
 
 The CPU baseline runs the FP64 oracle (SuperLU solves and sparse products)
 on the same grid: the whole Hessian split over every host core, one process
@@ -30,35 +30,36 @@ sys.path.insert(0, str(ROOT))
 import numpy as np  # noqa: E402
 
 PEAK_HBM_GBS = 8000.0
-TRAFFIC_FILE = ROOT / "profiles" / "block_kernel_10k_hbm_traffic.txt"
+# per path the measured memory traffic and the sources it depends on: the
+# kernels, the planner that lays out what they read, and their shared headers
+TRAFFIC = {
+    "block_kernel": ("block_kernel_10k_hbm_traffic.txt", ("device.hip", "rh_internal.h", "sparse_lu.cpp")),
+    "tree path": ("tree_path_hbm_traffic.txt", ("tree.hip", "tree.cpp", "tree.h", "tree_device.h", "sparse_lu.cpp")),
+}
 
 
-# the sources the block kernel's memory traffic depends on: the kernel, the
-# planner that lays out its records, and their shared header
-TRAFFIC_SOURCES = ("device.hip", "rh_internal.h", "sparse_lu.cpp")
-
-
-def sources_digest():
-    """SHA-256 over the block kernel's sources (TRAFFIC_SOURCES), in name order."""
+def sources_digest(kernel):
+    """SHA-256 over a path's sources (TRAFFIC), in name order."""
     h = hashlib.sha256()
-    for name in sorted(TRAFFIC_SOURCES):
+    for name in sorted(TRAFFIC[kernel][1]):
         f = ROOT / "paper_2201_00241_amd" / "csrc" / name
         h.update(f.name.encode())
         h.update(f.read_bytes())
     return h.hexdigest()
 
 
-def measured_traffic():
-    """HBM bytes per launch of the block kernel from the committed counter
-    summary, or None if the kernel sources changed since it was measured."""
-    if not TRAFFIC_FILE.exists():
+def measured_traffic(kernel):
+    """HBM bytes per launch of the headline's path from the committed counter
+    summary, or None if its sources changed since it was measured."""
+    f = ROOT / "profiles" / TRAFFIC[kernel][0]
+    if not f.exists():
         return None
     kv = {}
-    for line in TRAFFIC_FILE.read_text().splitlines():
+    for line in f.read_text().splitlines():
         if ":" in line and not line.startswith(("#", " ", "|")):
             key, val = line.split(":", 1)
             kv[key.strip()] = val.strip()
-    if kv.get("sources_sha256") != sources_digest():
+    if kv.get("sources_sha256") != sources_digest(kernel):
         return None
     try:
         return float(kv["traffic_bytes_per_launch"])
@@ -357,7 +358,7 @@ def run_batch(instances, steps, warmup, config="c3"):
         rep = ctx.report()
         ctx.set_timing(0)
         out[name] = {"value": len(nets) * k / (ms / 1e3), "unit": "HVP/s", "ms_per_step": ms,
-                     "launch": "graph replay (rh_batch_launch), one kernel per step",
+                     "launch": "graph replay (rh_batch_launch)",
                      "dirs_per_group": info["dirs_per_group"], "workgroups": info["workgroups"],
                      "eager_kernel_ms": rep["last_kernel_ms"], "eager_wall_ms": eager_wall_ms}
         if HW64 is None:
@@ -661,7 +662,8 @@ def main():
     dirs = -(-n_p // max(1, launches // args.steps))
     bytes_launch = mean_bytes_per_launch(rep, g, n_p, dirs)
     achieved = bytes_launch / (avg_launch_ms / 1e3) / 1e9
-    traffic = measured_traffic()
+    kernel = "tree path" if rep["dirs_per_group"] == 16 else "block_kernel"
+    traffic = measured_traffic(kernel)
     phase_names = ["spmul", "L", "U", "projection", "Ut", "Lt", "spmuladd"]
     out = {
         "metric": "reduced-Hessian HVPs/sec at 10k buses (k=256) vs plain; p50/p99 latency",
@@ -698,7 +700,7 @@ def main():
             "bound": "hbm", "achieved": achieved, "peak": PEAK_HBM_GBS, "unit": "GB/s",
             "frac": achieved / PEAK_HBM_GBS, "traffic": traffic,
             "traffic_unit": "HBM bytes per launch (rocprofv3 FETCH_SIZE + WRITE_SIZE, copy-scaled)",
-            "kernel": "tree path" if rep["dirs_per_group"] == 16 else "block_kernel", "avg_launch_ms": avg_launch_ms,
+            "kernel": kernel, "avg_launch_ms": avg_launch_ms,
             "algorithmic_bytes_per_launch": bytes_launch,
         },
         "setup_s": setup_s,

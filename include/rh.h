@@ -103,7 +103,9 @@ typedef struct {
   int64_t nnz_gx, nnz_l, nnz_u; /* G_x and its LU factors (unit diagonal of L not stored) */
   int32_t levels_l, levels_u;   /* dependency depth of the L and U sweeps */
   int32_t steps_l, steps_u;     /* barrier-separated steps of the device sweeps
-                                   (narrow levels merged into dense-inverse blocks) */
+                                   (narrow levels merged into dense-inverse blocks);
+                                   from 16,000 states on the tiers of the elimination
+                                   tree, a launch each */
   int32_t newton_iters;
   double newton_resid;          /* ||g||_inf at the accepted state */
   int32_t last_k;               /* directions in the last product call */

@@ -2804,7 +2804,16 @@ rh_status upload_groups(Network &net, DeviceNet *dn, const std::function<rh_stat
 // (256 directions are one workgroup per CU, the other path's best case; 257
 // take it twice as long.)  The choice cannot depend on k, as a direction's
 // bits may not, and both precisions go one way, so that only one path's arrays
-// are uploaded: the line is where no case is slower.
+// are uploaded: the line is where no call on one network is slower.
+// In a batch the tree path reads every network's matrices (30 to 40 MB, three
+// times the other path's records), however few directions there are, while
+// the other has a CU for each of 256.  At 16,054 states:
+//   networks x directions    2 x 1      6 x 1      8 x 1      12 x 1     4 x 64     6 x 64
+//   FP64                   269 | 175  275 | 240  278 | 288  343 | 344  274 | 288  506 | 351
+//   refined                582 | 359  593 | 558  597 | 679  733 | 837  636 | 685  1201 | 875
+// So more than about eight networks of this size with a few directions each are
+// faster on the other path (32 x 1 at 18,599 states: 515 | 810, refined 1107 |
+// 2187), which the networks' other calls pay for there.
 constexpr int32_t kTreeMinStates = 16000;
 
 bool tree_wanted(const Network &net) {

@@ -1606,7 +1606,6 @@ rh_status tree_upload(Network &net, const double *d_factors, bool *used, std::st
   return s;
 }
 
-// Barrier-separated steps: a node's products, tier after tier.
 void tree_steps(const DevTree *t, int32_t &fwd, int32_t &bwd) { fwd = bwd = t->d.n_tiers; }
 
 void device_tree_free(Network &net) {

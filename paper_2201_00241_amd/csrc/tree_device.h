@@ -83,8 +83,7 @@ struct DevTree;  // a network's plan and device arrays (tree.hip)
 // factors when they are on the device already, else null.  RH_ENOMEM: there is
 // no memory for it, and nothing is kept.
 rh_status tree_upload(Network &net, const double *d_factors, bool *used, std::string &err);
-// Barrier-separated steps of a forward and a backward sweep, along the
-// tiers' longest nodes.
+// Launches of a forward and a backward sweep: the tiers.
 void tree_steps(const DevTree *t, int32_t &fwd, int32_t &bwd);
 int64_t tree_bytes(const DevTree *t);
 
